@@ -132,15 +132,17 @@ GP_API gp_status gp_substep_nonlinear(gp_plan_t* p, void* psi, double s);
 
 /* nsteps Strang steps of dt (nsteps < 0: |nsteps| steps of -dt), in place:
  * psi <- [L(dt/2) N(dt) L(dt/2)]^n psi with L = L_x L_y L_z (eq. adi_looptime).
- * Adjacent half steps are merged and the nonlinear rotation is fused into the
- * following x pass: 3 (|n| + 1) axis passes, each reading and writing psi once. */
+ * Adjacent half steps are merged, and the steps take the (commuting) axes in
+ * alternating order, so that each nonlinear rotation runs inside one pass between two
+ * sub-steps along one axis: 2 (|n| + 1) + 1 passes, each reading and writing psi once
+ * (|n| + 2 with two axes longer than 1 or the xy-plane pass). */
 GP_API gp_status gp_step_n(gp_plan_t* p, void* psi, int64_t nsteps);
 
 /* The same steps in the literal 3-D form: 3-D FFT, multiply by
  * exp(-i alpha |k|^2 dt/2), inverse 3-D FFT, nonlinear rotation, and again
  * (the wording of the spectral sub-step).  The multiplier is applied by the last
  * forward pass before it stores: 13 sweeps of the state per step (26 N^3 S bytes),
- * against 3 (6 N^3 S) for gp_step_n. */
+ * against 2 (4 N^3 S) for gp_step_n. */
 GP_API gp_status gp_step_literal_n(gp_plan_t* p, void* psi, int64_t nsteps);
 
 /* 3-D transform: dir = -1 forward with 1/N^3 (c_k = N^-3 sum_x psi e^{-ik.x}),
@@ -276,13 +278,13 @@ GP_API gp_status gp_argle_run(gp_plan_t* p, void* phi, const void* v, double dta
                               int64_t check_every, double eps, void* work, gp_argle_report* report);
 
 /* Ensemble: advance run i's state psis[i] (host array of dev pointers) by nsteps
- * (negative: backward).  The merged sequence L(h) [N L(dt)]^(n-1) N L(h) runs as
- * recorded HIP graphs: the opening half step, bodies of 2^j applications
- * (j = 0..7; the 128-application body repeated, the rest by the binary digits of
- * n - 1) and the closing half step.  Each graph holds one grouped launch per size
+ * (negative: backward).  The merged sequence L(h) [N L(dt)]^(n-1) N L(h), in the
+ * alternating order of gp_step_n, runs as recorded HIP graphs: its beginning, bodies
+ * of 2^j steps (j = 0..7; the 128-step body repeated, the rest by the binary digits
+ * of n - 2) and its end.  Each graph holds one grouped launch per size
  * group and pass, the size groups on parallel branches; a graph is recorded on
  * first use for the given states and replayed after, so a call launches at most
- * 2 + 7 + (n-1)/128 graphs of at most 3 x 128 launches per group, whatever n.
+ * 2 + 7 + (n-2)/128 graphs of at most 2 x 128 launches per group, whatever n.
  * New state pointers, gp_autotune or gp_select_variant drop the recorded graphs. */
 GP_API gp_status gp_step_n_batch(gp_plan_t* p, void* const* psis, int64_t nsteps);
 
@@ -307,12 +309,14 @@ GP_API const char* gp_schedule_name(const gp_plan_t* p, int32_t axis);
  * axis 3 selects how the two in-plane sub-steps run in gp_step_n and
  * gp_step_n_batch: variant 0 = separate x and y passes, 1 = one xy-plane pass per
  * z-plane (both sub-steps on chip, psi read and written once; the x and y factors
- * commute, time-evolution section).  Variant 1 needs nx == ny with a compiled
+ * commute, time-evolution section); a step is then one sweep.  Variant 1 needs nx == ny with a compiled
  * plane length (complex64: 16..96, complex128: 16..64); otherwise
  * GP_ERR_UNSUPPORTED.  axis 4 (single plans, separate passes) selects the axis pass
- * that carries the nonlinear rotation as its prologue and runs first in each
- * linear step (variant 0, 1, 2 = x, y, z; the linear sub-steps commute, so any
- * order is the same split step); default: the first axis of length > 1.  axis 5
+ * that comes first and carries the first nonlinear rotations (variant 0, 1, 2 = x, y,
+ * z; the linear sub-steps commute, so any order is the same split step): the
+ * rotations lie in the passes of that axis and of the last of the others in x, y, z
+ * order, in turn; default: the first axis of length > 1 (grids with ny = nz beyond the
+ * last-level cache: y).  axis 5
  * (single cubic plans) selects the form of the linear steps of gp_step_n: variant
  * 0 (default) the fixed layout, every pass in place; variant v = 1..R (R compiled
  * rotating schedules for the length) the v-th rotating schedule: layout-rotating

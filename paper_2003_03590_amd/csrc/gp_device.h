@@ -196,19 +196,25 @@ namespace ct {
 constexpr double inv_fact(int n) { double f = 1.0; for (int i = 2; i <= n; ++i) f *= double(i); return 1.0 / f; }
 }  // namespace ct
 
+constexpr double kSmallAngle = 0.0625;
+
+__device__ __forceinline__ void sincos_small(double a, double* sn, double* cs) {
+  const double r2 = a * a;
+  double ps = ct::inv_fact(9);
+  ps = fma(ps, r2, -ct::inv_fact(7));
+  ps = fma(ps, r2, ct::inv_fact(5));
+  ps = fma(ps, r2, -ct::inv_fact(3));
+  *sn = fma(ps * r2, a, a);
+  double pc = ct::inv_fact(8);
+  pc = fma(pc, r2, -ct::inv_fact(6));
+  pc = fma(pc, r2, ct::inv_fact(4));
+  pc = fma(pc, r2, -0.5);
+  *cs = fma(pc, r2, 1.0);
+}
+
 __device__ __forceinline__ void sincos_rot(double a, double* sn, double* cs) {
-  if (fabs(a) <= 0.0625) {
-    const double r2 = a * a;
-    double ps = ct::inv_fact(9);
-    ps = fma(ps, r2, -ct::inv_fact(7));
-    ps = fma(ps, r2, ct::inv_fact(5));
-    ps = fma(ps, r2, -ct::inv_fact(3));
-    *sn = fma(ps * r2, a, a);
-    double pc = ct::inv_fact(8);
-    pc = fma(pc, r2, -ct::inv_fact(6));
-    pc = fma(pc, r2, ct::inv_fact(4));
-    pc = fma(pc, r2, -0.5);
-    *cs = fma(pc, r2, 1.0);
+  if (fabs(a) <= kSmallAngle) {
+    sincos_small(a, sn, cs);
   } else if (fabs(a) < 1024.0) {
     const double q = rint(a * 0.6366197723675814);
     double r = fma(-q, 1.5707963267948966, a);
@@ -282,13 +288,16 @@ __device__ __forceinline__ void sincos_rot(float a, float* sn, float* cs) {
 // O(u a), where fl(cos a) + i fl(sin a) is off by up to u -- for |a| below
 // ~2.4e-4, fl(cos a) = 1 while sin a != 0 -- a gain that repeats at a point
 // every step with the slowly varying angle and so adds up coherently.
+__device__ __forceinline__ void sincos_m1_small(float a, float* sn, float* cm1) {
+  const float r2 = a * a;
+  const float ps = fmaf(float(ct::inv_fact(5)), r2, float(-ct::inv_fact(3)));
+  *sn = fmaf(ps * r2, a, a);
+  const float pc = fmaf(float(ct::inv_fact(4)), r2, -0.5f);
+  *cm1 = pc * r2;
+}
 __device__ __forceinline__ void sincos_m1(float a, float* sn, float* cm1) {
-  if (fabsf(a) <= 0.0625f) {
-    const float r2 = a * a;
-    const float ps = fmaf(float(ct::inv_fact(5)), r2, float(-ct::inv_fact(3)));
-    *sn = fmaf(ps * r2, a, a);
-    const float pc = fmaf(float(ct::inv_fact(4)), r2, -0.5f);
-    *cm1 = pc * r2;
+  if (fabsf(a) <= float(kSmallAngle)) {
+    sincos_m1_small(a, sn, cm1);
   } else {
     float sh, ch;
     sincos_rot(0.5f * a, &sh, &ch);

@@ -5,6 +5,8 @@
 //                                                  or a spectral derivative with m = i k_j / N_j)
 //   FWD : v <- scale * F_j v        (natural frequency order out)
 //   INV : v <- scale * F_j^-1 v     (natural frequency order in, unnormalised inverse)
+//   TURN: v <- S_2 P S_1 v, S_1 and S_2 two propagator sub-steps along the same axis and P
+//         the pointwise sub-step between them (see below)
 // with optional pointwise prologues (the nonlinear sub-step S(dt, N), its adjoint, the
 // density rho - 1) fused in front of the transform.
 //
@@ -16,6 +18,13 @@
 // that order and runs the exact inverse (conjugate-twiddle DIT) stages in reverse, so
 // no reordering pass is ever needed.  W pencils share one workgroup; for the strided
 // axes (y, z) the W pencils are x-adjacent so each global access is a W*S-byte row.
+//
+// TURN: the linear sub-steps of one time step commute, so a run may take the axes of its
+// steps in alternating order (x y z | z y x | x y z ...).  Then the last sub-step of one
+// step, the nonlinear rotation and the first sub-step of the next act on the same
+// pencils and run in one pass, without psi leaving the registers in between: a step
+// reads and writes psi twice instead of three times (once for two axes or with the
+// xy-plane pass).
 //
 // Table layouts (built on the host for the schedule in use): every table load of one
 // instruction reads consecutive entries across the lanes, so it costs a few vector-L1
@@ -42,22 +51,36 @@ __device__ __forceinline__ const GPK_GLOBAL X* gptr(const void* p) { return (con
 template <class X>
 __device__ __forceinline__ GPK_GLOBAL X* gptr_mut(void* p) { return (GPK_GLOBAL X*)p; }
 
+// A table pointer the compiler cannot tell from another: two sub-steps in one kernel read
+// their twiddles from the same table, and keeping a stage's 15 to 31 entries from the first
+// for the second costs 60 to 120 registers a lane (1024 points: spills to scratch memory).
+__device__ __forceinline__ const void* reload(const void* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+s"(p));
+#endif
+  return p;
+}
+
 enum PassKind { CONTIG = 0, STRIDED = 1 };
-enum PassMode { PROP = 0, FWD = 1, INV = 2 };
+enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
 // pointwise work fused in front of the transform (PRO_KIN: none, but accumulate
 // sum k_j^2 |F_j v|^2 after the forward transform for the kinetic energy;
 // PRO_ARGLE: none, but turn the derivative after the inverse transform into the
 // explicit part of the imaginary-time step; PRO_MULT3: none, but multiply the
 // forward transform by the separable 3-D propagator m_x(k_x) m_y(k_y) m_z(k_z) before
 // it is stored -- the last forward pass of the literal 3-D form)
-enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DENSITY = 3, PRO_KIN = 4, PRO_ARGLE = 5, PRO_MULT3 = 6 };
+// In a TURN pass: the work between its two sub-steps (PRO_NL, PRO_ADJ_NL, or PRO_TAPE:
+// store the state there as well, then rotate it).  PRO_SWAP: none; the pass exchanges the
+// two outer axes of the layout (see pencil_pair).
+enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DENSITY = 3, PRO_KIN = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
+                PRO_TAPE = 7, PRO_SWAP = 8 };
 
 // per-run pointers of a grouped (ensemble) launch: run = blockIdx.y
 struct RunPtrs {
   const void* in;
   void* out;
   const void* mult;
-  const void* mult2;       // plane pass: the y multipliers (mult holds the x ones)
+  const void* mult2;       // turning passes: the multipliers of the second sub-step
   double nl_coef;
 };
 
@@ -66,11 +89,13 @@ struct PassArgs {
   const void* in;          // input field (complex, working precision)
   void* out;               // output field (may equal in)
   const void* mult;        // PROP: multiplier in lane order (N_j FP64 complex entries)
+  const void* mult2;       // TURN: multiplier of the second sub-step
   const void* tw;          // per-stage twiddles W_{R M}^{lo k} (Tab<Real> entries, layout above)
   const void* aux;         // PRO_ADJ_NL, PRO_ARGLE: the state phi at the same points;
                            // PRO_MULT3: m_x in natural frequency order (FP64 complex)
   const void* aux2;        // PRO_ARGLE: d phi / dx and d phi / dy at the same points;
   const void* aux3;        // PRO_MULT3: m_y and m_z
+  void* tape;              // PRO_TAPE: where the state between the sub-steps is stored
   const void* vel;         // PRO_ARGLE: velocity planes v_x, v_y, v_z (Real, one field each)
   double q4a;              // PRO_ARGLE: 1 / (4 alpha)
   const double* ksq;       // k_j^2 in position order (kinetic accumulation)
@@ -81,7 +106,7 @@ struct PassArgs {
   long inner, outer;       // pencil p starts at (p / inner) * outer + (p % inner)
   long es;                 // element stride along the axis
   int axis;                // PRO_MULT3: the pass's axis (0 x, 1 y, 2 z) ...
-  int nx, ny;              // ... and the grid's x and y lengths
+  int nx, ny;              // ... and the grid's x and y lengths (PRO_SWAP: ny = nz)
 };
 
 template <int N_, int T_, int W_, int R0, int R1, int R2>
@@ -327,35 +352,107 @@ __device__ __forceinline__ void store_tile_wide(const cplx<float>* v, cplx<float
   }
 }
 
-// nonlinear sub-step S(dt, N): v <- v exp(-i beta (|v|^2 - 1) dt), in the working precision
-template <class Real>
-__device__ __forceinline__ cplx<Real> nl_rotate(cplx<Real> v, double coef) {
-  Real s, c;
-  sincos_rot(-Real(coef) * (cabs2(v) - Real(1)), &s, &c);
+// PRO_SWAP (x passes of grids with n = ny = nz, n even): pencil (z, y) is written where
+// pencil (y, z) was and the reverse, in place, so the layout goes from [z][y][x] to
+// [y][z][x] and back with the next such pass.  The axis that then has the stride nx can be
+// transformed with rows that lie nx points apart instead of nx ny: at 1024^3 complex64 every
+// row of a z tile falls in a memory page of its own and the turning pass takes 10.6 ms,
+// against 7.0 with the y stride, while this pass still moves whole contiguous pencils.
+// A tile holds W / 2 pairs {(i, j), (j, i)}, i <= j (a pencil of the diagonal fills both
+// places, with equal bytes), which it has read completely before it writes.  Pairs
+// are counted along row i together with row n - 1 - i, n + 1 pairs for the two.
+__device__ __forceinline__ void pencil_pair(unsigned u, unsigned n, unsigned& i, unsigned& j) {
+  const unsigned r = u / (n + 1), c = u % (n + 1);
+  if (c < n - r) { i = r; j = r + c; }
+  else { i = n - 1 - r; j = i + (c - (n - r)); }
+}
+
+// nonlinear sub-step S(dt, N): v <- v exp(-i beta (|v|^2 - 1) dt), in the working precision.
+// SMALL: the angle is known to be within the short series' range.
+template <bool SMALL>
+__device__ __forceinline__ cplx<double> nl_rotate(cplx<double> v, double coef) {
+  double s, c;
+  const double a = -coef * (cabs2(v) - 1.0);
+  if constexpr (SMALL) sincos_small(a, &s, &c);
+  else sincos_rot(a, &s, &c);
   return cmul(v, mk(c, s));
 }
 // FP32: v + v (cos a - 1 + i sin a), see sincos_m1; the small correction is formed
 // first, so the result carries one rounding at the size of v
-template <>
-__device__ __forceinline__ cplx<float> nl_rotate<float>(cplx<float> v, double coef) {
+template <bool SMALL>
+__device__ __forceinline__ cplx<float> nl_rotate(cplx<float> v, double coef) {
   float s, cm1;
-  sincos_m1(-float(coef) * (cabs2(v) - 1.0f), &s, &cm1);
+  const float a = -float(coef) * (cabs2(v) - 1.0f);
+  if constexpr (SMALL) sincos_m1_small(a, &s, &cm1);
+  else sincos_m1(a, &s, &cm1);
   const float dx = fmaf(v.x, cm1, -v.y * s), dy = fmaf(v.y, cm1, v.x * s);
   return mk(v.x + dx, v.y + dy);
 }
 
 // adjoint of the linearised nonlinear sub-step at phi:
 //   lam <- conj(u) lam + 2 beta dt Im(conj(lam) u phi) phi,  u = exp(-i beta (|phi|^2-1) dt)
-template <class Real>
+template <bool SMALL, class Real>
 __device__ __forceinline__ cplx<Real> nl_adjoint(cplx<Real> lam, cplx<Real> phi, Real coef) {
   Real s, c;
-  sincos_rot(-coef * (cabs2(phi) - Real(1)), &s, &c);
+  const Real a = -coef * (cabs2(phi) - Real(1));
+  if constexpr (SMALL) sincos_small(a, &s, &c);
+  else sincos_rot(a, &s, &c);
   const cplx<Real> u = mk(c, s);
   const cplx<Real> up = cmul(u, phi);
   const Real im = lam.x * up.y - lam.y * up.x;          // Im(conj(lam) * up)
   const cplx<Real> r = cmulc(lam, u);                    // conj(u) lam
   const Real f = Real(2) * coef * im;
   return mk(r.x + f * phi.x, r.y + f * phi.y);
+}
+
+// The rotations of all points a lane holds.  One branch for the lane: the angle
+// beta (|v|^2 - 1) dt stays within the short series in every run of the method, and that
+// path is straight code for all points.  Otherwise the points take the general routine
+// one after another in a rolled loop that turns the register array by one place.
+// (Unrolled with the general routine at every point, its code was 35 KB of a 43 KB
+// kernel at 256 points complex128, 45 of 65 KB at 1024 points complex64, beside a
+// 64 KB instruction cache that two compute units share: the turning pass took 13.7 ms
+// at 1024^3 where the plain pass takes 3.6.)
+template <class Real>
+__device__ __forceinline__ bool angle_small(cplx<Real> v, Real coef) {
+  return fabs(coef * (cabs2(v) - Real(1))) <= Real(kSmallAngle);    // false for a NaN
+}
+template <int E, class Real>
+__device__ __forceinline__ void rotate_points(cplx<Real>* v, double coef) {
+  bool small = true;
+#pragma unroll
+  for (int e = 0; e < E; ++e) small = small && angle_small(v[e], Real(coef));
+  if (small) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = nl_rotate<true>(v[e], coef);
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < E; ++i) {
+      const cplx<Real> x = nl_rotate<false>(v[0], coef);
+#pragma unroll
+      for (int e = 0; e + 1 < E; ++e) v[e] = v[e + 1];
+      v[E - 1] = x;
+    }
+  }
+}
+// the same for the adjoint at the states phi
+template <int E, class Real>
+__device__ __forceinline__ void rotate_adjoint(cplx<Real>* v, cplx<Real>* phi, Real coef) {
+  bool small = true;
+#pragma unroll
+  for (int e = 0; e < E; ++e) small = small && angle_small(phi[e], coef);
+  if (small) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = nl_adjoint<true>(v[e], phi[e], coef);
+  } else {
+#pragma unroll 1
+    for (int i = 0; i < E; ++i) {
+      const cplx<Real> x = nl_adjoint<false>(v[0], phi[0], coef);
+#pragma unroll
+      for (int e = 0; e + 1 < E; ++e) { v[e] = v[e + 1]; phi[e] = phi[e + 1]; }
+      v[E - 1] = x;
+    }
+  }
 }
 
 template <class Real, class S, int KIND, int MODE, int PRO>
@@ -367,7 +464,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
 
   if (a.batch) {                          // uniform per workgroup
     const RunPtrs r = a.batch[blockIdx.y];
-    a.in = r.in; a.out = r.out; a.mult = r.mult; a.nl_coef = r.nl_coef;
+    a.in = r.in; a.out = r.out; a.mult = r.mult; a.mult2 = r.mult2; a.nl_coef = r.nl_coef;
   }
   const int tid = threadIdx.x;
   int t, col;
@@ -423,28 +520,51 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
   // x pencils of complex64 propagator passes: whole tiles of contiguous pencils,
   // moved with 16-byte accesses (a pencil past the last one takes the last one, as
   // the lanes do, so the duplicate stores write equal bytes)
-  constexpr bool WIDE = sizeof(Real) == 4 && KIND == CONTIG && MODE == PROP &&
-                        (PRO == PRO_NONE || PRO == PRO_NL) && wide_io<S>();
+  constexpr bool WIDE = sizeof(Real) == 4 && KIND == CONTIG && (MODE == PROP || MODE == TURN) &&
+                        (PRO == PRO_NONE || PRO == PRO_NL || PRO == PRO_SWAP) && wide_io<S>();
+  // first point of pencil pc of the tile, as it is read and as it is written
+  auto swap_pencil = [&](int pc, bool written) {
+    const unsigned n = (unsigned)a.ny, last = n * (n + 1) / 2 - 1;
+    const unsigned u = (unsigned)tile * (W / 2) + (unsigned)pc / 2;
+    unsigned i, j;
+    pencil_pair(u < last ? u : last, n, i, j);
+    return (long)((((pc & 1) != 0) != written) ? j * n + i : i * n + j) * S::N;
+  };
   auto tile_pencil = [&](int pc) {
+    if constexpr (PRO == PRO_SWAP) return swap_pencil(pc, false);
     const long p = tile * W + pc;
     return (p < a.npencils ? p : a.npencils - 1) * (long)S::N;
+  };
+  auto out_pencil = [&](int pc) {
+    if constexpr (PRO == PRO_SWAP) return swap_pencil(pc, true);
+    else return tile_pencil(pc);
+  };
+
+  // nonlinear sub-step (or its adjoint) on the points the lane holds
+  auto rotate = [&](C* v, const Where& cur) {
+    if constexpr (PRO == PRO_NL || PRO == PRO_TAPE) {
+      rotate_points<E>(v, a.nl_coef);
+    } else if constexpr (PRO == PRO_ADJ_NL) {
+      // a few points at a time: the tape's points beside all of the lane's own do not fit
+      // the registers
+      constexpr int CH = E % 4 == 0 ? 4 : E % 3 == 0 ? 3 : E % 2 == 0 ? 2 : 1;
+      const auto phib = gptr<char>(a.aux) + cur.bbase * (long)sizeof(C);
+#pragma unroll
+      for (int e0 = 0; e0 < E; e0 += CH) {
+        C f[CH];
+#pragma unroll
+        for (int e = 0; e < CH; ++e) f[e] = *(const GPK_GLOBAL C*)(phib + (e0 + e) * estep + cur.loff);
+        rotate_adjoint<CH>(v + e0, f, Real(a.nl_coef));
+      }
+    }
   };
 
   double kin_acc = 0.0;
   // transform one tile held in v (prologue, transform, multiplier, inverse) and store it
   auto process = [&](C* v, const Where& cur) {
-    if constexpr (MODE != INV) {
-      if constexpr (PRO == PRO_NL) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = nl_rotate(v[e], a.nl_coef);
-      } else if constexpr (PRO == PRO_ADJ_NL) {
-        const auto phib = gptr<char>(a.aux) + cur.bbase * (long)sizeof(C);
-        const Real coef = Real(a.nl_coef);
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-          const C f = *(const GPK_GLOBAL C*)(phib + e * estep + cur.loff);
-          v[e] = nl_adjoint(v[e], f, coef);
-        }
+    if constexpr (MODE == PROP || MODE == FWD) {
+      if constexpr (PRO == PRO_NL || PRO == PRO_ADJ_NL) {
+        rotate(v, cur);
       } else if constexpr (PRO == PRO_DENSITY) {
 #pragma unroll
         for (int e = 0; e < E; ++e) v[e] = mk(cabs2(v[e]) - Real(1), Real(0));
@@ -457,6 +577,27 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
       const Real sc = Real(a.scale);
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = cscale(v[e], sc);
+    } else if constexpr (MODE == TURN) {
+      constexpr int L = S::NS - 1, B = E / S::rad(L);
+      auto substep = [&](const void* table) {
+        const auto tw = gptr<Tab<Real>>(reload(a.tw));
+        const auto m = gptr<cplx<double>>(table);
+        forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
+#pragma unroll
+        for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+          for (int j = 0; j < B; ++j)
+            v[j + B * r] = pmul(v[j + B * r], tab_at(m, r * (S::N / S::rad(L)) + t + T * j));
+        inverse_all<Real, S, KIND, L>(v, lds, t, col, tw);
+      };
+      substep(a.mult);
+      if constexpr (PRO == PRO_TAPE) {
+        const auto tb = gptr_mut<char>(a.tape) + cur.bbase * (long)sizeof(C);
+#pragma unroll
+        for (int e = 0; e < E; ++e) *(GPK_GLOBAL C*)(tb + e * estep + cur.loff) = v[e];
+      }
+      rotate(v, cur);
+      substep(a.mult2);
     } else {
       forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
       constexpr int L = S::NS - 1;
@@ -523,7 +664,11 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     }
 
     if constexpr (WIDE) {
-      store_tile_wide<S>(v, lds, a.out, tile_pencil, t, col);
+      store_tile_wide<S>(v, lds, a.out, out_pencil, t, col);
+    } else if constexpr (PRO == PRO_SWAP) {
+      const auto dst = gptr_mut<C>(a.out) + out_pencil(col) + t;
+#pragma unroll
+      for (int e = 0; e < E; ++e) dst[T * e] = v[e];
     } else {
       const auto outb = gptr_mut<char>(a.out) + cur.bbase * (long)sizeof(C);
 #pragma unroll
@@ -534,7 +679,11 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
   C v[E];
   const Where w = where(tile);
   if constexpr (WIDE) load_tile_wide<S>(v, lds, a.in, tile_pencil, t, col);
-  else load(v, w);
+  else if constexpr (PRO == PRO_SWAP) {
+    const auto src = gptr<C>(a.in) + tile_pencil(col) + t;
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = src[T * e];
+  } else load(v, w);
   process(v, w);
 
   if constexpr (PRO == PRO_KIN) {
@@ -562,6 +711,6 @@ void launch_pass(const PassArgs& a, unsigned grid, unsigned runs, hipStream_t st
 
 // kernel variants compiled for every schedule
 enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_PROP_KIN, V_FWD, V_FWD_DENSITY, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
-               V_COUNT };
+               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_COUNT };
 
 }  // namespace gpk

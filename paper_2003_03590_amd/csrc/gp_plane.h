@@ -6,9 +6,12 @@
 // enough to stay on chip: the rows are loaded from global memory and transformed
 // with the row (contiguous) mapping of the axis pass, written to LDS in natural
 // order, read back as columns and transformed with the column (strided) mapping,
-// then stored.  A Strang step then costs two sweeps of psi (this pass and the
-// z pass) instead of three.  The transform stages, tables and the nonlinear
-// prologue are those of the axis pass (same schedule type, W = N).
+// then stored.  The transform stages, tables and the nonlinear prologue are those of
+// the axis pass (same schedule type, W = N).
+//
+// TURN: the plane's sub-steps end one time step and begin the next (gp_pass.h), rows,
+// columns, nonlinear rotation, columns, rows in one launch.  With the z pass turning
+// as well, a step is one sweep of psi and one launch.
 #pragma once
 
 #include "gp_pass.h"
@@ -16,89 +19,103 @@
 namespace gpk {
 
 struct PlaneArgs {
-  const RunPtrs* batch;    // grouped launch over runs of one size (mult = x, mult2 = y), or null
+  const RunPtrs* batch;    // grouped launch over runs of one size, or null
   const void* in;
   void* out;
-  const void* multx;       // FP64 complex multipliers in the plane schedule's lane order
-  const void* multy;
+  const void* mult;        // FP64 complex multipliers in the plane schedule's lane order (x and
+                           // y share them: one length, one alpha)
+  const void* mult2;       // TURN: multipliers of the second time step
   const void* tw;          // per-stage twiddles of the plane schedule (Tab<Real>)
-  double nl_coef;          // beta * dt for the fused nonlinear prologue
+  double nl_coef;          // beta * dt for the fused nonlinear rotation
 };
 
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 
-template <class Real, class S, int PRO>
+template <class Real, class S, int MODE, int PRO>
 __global__ __launch_bounds__(S::THREADS) void plane_pass(PlaneArgs a) {
-  static_assert(S::W == S::N, "a plane workgroup holds all N rows");
+  static_assert(S::W == S::N && S::NS > 1, "a plane workgroup holds all N rows; the stage exchanges order its LDS use");
   using C = cplx<Real>;
   constexpr int N = S::N, T = S::T, E = S::E;
   // plane row pitch in LDS: rows that share an LDS cycle in the row-major write get
   // their own banks (the column reads take consecutive points of one row)
-  constexpr int SZ = (int)sizeof(C), TLX = lanes_per_pencil<S, SZ>();
-  constexpr int P = (TLX < 128 / SZ) ? row_pitch<SZ>(N, TLX) : N + 1;
+  constexpr int SZ = (int)sizeof(C), TL = lanes_per_pencil<S, SZ>();
+  constexpr int P = (TL < 128 / SZ) ? row_pitch<SZ>(N, TL) : N + 1;
   constexpr int L = S::NS - 1, B = E / S::rad(L);
   constexpr int EX = Lds<S, (int)sizeof(C), CONTIG>::ELEMS, EY = Lds<S, (int)sizeof(C), STRIDED>::ELEMS;
   // one buffer serves the row exchanges, the plane and the column exchanges in turn
   __shared__ C lds[cmax(cmax(EX, EY), N * P)];
 
-  const void* multx = a.multx;
-  const void* multy = a.multy;
   if (a.batch) {                          // uniform per workgroup
     const RunPtrs r = a.batch[blockIdx.y];
-    a.in = r.in; a.out = r.out; multx = r.mult; multy = r.mult2; a.nl_coef = r.nl_coef;
+    a.in = r.in; a.out = r.out; a.mult = r.mult; a.mult2 = r.mult2; a.nl_coef = r.nl_coef;
   }
   const int tid = threadIdx.x;
   const long base = (long)blockIdx.x * N * N;   // first point of this z-plane
-  const auto tw = gptr<Tab<Real>>(a.tw);
+  // lane (tr, row) of the row mapping, lane (tc, col) of the column mapping
+  const int tr = tid % TL + TL * (tid / (TL * N)), row = (tid / TL) % N;
+  const int tc = tid / N, col = tid % N;
   C v[E];
 
-  {  // rows: S(s, L_x) (with the nonlinear prologue)
-    constexpr int TL = TLX;
-    const int t = tid % TL + TL * (tid / (TL * N));
-    const int row = (tid / TL) % N;
-    const auto src = gptr<C>(a.in) + base + (long)row * N + t;
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = src[T * e];
-    if constexpr (PRO == PRO_NL) {
-#pragma unroll
-      for (int e = 0; e < E; ++e) v[e] = nl_rotate(v[e], a.nl_coef);
-    }
-    forward_all<Real, S, CONTIG, 0>(v, lds, t, row, tw);
-    const auto m = gptr<cplx<double>>(multx);
+  auto rotate = [&] { rotate_points<E>(v, a.nl_coef); };
+  auto multiply = [&](const void* table, int t) {
+    const auto m = gptr<cplx<double>>(table);
 #pragma unroll
     for (int r = 0; r < S::rad(L); ++r)
 #pragma unroll
       for (int j = 0; j < B; ++j) v[j + B * r] = pmul(v[j + B * r], m[(unsigned)(r * (N / S::rad(L)) + t + T * j)]);
-    inverse_all<Real, S, CONTIG, L>(v, lds, t, row, tw);
-    __syncthreads();                       // the last row exchange has been read
+  };
+  auto rows = [&](const void* table) {    // S(s, L_x)
+    const auto tw = gptr<Tab<Real>>(reload(a.tw));
+    forward_all<Real, S, CONTIG, 0>(v, lds, tr, row, tw);
+    multiply(table, tr);
+    inverse_all<Real, S, CONTIG, L>(v, lds, tr, row, tw);
+  };
+  auto columns = [&](const void* table) { // S(s, L_y)
+    const auto tw = gptr<Tab<Real>>(reload(a.tw));
+    // the first exchange starts with a barrier: every read of the plane is done by then
+    forward_all<Real, S, STRIDED, 0>(v, lds, tc, col, tw);
+    multiply(table, tc);
+    inverse_all<Real, S, STRIDED, L>(v, lds, tc, col, tw);
+  };
+
+  const auto src = gptr<C>(a.in) + base + (long)row * N + tr;
 #pragma unroll
-    for (int e = 0; e < E; ++e) lds[row * P + t + T * e] = v[e];
-  }
+  for (int e = 0; e < E; ++e) v[e] = src[T * e];
+  if constexpr (MODE == PROP && PRO == PRO_NL) rotate();
+  rows(a.mult);
+  __syncthreads();                         // the last row exchange has been read
+#pragma unroll
+  for (int e = 0; e < E; ++e) lds[row * P + tr + T * e] = v[e];
   __syncthreads();
-  {  // columns: S(s, L_y)
-    const int col = tid % N;
-    const int t = tid / N;
 #pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = lds[(t + T * e) * P + col];
-    // the first column exchange starts with a barrier: every plane read is done by then
-    forward_all<Real, S, STRIDED, 0>(v, lds, t, col, tw);
-    const auto m = gptr<cplx<double>>(multy);
-#pragma unroll
-    for (int r = 0; r < S::rad(L); ++r)
-#pragma unroll
-      for (int j = 0; j < B; ++j) v[j + B * r] = pmul(v[j + B * r], m[(unsigned)(r * (N / S::rad(L)) + t + T * j)]);
-    inverse_all<Real, S, STRIDED, L>(v, lds, t, col, tw);
+  for (int e = 0; e < E; ++e) v[e] = lds[(tc + T * e) * P + col];
+  if constexpr (MODE == PROP) {
+    columns(a.mult);
     const auto dst = gptr_mut<C>(a.out) + base + col;
 #pragma unroll
-    for (int e = 0; e < E; ++e) dst[(long)(t + T * e) * N] = v[e];
+    for (int e = 0; e < E; ++e) dst[(long)(tc + T * e) * N] = v[e];
+  } else {
+    columns(a.mult);
+    rotate();
+    columns(a.mult2);
+    __syncthreads();                       // the last column exchange has been read
+#pragma unroll
+    for (int e = 0; e < E; ++e) lds[(tc + T * e) * P + col] = v[e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < E; ++e) v[e] = lds[row * P + tr + T * e];
+    rows(a.mult2);
+    const auto dst = gptr_mut<C>(a.out) + base + (long)row * N + tr;
+#pragma unroll
+    for (int e = 0; e < E; ++e) dst[T * e] = v[e];
   }
 }
 
 using PlaneLauncher = void (*)(const PlaneArgs&, unsigned planes, unsigned runs, hipStream_t stream);
 
-template <class Real, class S, int PRO>
+template <class Real, class S, int MODE, int PRO>
 void launch_plane(const PlaneArgs& a, unsigned planes, unsigned runs, hipStream_t stream) {
-  hipLaunchKernelGGL((plane_pass<Real, S, PRO>), dim3(planes, runs), dim3(S::THREADS), 0, stream, a);
+  hipLaunchKernelGGL((plane_pass<Real, S, MODE, PRO>), dim3(planes, runs), dim3(S::THREADS), 0, stream, a);
 }
 
 }  // namespace gpk

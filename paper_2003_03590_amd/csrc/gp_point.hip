@@ -90,7 +90,7 @@ template <class Real>
 __global__ void k_nonlinear(void* psi, long n, double coef) {
   cplx<Real>* p = reinterpret_cast<cplx<Real>*>(psi);
   for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x)
-    p[i] = nl_rotate(p[i], coef);
+    p[i] = nl_rotate<false>(p[i], coef);
 }
 
 template <class Real>

@@ -26,7 +26,7 @@ struct PlaneEntry {
   int n, prec;
   int T, NS, threads;
   int radix[3];
-  PlaneLauncher fn[2];           // [0] propagator, [1] with the nonlinear prologue
+  PlaneLauncher fn[3];           // [0] propagator, [1] with the nonlinear prologue, [2] turning
 };
 
 std::vector<PlaneEntry>& plane_registry();
@@ -42,8 +42,9 @@ PlaneEntry make_plane_entry(int prec) {
   e.n = S::N; e.prec = prec;
   e.T = S::T; e.NS = S::NS; e.threads = S::THREADS;
   for (int s = 0; s < 3; ++s) e.radix[s] = s < S::NS ? S::rad(s) : 1;
-  e.fn[0] = &launch_plane<Real, S, PRO_NONE>;
-  e.fn[1] = &launch_plane<Real, S, PRO_NL>;
+  e.fn[0] = &launch_plane<Real, S, PROP, PRO_NONE>;
+  e.fn[1] = &launch_plane<Real, S, PROP, PRO_NL>;
+  e.fn[2] = &launch_plane<Real, S, TURN, PRO_NL>;
   return e;
 }
 
@@ -55,13 +56,20 @@ template <class Real, class S, int KIND>
 void fill(PassEntry& e) {
   e.fn[KIND][V_PROP] = &launch_pass<Real, S, KIND, PROP, PRO_NONE>;
   e.fn[KIND][V_PROP_NL] = &launch_pass<Real, S, KIND, PROP, PRO_NL>;
-  e.fn[KIND][V_PROP_ADJ] = &launch_pass<Real, S, KIND, PROP, PRO_ADJ_NL>;
   e.fn[KIND][V_PROP_KIN] = &launch_pass<Real, S, KIND, PROP, PRO_KIN>;
   e.fn[KIND][V_FWD] = &launch_pass<Real, S, KIND, FWD, PRO_NONE>;
   e.fn[KIND][V_FWD_DENSITY] = &launch_pass<Real, S, KIND, FWD, PRO_DENSITY>;
   e.fn[KIND][V_INV] = &launch_pass<Real, S, KIND, INV, PRO_NONE>;
   e.fn[KIND][V_PROP_ARGLE] = &launch_pass<Real, S, KIND, PROP, PRO_ARGLE>;
   e.fn[KIND][V_FWD_MULT3] = &launch_pass<Real, S, KIND, FWD, PRO_MULT3>;
+  e.fn[KIND][V_TURN] = &launch_pass<Real, S, KIND, TURN, PRO_NL>;
+  // the stage exchanges order a swapping tile's reads before its writes
+  if constexpr (KIND == CONTIG && S::NS > 1) e.fn[KIND][V_PROP_SWAP] = &launch_pass<Real, S, KIND, PROP, PRO_SWAP>;
+  if constexpr (sizeof(Real) == 8) {           // the adjoint takes complex128 plans only
+    e.fn[KIND][V_PROP_ADJ] = &launch_pass<Real, S, KIND, PROP, PRO_ADJ_NL>;
+    e.fn[KIND][V_TURN_TAPE] = &launch_pass<Real, S, KIND, TURN, PRO_TAPE>;
+    e.fn[KIND][V_TURN_ADJ] = &launch_pass<Real, S, KIND, TURN, PRO_ADJ_NL>;
+  }
 }
 
 template <class Real, class S>

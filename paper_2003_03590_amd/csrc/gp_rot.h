@@ -64,8 +64,7 @@ __global__ __launch_bounds__(S::THREADS) void rot_pass(RotArgs a) {
   }
 
   if constexpr (PRO == PRO_NL) {
-#pragma unroll
-    for (int e = 0; e < E; ++e) v[e] = nl_rotate(v[e], a.nl_coef);
+    rotate_points<E>(v, a.nl_coef);
   }
   const auto tw = gptr<Tab<Real>>(a.tw);
   const auto mult = gptr<cplx<double>>(a.mult);

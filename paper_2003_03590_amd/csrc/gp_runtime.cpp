@@ -183,8 +183,7 @@ struct gp_plan_s {
     const PlaneEntry* e = nullptr;
     bool on = false;
     void* tw = nullptr;
-    void* mx[NTAU] = {};
-    void* my[NTAU] = {};
+    void* mult[NTAU] = {};
   } plane;
   // layout-rotating passes (cubic grids): every linear step as x, z, y passes that
   // turn the layout, out of place between psi and one state of workspace
@@ -203,9 +202,8 @@ struct gp_plan_s {
   std::vector<gp_plan_s*> runs;
   struct Group { int n; std::vector<int> members; RunPtrs* d_ptrs = nullptr; size_t nptrs = 0; };
   std::vector<Group> groups;
-  // recorded step graphs, [sign: 0 forward, 1 backward][slot]: slot 0 the opening
-  // half step L(h), 1 the closing [N, L(h)], 2 + j the body [N, L(dt)] x 2^j
-  static constexpr int GPOW = 8, GSLOTS = 2 + GPOW;
+  // recorded step graphs, [sign: 0 forward, 1 backward][slot] (batch_record)
+  static constexpr int GPOW = 8, GBODY = 4, GSLOTS = GBODY + GPOW;
   hipGraphExec_t gexec[2][GSLOTS] = {};
   std::vector<void*> graph_key;      // the states the recorded graphs and tables refer to
   std::vector<hipStream_t> side;     // capture branches of size groups 1, 2, ...
@@ -368,8 +366,8 @@ PassEntry plane_as_entry(const PlaneEntry& pe) {
   return e;
 }
 
-// twiddles and x/y multipliers of the plane schedule (built once per plan; with
-// nx == ny and one alpha the x and y multipliers are the same table)
+// twiddles and multipliers of the plane schedule (built once per plan; with nx == ny and
+// one alpha the x and y multipliers are the same table)
 gp_status build_plane_tables(gp_plan_s* p) {
   auto& P = p->plane;
   if (P.tw) return GP_OK;
@@ -389,8 +387,7 @@ gp_status build_plane_tables(gp_plan_s* p) {
       m[2 * i] = u.c / n;
       m[2 * i + 1] = -u.s / n;
     }
-    if ((st = upload_c128(p, &P.mx[t], m)) != GP_OK) return st;
-    P.my[t] = P.mx[t];
+    if ((st = upload_c128(p, &P.mult[t], m)) != GP_OK) return st;
   }
   return GP_OK;
 }
@@ -527,32 +524,135 @@ int first_real_axis(const gp_plan_s* p) {
   return -1;
 }
 
-// L(tau) on psi in place, the nonlinear rotation of coefficient nl (if any) fused in front
-// of the first pass
-gp_status linear_all(gp_plan_s* p, void* psi, int tau, bool with_nl, double nl) {
+// The sub-steps that make up L(tau): axis passes (0 x, 1 y, 2 z) or the xy-plane pass.
+// They commute; the axis that carries the first rotation comes first, the others in
+// x, y, z order.
+enum { STAGE_PLANE = 3 };
+struct Stages { int n = 0, id[3]; };
+
+Stages stages_of(const gp_plan_s* p) {
+  Stages s;
+  if (p->plane.on) {
+    s.id[s.n++] = STAGE_PLANE;
+    if (p->ax[2].n > 1) s.id[s.n++] = 2;
+    return s;
+  }
   const int c = first_real_axis(p);
+  const int carrier = (p->nl_axis >= 0 && p->ax[p->nl_axis].n > 1) ? p->nl_axis : c;
+  for (int a : {carrier, carrier == 0 ? 1 : 0, carrier == 2 ? 1 : 2})
+    if (a >= 0 && p->ax[a].n > 1) s.id[s.n++] = a;
+  return s;
+}
+
+const void* stage_mult(const gp_plan_s* p, int id, int tau) {
+  return id == STAGE_PLANE ? p->plane.mult[tau] : p->ax[id].mult[tau];
+}
+
+// How a stage runs: the sub-step alone, with the nonlinear rotation in front of it, or
+// turning (the sub-step, the rotation, and the sub-step of the next time step).
+enum StageMode { S_PLAIN = 0, S_NL = 1, S_TURN = 2 };
+
+// one stage on in -> out, or (ptrs not null) on `runs` runs at once
+void launch_stage(const gp_plan_s* p, int id, StageMode mode, const void* in, void* out, int tau, int tau2, double nl,
+                  const RunPtrs* ptrs, unsigned runs, hipStream_t st) {
+  if (id == STAGE_PLANE) {
+    PlaneArgs g{};
+    g.batch = ptrs; g.in = in; g.out = out; g.tw = p->plane.tw; g.nl_coef = nl;
+    g.mult = p->plane.mult[tau]; g.mult2 = p->plane.mult[tau2];
+    p->plane.e->fn[mode](g, (unsigned)p->d.n[2], runs, st);
+    return;
+  }
+  const Axis& A = p->ax[id];
+  PassArgs g{};
+  g.batch = ptrs; g.in = in; g.out = out; g.tw = A.tw; g.nl_coef = nl; g.scale = 1.0;
+  g.mult = A.mult[tau]; g.mult2 = A.mult[tau2];
+  g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
+  A.e->fn[A.kind][mode == S_PLAIN ? V_PROP : mode == S_NL ? V_PROP_NL : V_TURN](g, A.blocks, runs, st);
+}
+
+gp_status stage(gp_plan_s* p, int id, StageMode mode, void* psi, int tau, int tau2 = 0, double nl = 0.0) {
+  launch_stage(p, id, mode, psi, psi, tau, tau2, nl, nullptr, 1, p->stream);
+  return check_launch(p);
+}
+
+// L(tau) on psi in place
+gp_status linear_all(gp_plan_s* p, void* psi, int tau) {
+  const Stages q = stages_of(p);
   gp_status st;
-  if (c < 0) {   // 1x1x1 grid: only the nonlinear rotation acts (k = 0)
-    if (with_nl) { launch_nonlinear(p->prec, psi, p->ntot, nl, p->stream); return check_launch(p); }
+  for (int i = 0; i < q.n; ++i)
+    if ((st = stage(p, q.id[i], S_PLAIN, psi, tau)) != GP_OK) return st;
+  return GP_OK;
+}
+
+// x pass that exchanges y and z in the layout as it goes (ny = nz; PRO_SWAP)
+gp_status stage_swap(gp_plan_s* p, void* psi, int tau) {
+  const Axis& A = p->ax[0];
+  const long n = p->ax[1].n;
+  PassArgs g{};
+  g.in = psi; g.out = psi; g.tw = A.tw; g.mult = A.mult[tau]; g.scale = 1.0;
+  g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
+  g.ny = (int)n;
+  const long pairs = n * (n + 1) / 2, per = A.e->W / 2;
+  A.e->fn[CONTIG][V_PROP_SWAP](g, (unsigned)((pairs + per - 1) / per), 1, p->stream);
+  return check_launch(p);
+}
+
+// Whether the chain runs with the swapping x pass in the middle: states larger than the
+// 256 MiB last-level cache, with ny = nz.  Per linear step, all passes in the fixed
+// layout against swapping: 1024^3 complex64 13.3 and 12.0 ms, 512^3 complex128 2.32 and
+// 2.24, 768x256x256 complex64 0.84 and 0.76, 384^3 complex64 1.07 and 0.99.  In the cache
+// the z rows cost nothing extra and the scattered pencils do: 256^3 complex128 0.203 and
+// 0.205, 128^3 complex64 0.032 and 0.037.  Not where the caller took x as the carrier
+// (the x passes then turn).
+constexpr size_t kLastLevelCache = (size_t)256 << 20;
+bool swaps(const gp_plan_s* p) {
+  const int n = p->ax[1].n;
+  return (size_t)p->ntot * p->S > kLastLevelCache && !p->plane.on && p->nl_axis != 0 && p->ax[0].n > 1 && n > 1 &&
+         n % 2 == 0 && p->ax[2].n == n && p->ax[0].e->fn[CONTIG][V_PROP_SWAP];
+}
+
+// linear_chain with the x passes swapping y and z in the layout: the other stage is always
+// the pass of stride nx (y in [z][y][x], z in [y][z][x]: one length, one alpha, so the y
+// tables serve both).  An odd number of x passes starts with one that does not swap, after
+// a z pass in the given layout, so psi ends in [z][y][x].
+gp_status swap_chain(gp_plan_s* p, void* psi, int64_t n, double nl, const std::function<int(int64_t)>& tau_of) {
+  gp_status st;
+  const bool odd = (n + 1) % 2 != 0;
+  if ((st = stage(p, odd ? 2 : 1, S_PLAIN, psi, tau_of(0))) != GP_OK) return st;
+  for (int64_t k = 0; k <= n; ++k) {
+    st = odd && k == 0 ? stage(p, 0, S_PLAIN, psi, tau_of(k)) : stage_swap(p, psi, tau_of(k));
+    if (st != GP_OK) return st;
+    st = k < n ? stage(p, 1, S_TURN, psi, tau_of(k), tau_of(k + 1), nl) : stage(p, 1, S_PLAIN, psi, tau_of(k));
+    if (st != GP_OK) return st;
+  }
+  return GP_OK;
+}
+
+// L(t_0) N L(t_1) N ... N L(t_n) on psi in place, t_k = tau_of(k).  With two stages or more
+// the linear steps take them in alternating order, so that each rotation lies between
+// two sub-steps of one stage and the three run as one turning pass.
+gp_status linear_chain(gp_plan_s* p, void* psi, int64_t n, double nl, const std::function<int(int64_t)>& tau_of) {
+  if (swaps(p)) return swap_chain(p, psi, n, nl, tau_of);
+  const Stages q = stages_of(p);
+  gp_status st;
+  if (q.n == 0) {   // 1x1x1 grid: only the nonlinear rotations act (k = 0)
+    for (int64_t k = 0; k < n; ++k) {
+      launch_nonlinear(p->prec, psi, p->ntot, nl, p->stream);
+      if ((st = check_launch(p)) != GP_OK) return st;
+    }
     return GP_OK;
   }
-  if (p->plane.on) {          // x and y in one plane pass (nonlinear prologue there), then z
-    PlaneArgs g{};
-    g.in = psi; g.out = psi; g.multx = p->plane.mx[tau]; g.multy = p->plane.my[tau];
-    g.tw = p->plane.tw; g.nl_coef = nl;
-    p->plane.e->fn[with_nl ? 1 : 0](g, (unsigned)p->d.n[2], 1, p->stream);
-    if ((st = check_launch(p)) != GP_OK) return st;
-    return p->ax[2].n > 1 ? pass(p, 2, V_PROP, psi, psi, p->ax[2].mult[tau]) : GP_OK;
-  }
-  // the linear sub-steps commute: the axis that carries the nonlinear prologue runs
-  // first, the others follow in x, y, z order
-  const int carrier = (p->nl_axis >= 0 && p->ax[p->nl_axis].n > 1) ? p->nl_axis : c;
-  const int order[3] = {carrier, carrier == 0 ? 1 : 0, carrier == 2 ? 1 : 2};
-  for (int q = 0; q < 3; ++q) {
-    const int a = order[q];
-    if (p->ax[a].n == 1) continue;
-    const bool nl_here = with_nl && a == carrier;
-    if ((st = pass(p, a, nl_here ? V_PROP_NL : V_PROP, psi, psi, p->ax[a].mult[tau], nl)) != GP_OK) return st;
+  if ((st = stage(p, q.id[0], S_PLAIN, psi, tau_of(0))) != GP_OK) return st;
+  for (int64_t k = 0; k <= n; ++k) {
+    if (q.n == 1) {
+      if (k < n && (st = stage(p, q.id[0], S_NL, psi, tau_of(k + 1), 0, nl)) != GP_OK) return st;
+      continue;
+    }
+    for (int i = 1; i + 1 < q.n; ++i)
+      if ((st = stage(p, q.id[i], S_PLAIN, psi, tau_of(k))) != GP_OK) return st;
+    const int last = k % 2 ? q.id[0] : q.id[q.n - 1];
+    st = k < n ? stage(p, last, S_TURN, psi, tau_of(k), tau_of(k + 1), nl) : stage(p, last, S_PLAIN, psi, tau_of(k));
+    if (st != GP_OK) return st;
   }
   return GP_OK;
 }
@@ -601,16 +701,16 @@ gp_status step_n(gp_plan_s* p, void* psi, int64_t nsteps) {
   const int th = back ? TAU_MH : TAU_H, tf = back ? TAU_MDT : TAU_DT;
   const double nl = p->d.beta * (back ? -p->d.dt : p->d.dt);
   gp_status st;
+  auto tau_of = [&](int64_t k) { return (k == 0 || k == n) ? th : tf; };
   if (p->rot.on && p->rot.mixed) {
     // n + 1 linear steps; three mixed ones bring the layout back, each keeps the state
     // in psi; a remainder of one runs in place with the fixed-layout passes, of two as
     // two fully rotating steps (psi -> workspace -> psi); all before the cycles, while
     // the layout is [z][y][x]
-    auto tau_of = [&](int64_t k) { return (k == 0 || k == n) ? th : tf; };
     const int64_t r = (n + 1) % 3;
     int64_t k = 0;
     if (r == 1) {
-      if ((st = linear_all(p, psi, th, false, 0.0)) != GP_OK) return st;
+      if ((st = linear_all(p, psi, th)) != GP_OK) return st;
       k = 1;
     } else if (r == 2) {
       if ((st = rot_linear(p, psi, p->rot.work, tau_of(0), false, nl)) != GP_OK) return st;
@@ -627,22 +727,18 @@ gp_status step_n(gp_plan_s* p, void* psi, int64_t nsteps) {
     // passes and the state ends in psi
     int64_t first = 0;
     if ((n + 1) % 2 == 1) {
-      if ((st = linear_all(p, psi, th, false, 0.0)) != GP_OK) return st;
+      if ((st = linear_all(p, psi, th)) != GP_OK) return st;
       first = 1;
     }
     void* cur = psi;
     void* oth = p->rot.work;
     for (int64_t k = first; k <= n; ++k) {
-      const int tau = (k == 0 || k == n) ? th : tf;
-      if ((st = rot_linear(p, cur, oth, tau, k > 0, nl)) != GP_OK) return st;
+      if ((st = rot_linear(p, cur, oth, tau_of(k), k > 0, nl)) != GP_OK) return st;
       std::swap(cur, oth);
     }
     return GP_OK;
   }
-  if ((st = linear_all(p, psi, th, false, 0.0)) != GP_OK) return st;
-  for (int64_t s = 0; s < n; ++s)
-    if ((st = linear_all(p, psi, s + 1 < n ? tf : th, true, nl)) != GP_OK) return st;
-  return GP_OK;
+  return linear_chain(p, psi, n, nl, tau_of);
 }
 
 // the v-th compiled rotating schedule of length n (registration order)
@@ -1465,50 +1561,53 @@ gp_status gp_adjoint_step_n(gp_plan_t* p, const void* psi_seg_start, void* lam, 
   const size_t sb = p->ntot * p->S;
   auto slot = [&](int64_t i) { return (void*)((char*)tape + (size_t)i * sb); };
   const double nl = p->d.beta * p->d.dt;
-  const int c = first_real_axis(p);
-  // forward recompute: phi_0 = L(h) psi_0, phi_{n+1} = L(dt) N(phi_n), stored in the tape
-  {
-    const void* src = psi_seg_start;
-    bool first = true;
-    for (int a = 0; a < 3; ++a) {
-      if (p->ax[a].n == 1) continue;
-      if ((st = pass(p, a, V_PROP, first ? src : slot(0), slot(0), p->ax[a].mult[TAU_H])) != GP_OK) return st;
-      first = false;
-    }
-    if (first) {  // 1x1x1 grid
-      launch_scale_copy(p->prec, src, slot(0), p->ntot, 1.0, p->stream);
-      if ((st = check_launch(p)) != GP_OK) return st;
-    }
-  }
-  for (int64_t s = 0; s + 1 < nsteps; ++s) {
-    if (c < 0) {
-      launch_scale_copy(p->prec, slot(s), slot(s + 1), p->ntot, 1.0, p->stream);
-      launch_nonlinear(p->prec, slot(s + 1), p->ntot, nl, p->stream);
-      if ((st = check_launch(p)) != GP_OK) return st;
+  // one pass of axis a; mode V_PROP*, or a turning one with the multipliers of tau2 for
+  // its second sub-step; aux: the tape state the rotation's adjoint needs, keep: where a
+  // turning forward pass stores the state between its sub-steps
+  auto run = [&](int a, int var, const void* in, void* out, int tau, int tau2, const void* aux, void* keep) {
+    const Axis& A = p->ax[a];
+    PassArgs g{};
+    g.in = in; g.out = out; g.tw = A.tw; g.mult = A.mult[tau]; g.mult2 = A.mult[tau2];
+    g.nl_coef = nl; g.aux = aux; g.tape = keep; g.scale = 1.0;
+    g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
+    A.e->fn[A.kind][var](g, A.blocks, 1, p->stream);
+    return check_launch(p);
+  };
+  int q[3], m = 0;
+  for (int a = 0; a < 3; ++a) if (p->ax[a].n > 1) q[m++] = a;
+  // forward recompute: phi_0 = L(h) psi_0, phi_{n+1} = L(dt) N(phi_n), stored in the tape.
+  // The axes alternate as in the step itself, so the pass that completes phi_n stores it
+  // and goes on with the rotation and the first sub-step of the next state.
+  if (m == 0) return fail(GP_ERR_UNSUPPORTED, "adjoint on a 1x1x1 grid");
+  if ((st = run(q[0], V_PROP, psi_seg_start, slot(0), TAU_H, TAU_H, nullptr, nullptr)) != GP_OK) return st;
+  for (int64_t s = 0; s < nsteps; ++s) {
+    const int tau = s == 0 ? TAU_H : TAU_DT;
+    const bool more = s + 1 < nsteps;
+    if (m == 1) {
+      if (more && (st = run(q[0], V_PROP_NL, slot(s), slot(s + 1), TAU_DT, TAU_DT, nullptr, nullptr)) != GP_OK) return st;
       continue;
     }
-    for (int a = 0; a < 3; ++a) {
-      if (p->ax[a].n == 1) continue;
-      const bool carrier = (a == c);
-      if ((st = pass(p, a, carrier ? V_PROP_NL : V_PROP, carrier ? slot(s) : slot(s + 1), slot(s + 1),
-                     p->ax[a].mult[TAU_DT], nl)) != GP_OK)
-        return st;
-    }
+    if (m == 3 && (st = run(q[1], V_PROP, slot(s), slot(s), tau, tau, nullptr, nullptr)) != GP_OK) return st;
+    const int last = s % 2 ? q[0] : q[m - 1];
+    st = more ? run(last, V_TURN_TAPE, slot(s), slot(s + 1), tau, TAU_DT, nullptr, slot(s))
+              : run(last, V_PROP, slot(s), slot(s), tau, tau, nullptr, nullptr);
+    if (st != GP_OK) return st;
   }
-  // backward: lam <- L(-h); then per step n (reverse): N'(phi_n)^dagger fused, L(-dt) or L(-h)
-  if ((st = linear_all(p, lam, TAU_MH, false, 0.0)) != GP_OK) return st;
-  for (int64_t s = nsteps - 1; s >= 0; --s) {
-    const int tau = s > 0 ? TAU_MDT : TAU_MH;
-    if (c < 0) {
-      return fail(GP_ERR_UNSUPPORTED, "adjoint on a 1x1x1 grid");
+  // backward: L(-h) N'(phi_{n-1})^dagger L(-dt) ... N'(phi_0)^dagger L(-h) on lam, the
+  // adjoint of each rotation between two sub-steps of one axis
+  if ((st = run(q[0], V_PROP, lam, lam, TAU_MH, TAU_MH, nullptr, nullptr)) != GP_OK) return st;
+  for (int64_t j = 0; j <= nsteps; ++j) {
+    const int tau = j == 0 || j == nsteps ? TAU_MH : TAU_MDT, next = j + 1 < nsteps ? TAU_MDT : TAU_MH;
+    const void* phi = j < nsteps ? slot(nsteps - 1 - j) : nullptr;
+    if (m == 1) {
+      if (phi && (st = run(q[0], V_PROP_ADJ, lam, lam, next, next, phi, nullptr)) != GP_OK) return st;
+      continue;
     }
-    for (int a = 0; a < 3; ++a) {
-      if (p->ax[a].n == 1) continue;
-      const bool carrier = (a == c);
-      if ((st = pass(p, a, carrier ? V_PROP_ADJ : V_PROP, lam, lam, p->ax[a].mult[tau], nl, carrier ? slot(s) : nullptr)) !=
-          GP_OK)
-        return st;
-    }
+    if (m == 3 && (st = run(q[1], V_PROP, lam, lam, tau, tau, nullptr, nullptr)) != GP_OK) return st;
+    const int last = j % 2 ? q[0] : q[m - 1];
+    st = phi ? run(last, V_TURN_ADJ, lam, lam, tau, next, phi, nullptr)
+             : run(last, V_PROP, lam, lam, tau, tau, nullptr, nullptr);
+    if (st != GP_OK) return st;
   }
   return GP_OK;
 }
@@ -1589,30 +1688,33 @@ gp_status gp_plan_batch(const gp_desc* runs, int32_t nruns, void* hip_stream, gp
   return GP_OK;
 }
 
+// Multipliers of a grouped launch: one sub-step (half or full time step), or the two of a
+// turning pass.
+enum BatchTau { B_H = 0, B_DT, B_H_DT, B_DT_DT, B_DT_H, B_H_H, NBATCHTAU };
+static int batch_tau(int t, int t2) { return t == 0 ? (t2 == 0 ? B_H_H : B_H_DT) : (t2 == 0 ? B_DT_H : B_DT_DT); }
+
 // pointer tables of the grouped launches, both signs:
-// RunPtrs[sign][axis][tau: 0 half step, 1 full step][member] per group
+// RunPtrs[sign][stage][BatchTau][member] per group
 static gp_status batch_tables(gp_plan_s* p, void* const* psis) {
   // a launch of a recorded graph may still read the tables: let it finish
   HIPCHK(p, hipStreamSynchronize(p->stream));
   drop_graphs(p);
   for (auto& g : p->groups) {
     const size_t m = g.members.size();
-    std::vector<RunPtrs> h(2 * 3 * 2 * m);
+    const Stages q = stages_of(p->runs[g.members[0]]);    // every member made the same choices
+    std::vector<RunPtrs> h(2 * 3 * NBATCHTAU * m);
     for (int sg = 0; sg < 2; ++sg)
-      for (int a = 0; a < 3; ++a)
-        for (int t = 0; t < 2; ++t)
-          for (size_t i = 0; i < m; ++i) {
-            gp_plan_s* r = p->runs[g.members[i]];
-            const int tau = sg ? (t == 0 ? TAU_MH : TAU_MDT) : (t == 0 ? TAU_H : TAU_DT);
-            RunPtrs& e = h[((sg * 3 + a) * 2 + t) * m + i];
-            e.in = psis[g.members[i]];
-            e.out = psis[g.members[i]];
-            e.mult = r->ax[a].mult[tau];
+      for (int i = 0; i < q.n; ++i)
+        for (int t = 0; t < NBATCHTAU; ++t)
+          for (size_t k = 0; k < m; ++k) {
+            gp_plan_s* r = p->runs[g.members[k]];
+            const int half = sg ? TAU_MH : TAU_H, full = sg ? TAU_MDT : TAU_DT;
+            RunPtrs& e = h[((sg * 3 + i) * NBATCHTAU + t) * m + k];
+            e.in = psis[g.members[k]];
+            e.out = psis[g.members[k]];
+            e.mult = stage_mult(r, q.id[i], t == B_H || t == B_H_DT || t == B_H_H ? half : full);
+            e.mult2 = stage_mult(r, q.id[i], t == B_DT_H || t == B_H_H ? half : full);
             e.nl_coef = r->d.beta * (sg ? -r->d.dt : r->d.dt);
-            if (a == 0 && r->plane.on) {   // the x slot carries the plane pass's x and y tables
-              e.mult = r->plane.mx[tau];
-              e.mult2 = r->plane.my[tau];
-            }
           }
     if (g.nptrs < h.size()) {
       if (g.d_ptrs) (void)hipFree(g.d_ptrs);
@@ -1627,13 +1729,39 @@ static gp_status batch_tables(gp_plan_s* p, void* const* psis) {
   return GP_OK;
 }
 
-// record one step graph: slot 0 = L(h); 1 = N, L(h); 2 + j = (N, L(dt)) x 2^j, with the
-// nonlinear rotation fused into each application's first pass; size group g > 0 is
-// captured on its own branch (fork from and join into the plan's stream)
+// Launches of one size group for a stretch of the chain L(t_0) N L(t_1) ... N L(t_n)
+// (linear_chain), t = 0 a half step, 1 a full one.
+struct GroupChain {
+  const gp_plan_s* r0;
+  Stages q;
+  const RunPtrs* ptrs;     // of the sign
+  unsigned members;
+  hipStream_t st;
+  void put(int i, StageMode mode, int bt) const {
+    launch_stage(r0, q.id[i], mode, nullptr, nullptr, 0, 0, 0.0, ptrs + ((size_t)i * NBATCHTAU + bt) * members, members, st);
+  }
+  void begin() const { put(0, S_PLAIN, B_H); }
+  void middle(int t) const { for (int i = 1; i + 1 < q.n; ++i) put(i, S_PLAIN, t == 0 ? B_H : B_DT); }
+  // the rest of linear step k (odd: in reverse order), N and the first sub-step of the next
+  void element(bool odd, int t, int t2) const {
+    if (q.n == 1) { put(0, S_NL, t2 == 0 ? B_H : B_DT); return; }
+    middle(t);
+    put(odd ? 0 : q.n - 1, S_TURN, batch_tau(t, t2));
+  }
+  // the rest of the last linear step
+  void finish(bool odd) const {
+    if (q.n == 1) return;
+    middle(0);
+    put(odd ? 0 : q.n - 1, S_PLAIN, B_H);
+  }
+};
+
+// Record one step graph of the chain of n >= 2 steps: slot 0 = its beginning up to the first
+// sub-step of linear step 1; GBODY + j = 2^j elements from an odd linear step on; 2 and 3 =
+// from linear step n - 1 (even, odd) to the end.  Slot 1 = the whole chain of one step.
+// Size group g > 0 is captured on its own branch (fork from and join into the plan's stream).
 static gp_status batch_record(gp_plan_s* p, int sg, int slot) {
-  const int64_t reps = slot < 2 ? 1 : (int64_t)1 << (slot - 2);
-  const int t = slot < 2 ? 0 : 1;
-  const bool nl = slot != 0;
+  constexpr int BODY = gp_plan_s::GBODY;
   HIPCHK(p, hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
   hipError_t ce = hipSuccess;
   if (p->groups.size() > 1) ce = hipEventRecord(p->fork_ev, p->stream);
@@ -1642,34 +1770,13 @@ static gp_status batch_record(gp_plan_s* p, int sg, int slot) {
     hipStream_t st = gi == 0 ? p->stream : p->side[gi - 1];
     if (gi > 0) ce = hipStreamWaitEvent(st, p->fork_ev, 0);
     if (ce != hipSuccess) break;
-    gp_plan_s* r0 = p->runs[g.members[0]];
-    const int c = first_real_axis(r0);
+    const gp_plan_s* r0 = p->runs[g.members[0]];
     const size_t m = g.members.size();
-    auto ptrs = [&](int a) { return g.d_ptrs + ((sg * 3 + a) * 2 + t) * m; };
-    for (int64_t k = 0; k < reps; ++k) {
-      if (r0->plane.on) {      // every member of the group made the same choice
-        PlaneArgs args{};
-        args.batch = ptrs(0);
-        args.tw = r0->plane.tw;
-        r0->plane.e->fn[nl ? 1 : 0](args, (unsigned)r0->d.n[2], (unsigned)m, st);
-        if (r0->ax[2].n > 1) {
-          const Axis& A = r0->ax[2];
-          PassArgs pa{};
-          pa.batch = ptrs(2); pa.tw = A.tw; pa.ksq = A.ksq; pa.scale = 1.0;
-          pa.npencils = A.npencils; pa.inner = A.inner; pa.outer = A.outer; pa.es = A.es;
-          A.e->fn[A.kind][V_PROP](pa, A.blocks, (unsigned)m, st);
-        }
-        continue;
-      }
-      for (int a = 0; a < 3; ++a) {
-        if (r0->ax[a].n == 1) continue;
-        const Axis& A = r0->ax[a];
-        PassArgs pa{};
-        pa.batch = ptrs(a); pa.tw = A.tw; pa.ksq = A.ksq; pa.scale = 1.0;
-        pa.npencils = A.npencils; pa.inner = A.inner; pa.outer = A.outer; pa.es = A.es;
-        A.e->fn[A.kind][(nl && a == c) ? V_PROP_NL : V_PROP](pa, A.blocks, (unsigned)m, st);
-      }
-    }
+    const GroupChain c{r0, stages_of(r0), g.d_ptrs + (size_t)sg * 3 * NBATCHTAU * m, (unsigned)m, st};
+    if (slot == 0) { c.begin(); c.element(false, 0, 1); }
+    else if (slot == 1) { c.begin(); c.element(false, 0, 0); c.finish(true); }
+    else if (slot < BODY) { c.element(slot == 3, 1, 0); c.finish(slot == 2); }
+    else for (int64_t k = 0; k < (int64_t)1 << (slot - BODY); ++k) c.element(k % 2 == 0, 1, 1);
     if (gi > 0) {
       ce = hipEventRecord(p->join_ev[gi - 1], st);
       if (ce == hipSuccess) ce = hipStreamWaitEvent(p->stream, p->join_ev[gi - 1], 0);
@@ -1712,21 +1819,23 @@ gp_status gp_step_n_batch(gp_plan_t* p, void* const* psis, int64_t nsteps) {
   const bool same = p->graph_key.size() == p->runs.size() &&
                     std::equal(p->graph_key.begin(), p->graph_key.end(), psis);
   if (!same && (st = batch_tables(p, psis)) != GP_OK) return st;
-  // L(h) [N L(dt)]^(n-1) N L(h): the body's n - 1 applications as recorded graphs of
-  // 2^j applications each (the largest repeated, the rest by the binary digits), so a
-  // call of any length launches a bounded set of graphs of bounded size
+  // the chain's n - 2 inner elements as recorded graphs of 2^j elements each (the largest
+  // repeated, the rest by the binary digits, the single one last), so a call of any
+  // length launches a bounded set of graphs of bounded size
   const int sg = nsteps < 0 ? 1 : 0;
-  int64_t rem = (nsteps < 0 ? -nsteps : nsteps) - 1;
+  const int64_t n = nsteps < 0 ? -nsteps : nsteps;
+  if (n == 1) return batch_launch(p, sg, 1);
   if ((st = batch_launch(p, sg, 0)) != GP_OK) return st;
-  constexpr int top = gp_plan_s::GPOW - 1;
+  constexpr int BODY = gp_plan_s::GBODY, top = gp_plan_s::GPOW - 1;
+  int64_t rem = n - 2;
   while (rem >= ((int64_t)1 << top)) {
-    if ((st = batch_launch(p, sg, 2 + top)) != GP_OK) return st;
+    if ((st = batch_launch(p, sg, BODY + top)) != GP_OK) return st;
     rem -= (int64_t)1 << top;
   }
   for (int j = top - 1; j >= 0; --j)
     if (rem & ((int64_t)1 << j))
-      if ((st = batch_launch(p, sg, 2 + j)) != GP_OK) return st;
-  return batch_launch(p, sg, 1);
+      if ((st = batch_launch(p, sg, BODY + j)) != GP_OK) return st;
+  return batch_launch(p, sg, (n - 1) % 2 ? 3 : 2);
 }
 
 gp_status gp_energies_batch(gp_plan_t* p, void* const* psis, void* work, double* out) {
@@ -1843,10 +1952,6 @@ static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::funct
   return check_launch(p);
 }
 
-// xy choice: separate x and y passes against one plane pass, both launched for
-// `runs` copies of the scratch state at once (the ensemble launches a size group
-// together, which changes how well each option fills the GPU; the copies all
-// alias `scratch`, whose contents are undefined afterwards)
 // Timings within 1 % count as ties, resolved to the candidate tried first (the lower
 // variant index, the first axis, separate passes), so that repeated tunings agree.
 constexpr double TUNE_TIE = 0.99;
@@ -1859,45 +1964,70 @@ static void tune_note(const gp_plan_s* p, const char* what, int axis, int cand, 
             what, axis, cand, us);
 }
 
+// two steps of the running chain for `runs` states at once (ptrs: [x, y, z, plane][runs], or
+// null for the one state psi): every stage once plain or turning, as linear_chain
+// repeats them
+static gp_status chain_cycle(gp_plan_s* p, void* psi, const RunPtrs* ptrs, unsigned runs, double nl) {
+  if (!ptrs && swaps(p)) {
+    gp_status st = GP_OK;
+    for (int k = 0; k < 2 && st == GP_OK; ++k)
+      if ((st = stage_swap(p, psi, TAU_DT)) == GP_OK) st = stage(p, 1, S_TURN, psi, TAU_DT, TAU_DT, nl);
+    return st;
+  }
+  const Stages q = stages_of(p);
+  auto put = [&](int i, StageMode mode) {
+    launch_stage(p, q.id[i], mode, psi, psi, TAU_DT, TAU_DT, nl, ptrs ? ptrs + (size_t)q.id[i] * runs : nullptr, runs,
+                 p->stream);
+  };
+  for (int k = 0; k < 2; ++k) {
+    for (int i = 1; i + 1 < q.n; ++i) put(i, S_PLAIN);
+    if (q.n > 0) put(k ? 0 : q.n - 1, q.n == 1 ? S_NL : S_TURN);
+  }
+  return check_launch(p);
+}
+
+// xy choice: separate x and y passes against one plane pass, both in the running chain
+// and launched for `runs` copies of the scratch state at once (the ensemble launches a
+// size group together, which changes how well each option fills the GPU; the copies
+// all alias `scratch`, whose contents are undefined afterwards)
 static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, int* choice) {
   gp_status st;
   *choice = 0;
   if (!p->plane.e || p->ax[0].n == 1) return GP_OK;
   if ((st = build_plane_tables(p)) != GP_OK) return st;
-  const size_t need = 3 * (size_t)runs;
+  const size_t need = 4 * (size_t)runs;
   if (p->n_tune_ptrs < need) {
     if ((st = dev_alloc(p, (void**)&p->d_tune_ptrs, need * sizeof(RunPtrs))) != GP_OK) return st;
     p->n_tune_ptrs = need;
   }
+  const double nl = p->d.beta * p->d.dt;
   std::vector<RunPtrs> h(need);
-  for (int i = 0; i < runs; ++i) {
-    h[i] = RunPtrs{scratch, scratch, p->ax[0].mult[TAU_DT], nullptr, 0.0};
-    h[runs + i] = RunPtrs{scratch, scratch, p->ax[1].mult[TAU_DT], nullptr, 0.0};
-    h[2 * runs + i] = RunPtrs{scratch, scratch, p->plane.mx[TAU_DT], p->plane.my[TAU_DT], 0.0};
-  }
+  for (int id = 0; id < 4; ++id)
+    for (int i = 0; i < runs; ++i)
+      h[id * runs + i] = RunPtrs{scratch, scratch, stage_mult(p, id, TAU_DT), stage_mult(p, id, TAU_DT), nl};
   HIPCHK(p, hipMemcpy(p->d_tune_ptrs, h.data(), need * sizeof(RunPtrs), hipMemcpyHostToDevice));
-  auto axis_launch = [&](int a, const RunPtrs* ptrs) {
-    const Axis& A = p->ax[a];
-    PassArgs g{};
-    g.batch = ptrs; g.tw = A.tw; g.ksq = A.ksq; g.scale = 1.0;
-    g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
-    A.e->fn[A.kind][V_PROP](g, A.blocks, (unsigned)runs, p->stream);
-  };
-  double t_sep = 0, t_plane = 0;
-  if ((st = time_calls(p, reps, &t_sep, [&] { axis_launch(0, p->d_tune_ptrs); axis_launch(1, p->d_tune_ptrs + runs); })) != GP_OK)
-    return st;
-  if ((st = time_calls(p, reps, &t_plane, [&] {
-         PlaneArgs g{};
-         g.batch = p->d_tune_ptrs + 2 * runs; g.tw = p->plane.tw;
-         p->plane.e->fn[0](g, (unsigned)p->d.n[2], (unsigned)runs, p->stream);
-       })) != GP_OK)
-    return st;
-  *choice = t_plane < TUNE_TIE * t_sep ? 1 : 0;
+  launch_fill(p->prec, scratch, p->ntot, 1.0, 0.0, p->stream);
+  const bool was = p->plane.on;
+  double t[2] = {0, 0};
+  gp_status inner = GP_OK;
+  for (int plane = 0; plane < 2; ++plane) {
+    p->plane.on = plane == 1;
+    st = time_calls(p, reps, &t[plane], [&] {
+      if (inner == GP_OK) inner = chain_cycle(p, scratch, p->d_tune_ptrs, (unsigned)runs, nl);
+    });
+    p->plane.on = was;
+    if (st != GP_OK) return st;
+    if (inner != GP_OK) return inner;
+    tune_note(p, "xy choice", 3, plane, t[plane]);
+  }
+  *choice = t[1] < TUNE_TIE * t[0] ? 1 : 0;
   return GP_OK;
 }
 
-// time the composed step L(dt) with the nonlinear prologue on each real axis in turn
-// (state: psi = 1, the small-angle rotation of every real run); keep the fastest
+// time the running chain with the first rotation on each real axis in turn (state:
+// psi = 1, the small-angle rotation of every real run); keep the fastest.  The carrier
+// decides which axis lies between the turning ones: y for x, x for y, and x again for z,
+// which is therefore not timed on its own
 static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {
   gp_status st;
   launch_fill(p->prec, scratch, p->ntot, 1.0, 0.0, p->stream);
@@ -1905,13 +2035,13 @@ static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {
   const double nl = p->d.beta * p->d.dt;
   double best = 1e300;
   *choice = first_real_axis(p);
-  for (int a = 0; a < 3; ++a) {
+  for (int a = 0; a < 2; ++a) {
     if (p->ax[a].n == 1) continue;
     p->nl_axis = a;
     double us = 0;
     gp_status inner = GP_OK;
     if ((st = time_calls(p, reps, &us, [&] {
-           if (inner == GP_OK) inner = linear_all(p, scratch, TAU_DT, true, nl);
+           if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, nl);
          })) != GP_OK)
       return st;
     if (inner != GP_OK) return inner;
@@ -1939,10 +2069,11 @@ static gp_status tune_rot(gp_plan_s* p, void* scratch, int reps, int* choice) {
     for (int v = 0; v <= 2 * nrot; ++v) {
       double us = 0;
       if (v == 0) {
-        if ((st = time_calls(p, reps, &us, [&] {
-               if (inner == GP_OK) inner = linear_all(p, scratch, TAU_DT, true, nl);
+        if ((st = time_calls(p, (reps + 1) / 2, &us, [&] {       // two steps
+               if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, nl);
              })) != GP_OK)
           return st;
+        us *= 0.5;
       } else if (v <= nrot) {
         if ((st = gp_select_variant(p, 5, v)) != GP_OK) return st;
         if ((st = time_calls(p, reps, &us, [&] {       // two steps: back in `scratch`

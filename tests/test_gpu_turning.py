@@ -1,0 +1,95 @@
+"""The running chain of the split step: passes that turn (two sub-steps along one axis with
+the nonlinear rotation between them), the xy-plane pass that turns, and the x passes
+that exchange y and z in the layout of states larger than the last-level cache, against
+the same steps composed of single sub-steps (gp_substep_linear, gp_substep_nonlinear).
+
+Tolerances: a pass rounds each point by a few units in the last place (5e-15 complex128,
+2e-7 complex64 after the transform's stages); at most 3 steps make 21 passes; a rotation
+by coef (|psi|^2 - 1) turns a relative error d of psi into an angle error 2 coef |psi|^2 d,
+with |psi|^2 below 4 on average over the few points that count."""
+import numpy as np
+import pytest
+
+import gp_inputs as I
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def _composed(plan, psi, n):
+    dt = plan.dt if n > 0 else -plan.dt
+    for _ in range(abs(n)):
+        for axis in range(3):
+            plan.substep_linear(psi, axis, 0.5 * dt)
+        plan.substep_nonlinear(psi, dt)
+        for axis in range(3):
+            plan.substep_linear(psi, axis, 0.5 * dt)
+    return psi
+
+
+def _check(plan, psi0, n, tol):
+    a = plan.step_n(psi0.clone(), n)
+    b = _composed(plan, psi0.clone(), n)
+    rel = float(torch.linalg.vector_norm(a - b) / torch.linalg.vector_norm(b))
+    assert rel < tol, (plan.n, n, rel)
+
+
+@pytest.mark.parametrize("coef", [0.04, 0.5], ids=["small", "mixed"])
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("shape", [(96, 48, 24), (16, 1, 8), (1, 64, 1), (32, 32, 1), (24, 192, 2), (64, 3, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_chain_matches_composed_substeps(shape, prec, coef):
+    """Three, two and one axes longer than 1, forward and backward; rotation angles all
+    small, and small beside general ones in one lane."""
+    import paper_2003_03590_amd as gp
+    plan = gp.Plan(shape, 0.3, coef / 0.01, 0.01, prec)
+    psi0 = torch.from_numpy(I.random_field(shape[::-1], seed=41)).to(DEV).to(plan.dtype).contiguous()
+    tol = (1e-13 if prec == "c128" else 4e-6) * (1.0 + 8.0 * coef)
+    for carrier in [a for a in range(3) if shape[a] > 1]:
+        plan.select_variant(4, carrier)
+        for n in (1, 2, 3, -2):
+            _check(plan, psi0, n, tol)
+    plan.close()
+
+
+def test_angles_beyond_the_reduced_range():
+    """Angles up to several thousand (one rotation: each one multiplies the error again)."""
+    import paper_2003_03590_amd as gp
+    coef = 600.0
+    plan = gp.Plan((96, 48, 24), 0.3, coef / 0.01, 0.01, "c128")
+    psi0 = torch.from_numpy(I.random_field((24, 48, 96), seed=41)).to(DEV)
+    _check(plan, psi0, 1, 1e-13 * (1.0 + 8.0 * coef))
+    plan.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("shape", [(16, 16, 2), (32, 32, 1), (48, 48, 12), (64, 64, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_turning_plane_pass(shape, prec):
+    import paper_2003_03590_amd as gp
+    for coef in (0.04, 0.5):
+        plan = gp.Plan(shape, 0.3, coef / 0.01, 0.01, prec)
+        plan.select_variant(3, 1)
+        psi0 = torch.from_numpy(I.random_field(shape[::-1], seed=42)).to(DEV).to(plan.dtype).contiguous()
+        tol = (1e-13 if prec == "c128" else 4e-6) * (1.0 + 8.0 * coef)
+        for n in (1, 2, 3, -2):
+            _check(plan, psi0, n, tol)
+        plan.close()
+
+
+@pytest.mark.parametrize("shape,prec", [((768, 256, 256), "c64"), ((96, 512, 512), "c128"), ((24, 1024, 1024), "c128")],
+                         ids=["768x256x256-c64", "96x512x512-c128", "24x1024x1024-c128"])
+def test_swapping_x_pass(shape, prec):
+    """States beyond 256 MiB with ny = nz: even and odd numbers of linear steps, every
+    compiled x schedule (pencil tiles of every width)."""
+    import paper_2003_03590_amd as gp
+    plan = gp.Plan(shape, 0.3, 4.0, 0.01, prec)
+    assert plan.state_bytes() > 256 << 20
+    g = torch.Generator(device=DEV).manual_seed(43)
+    psi0 = torch.randn(plan.shape, dtype=plan.dtype, device=DEV, generator=g) * 0.3 + 1.0
+    for v in range(gp.lib().gp_variant_count(shape[0], plan.prec)):
+        plan.select_variant(0, v)
+        for n in (1, 2, -3):
+            _check(plan, psi0, n, 1.5e-13 if prec == "c128" else 5e-6)
+    plan.close()
