@@ -39,6 +39,16 @@ __device__ __forceinline__ cplx<Real> cscale(cplx<Real> a, Real s) { return mk(a
 template <class Real>
 __device__ __forceinline__ Real cabs2(cplx<Real> a) { return a.x * a.x + a.y * a.y; }
 
+struct Neu {          // Neumaier compensated sum
+  double s = 0.0, c = 0.0;
+  __device__ __forceinline__ void add(double x) {
+    const double t = s + x;
+    c += (fabs(s) >= fabs(x)) ? (s - t) + x : (x - t) + s;
+    s = t;
+  }
+  __device__ __forceinline__ double val() const { return s + c; }
+};
+
 // ---------------------------------------------------------------------------
 // Table entries.  complex128 tables hold the FP64 value.  complex64 tables hold
 // the FP64 value as an unevaluated sum hi + lo of two FP32 complex numbers, so

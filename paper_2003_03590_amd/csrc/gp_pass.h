@@ -61,19 +61,29 @@ __device__ __forceinline__ const void* reload(const void* p) {
   return p;
 }
 
+// Keeps the operations that make these values ahead of the next in_order's.
+template <class Real>
+__device__ __forceinline__ void in_order(double& acc, cplx<Real>& v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(acc), "+v"(v.x), "+v"(v.y));
+#endif
+}
+
 enum PassKind { CONTIG = 0, STRIDED = 1 };
 enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
-// pointwise work fused in front of the transform (PRO_KIN: none, but accumulate
-// sum k_j^2 |F_j v|^2 after the forward transform for the kinetic energy;
+// pointwise work fused in front of the transform (PRO_DERIV: none; the multiplier is that
+// of a spectral derivative, i k_j / N_j, and sum k_j^2 |F_j v|^2 is accumulated for the
+// kinetic energy;
 // PRO_ARGLE: none, but turn the derivative after the inverse transform into the
 // explicit part of the imaginary-time step; PRO_MULT3: none, but multiply the
 // forward transform by the separable 3-D propagator m_x(k_x) m_y(k_y) m_z(k_z) before
 // it is stored -- the last forward pass of the literal 3-D form)
 // In a TURN pass: the work between its two sub-steps (PRO_NL, PRO_ADJ_NL, or PRO_TAPE:
 // store the state there as well, then rotate it).  PRO_SWAP: none; the pass exchanges the
-// two outer axes of the layout (see pencil_pair).
-enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DENSITY = 3, PRO_KIN = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
-                PRO_TAPE = 7, PRO_SWAP = 8 };
+// two outer axes of the layout (see pencil_pair).  PRO_ENERGY (FWD): sums only, nothing is
+// stored: k_j^2 |F_j v|^2 and, where point_partial is given, |v|^2 and (|v|^2 - 1)^2.
+enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DENSITY = 3, PRO_DERIV = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
+                PRO_TAPE = 7, PRO_SWAP = 8, PRO_ENERGY = 9 };
 
 // per-run pointers of a grouped (ensemble) launch: run = blockIdx.y
 struct RunPtrs {
@@ -100,6 +110,7 @@ struct PassArgs {
   double q4a;              // PRO_ARGLE: 1 / (4 alpha)
   const double* ksq;       // k_j^2 in position order (kinetic accumulation)
   double* kin_partial;     // per-workgroup partial sum of k_j^2 |F_j v|^2 (or null)
+  double* point_partial;   // PRO_ENERGY: per-workgroup sums of |v|^2, then of (|v|^2 - 1)^2, or null
   double nl_coef;          // beta * dt of the nonlinear prologue
   double scale;            // FWD/INV output scale
   long npencils;           // number of pencils along this axis
@@ -187,9 +198,8 @@ __device__ __forceinline__ int stage_pos(int t, int j, int r) {
 
 // position of natural frequency k (digit-reversal of the DIF output order)
 template <class S>
-__device__ __forceinline__ int freq_pos(int k) {
+__host__ __device__ constexpr int freq_pos(int k) {
   int p = 0;
-#pragma unroll
   for (int s = 0; s < S::NS; ++s) p += ((k / S::K(s)) % S::rad(s)) * S::M(s);
   return p;
 }
@@ -521,7 +531,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
   // moved with 16-byte accesses (a pencil past the last one takes the last one, as
   // the lanes do, so the duplicate stores write equal bytes)
   constexpr bool WIDE = sizeof(Real) == 4 && KIND == CONTIG && (MODE == PROP || MODE == TURN) &&
-                        (PRO == PRO_NONE || PRO == PRO_NL || PRO == PRO_SWAP) && wide_io<S>();
+                        (PRO == PRO_NONE || PRO == PRO_NL || PRO == PRO_SWAP || PRO == PRO_DERIV) && wide_io<S>();
   // first point of pencil pc of the tile, as it is read and as it is written
   auto swap_pencil = [&](int pc, bool written) {
     const unsigned n = (unsigned)a.ny, last = n * (n + 1) / 2 - 1;
@@ -603,24 +613,35 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
       constexpr int L = S::NS - 1;
       constexpr int B = E / S::rad(L);
       if constexpr (MODE == PROP) {
-        if constexpr (PRO == PRO_KIN) {
+        if constexpr (PRO == PRO_DERIV) {
+          // i k/N F_j v; the energy sum_k k^2 |F_j v|^2 is N^2 times the sum of its squares,
+          // plus the Nyquist coefficient, which the derivative leaves out
+          constexpr int P = freq_pos<S>(S::N / 2), RL = S::RL, G = P / RL;
+          // With 24 points a lane or more the squares are summed a point at a time before the
+          // next table entry is taken (in_order): left to the scheduler, the sums fall behind
+          // and the FP64 products of all points wait in registers (512 points complex64: 306
+          // registers, one wavefront per SIMD, 1.22 ms a pass at 512^3 against 0.75).
           double acc = 0.0;
 #pragma unroll
           for (int r = 0; r < S::rad(L); ++r)
 #pragma unroll
             for (int j = 0; j < B; ++j) {
-              const int li = r * (S::N / S::rad(L)) + t + T * j;
-              const C x = v[j + B * r];
-              acc += gptr<double>(a.ksq)[(unsigned)li] *
-                     ((double)x.x * x.x + (double)x.y * x.y);
+              const double k = gptr<double>(a.mult)[(unsigned)(2 * (r * (S::N / S::rad(L)) + t + T * j) + 1)];
+              const double x = v[j + B * r].x, y = v[j + B * r].y;
+              if (S::N % 2 == 0 && r == P % RL && j == G / T && t == G % T) acc += 0.25 * (x * x + y * y);
+              const double re = -y * k, im = x * k;
+              acc = fma(re, re, fma(im, im, acc));
+              v[j + B * r] = mk(Real(re), Real(im));
+              if constexpr (E >= 24) in_order(acc, v[j + B * r]);
             }
-          if (cur.active) kin_acc += acc;
+          if (cur.active) kin_acc = acc * ((double)S::N * S::N);
+        } else {
+#pragma unroll
+          for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+            for (int j = 0; j < B; ++j)
+              v[j + B * r] = pmul(v[j + B * r], tab_at(mult, r * (S::N / S::rad(L)) + t + T * j));
         }
-#pragma unroll
-        for (int r = 0; r < S::rad(L); ++r)
-#pragma unroll
-          for (int j = 0; j < B; ++j)
-            v[j + B * r] = pmul(v[j + B * r], tab_at(mult, r * (S::N / S::rad(L)) + t + T * j));
         inverse_all<Real, S, KIND, L>(v, lds, t, col, tw);
         if constexpr (PRO == PRO_ARGLE) {
           // v holds d phi / dz (this pass is the z derivative); replace it by the explicit
@@ -676,8 +697,52 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     }
   };
 
+  // fixed-order sum over the workgroup (wave butterfly, then waves in order), in thread 0
+  auto block_sum = [&](double acc) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    __syncthreads();
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    __syncthreads();
+    double s = 0.0;
+    if (tid == 0)
+      for (int w = 0; w < S::THREADS / 64 + (S::THREADS % 64 ? 1 : 0); ++w) s += red[w];
+    return s;
+  };
+
   C v[E];
   const Where w = where(tile);
+  if constexpr (PRO == PRO_ENERGY) {
+    load(v, w);
+    Neu rho_acc, int_acc;
+    if (a.point_partial && w.active) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const double x = v[e].x, y = v[e].y, rho = x * x + y * y;
+        rho_acc.add(rho);
+        int_acc.add((rho - 1.0) * (rho - 1.0));
+      }
+    }
+    forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
+    constexpr int L = S::NS - 1, B = E / S::rad(L);
+#pragma unroll
+    for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const C x = v[j + B * r];
+        kin_acc += gptr<double>(a.ksq)[(unsigned)(r * (S::N / S::rad(L)) + t + T * j)] *
+                   ((double)x.x * x.x + (double)x.y * x.y);
+      }
+    if (!w.active) kin_acc = 0.0;
+    const long at = (long)blockIdx.y * gridDim.x + blockIdx.x, all = (long)gridDim.y * gridDim.x;
+    const double k = block_sum(kin_acc);
+    if (tid == 0) gptr_mut<double>(a.kin_partial)[at] = k;
+    if (a.point_partial) {
+      const double r = block_sum(rho_acc.val()), q = block_sum(int_acc.val());
+      if (tid == 0) { gptr_mut<double>(a.point_partial)[at] = r; gptr_mut<double>(a.point_partial)[all + at] = q; }
+    }
+    return;
+  }
   if constexpr (WIDE) load_tile_wide<S>(v, lds, a.in, tile_pencil, t, col);
   else if constexpr (PRO == PRO_SWAP) {
     const auto src = gptr<C>(a.in) + tile_pencil(col) + t;
@@ -686,18 +751,9 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
   } else load(v, w);
   process(v, w);
 
-  if constexpr (PRO == PRO_KIN) {
-    // fixed-order reduction: wave butterfly, then waves in order (one partial per workgroup)
-    double acc = kin_acc;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-    if ((tid & 63) == 0) red[tid >> 6] = acc;
-    __syncthreads();
-    if (tid == 0) {
-      double s = 0.0;
-      for (int w = 0; w < S::THREADS / 64 + (S::THREADS % 64 ? 1 : 0); ++w) s += red[w];
-      gptr_mut<double>(a.kin_partial)[blockIdx.x] = s;
-    }
+  if constexpr (PRO == PRO_DERIV) {
+    const double s = block_sum(kin_acc);
+    if (tid == 0) gptr_mut<double>(a.kin_partial)[blockIdx.x] = s;
   }
 }
 
@@ -710,7 +766,7 @@ void launch_pass(const PassArgs& a, unsigned grid, unsigned runs, hipStream_t st
 }
 
 // kernel variants compiled for every schedule
-enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_PROP_KIN, V_FWD, V_FWD_DENSITY, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
-               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_COUNT };
+enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_DERIV, V_FWD, V_FWD_DENSITY, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
+               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_ENERGY, V_COUNT };
 
 }  // namespace gpk

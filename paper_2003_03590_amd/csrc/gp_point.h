@@ -48,6 +48,10 @@ void launch_hel_spectral(int prec, const void* V01, const void* V2, const void* 
 // out[3][nj/2] per-axis structure functions from pk[3][nj]
 void launch_structure_axes(const double* pk, int nj, double ntot, double* out, hipStream_t st);
 void launch_segsum(const double* in, long len, int nseg, double* out, hipStream_t st);
+// segment sums of several quantities: quantity q holds, for each of m runs, len[q] numbers
+// from in + first[q] on; out[q][run] (len 0: the sum is 0)
+struct SegLens { long first[5], len[5]; };
+void launch_segsums(const double* in, const SegLens& s, unsigned m, double* out, hipStream_t st);
 void launch_finalize_diag(const double* red, double w0, double w1, double w2, int nshell, double alpha, double beta,
                           double ntot, double* out, hipStream_t st);
 void launch_loss_fields(int prec, const void* psi, const void* d0, const void* d1, const void* d2, void* f0,

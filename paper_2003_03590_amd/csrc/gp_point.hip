@@ -12,16 +12,6 @@
 namespace gpk {
 
 // ----------------------------------------------------------------- helpers
-struct Neu {          // Neumaier compensated sum
-  double s = 0.0, c = 0.0;
-  __device__ __forceinline__ void add(double x) {
-    const double t = s + x;
-    c += (fabs(s) >= fabs(x)) ? (s - t) + x : (x - t) + s;
-    s = t;
-  }
-  __device__ __forceinline__ double val() const { return s + c; }
-};
-
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
@@ -386,6 +376,17 @@ __global__ __launch_bounds__(256) void k_segsum(const double* __restrict__ in, l
   for (long b = threadIdx.x; b < len; b += 256) a.add(seg[b]);
   const double v = block_sum256(a.val(), sh);
   if (threadIdx.x == 0) out[blockIdx.x] = v;
+}
+
+// The same for several quantities at once (block: quantity blockIdx.y of run blockIdx.x).
+__global__ __launch_bounds__(256) void k_segsums(const double* __restrict__ in, SegLens s, double* __restrict__ out) {
+  __shared__ double sh[4];
+  const int q = blockIdx.y;
+  const double* seg = in + s.first[q] + (long)blockIdx.x * s.len[q];
+  Neu a;
+  for (long b = threadIdx.x; b < s.len[q]; b += 256) a.add(seg[b]);
+  const double v = block_sum256(a.val(), sh);
+  if (threadIdx.x == 0) out[q * gridDim.x + blockIdx.x] = v;
 }
 
 // Energies from the reduced sums.  red = [kin_x, kin_y, kin_z, sum rho, sum (rho-1)^2,
@@ -906,6 +907,9 @@ void launch_sup_diff2(int prec, const void* a, const void* b, long n, double* pa
 }
 void launch_segsum(const double* in, long len, int nseg, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_segsum, dim3(nseg), dim3(256), 0, st, in, len, out);
+}
+void launch_segsums(const double* in, const SegLens& s, unsigned m, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_segsums, dim3(m, 5), dim3(256), 0, st, in, s, out);
 }
 void launch_finalize_diag(const double* red, double w0, double w1, double w2, int nshell, double alpha, double beta,
                           double ntot, double* out, hipStream_t st) {

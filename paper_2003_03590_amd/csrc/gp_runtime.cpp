@@ -200,7 +200,17 @@ struct gp_plan_s {
   // ensemble
   bool is_batch = false;
   std::vector<gp_plan_s*> runs;
-  struct Group { int n; std::vector<int> members; RunPtrs* d_ptrs = nullptr; size_t nptrs = 0; };
+  struct Group {
+    int n;
+    std::vector<int> members;
+    RunPtrs* d_ptrs = nullptr;
+    size_t nptrs = 0;
+    double* e_part = nullptr;        // gp_energies_batch: per-workgroup sums of the members ...
+    size_t e_cap = 0;                // ... and how many there is room for
+  };
+  RunPtrs* d_eptrs = nullptr;        // gp_energies_batch: states the step tables do not refer to,
+  RunPtrs* h_eptrs = nullptr;        // and their pinned source
+  double* d_sums = nullptr;          // 5 sums per run
   std::vector<Group> groups;
   // recorded step graphs, [sign: 0 forward, 1 backward][slot] (batch_record)
   static constexpr int GPOW = 8, GBODY = 4, GSLOTS = GBODY + GPOW;
@@ -458,6 +468,7 @@ void plan_free(gp_plan_s* p) {
   for (void* a : p->allocs) (void)hipFree(a);
   for (auto& g : p->groups) if (g.d_ptrs) (void)hipFree(g.d_ptrs);
   if (p->h_result) (void)hipHostFree(p->h_result);
+  if (p->h_eptrs) (void)hipHostFree(p->h_eptrs);
   if (p->rot.work) (void)hipFree(p->rot.work);
   if (p->own_stream && p->stream) (void)hipStreamDestroy(p->stream);
   delete p;
@@ -839,8 +850,7 @@ gp_status derivatives(gp_plan_s* p, const void* psi, void* work, bool kin) {
       HIPCHK(p, hipMemsetAsync(out, 0, p->ntot * p->S, p->stream));
       continue;
     }
-    if ((st = pass(p, a, kin ? V_PROP_KIN : V_PROP, psi, out, p->ax[a].deriv, 0.0, nullptr, 1.0, kin ? kp : nullptr)) !=
-        GP_OK)
+    if ((st = pass(p, a, kin ? V_DERIV : V_PROP, psi, out, p->ax[a].deriv, 0.0, nullptr, 1.0, kin ? kp : nullptr)) != GP_OK)
       return st;
     kp += p->ax[a].blocks;
   }
@@ -1668,6 +1678,35 @@ gp_status gp_plan_batch(const gp_desc* runs, int32_t nruns, void* hip_stream, gp
   p->nshell = p->runs[0]->nshell;
   p->ntot = p->runs[0]->ntot;
   p->own_stream = own_stream;
+  // buffers of gp_energies_batch: per group the sums of every workgroup of the three axis
+  // passes (kinetic) and twice those of one pass (mass, interaction), for whichever
+  // schedules may be selected later
+  auto alloc_failed = [&](gp_status e) {
+    const std::string msg = g_err;
+    plan_free(p);
+    g_err = msg;
+    return e;
+  };
+  for (auto& g : p->groups) {
+    const gp_plan_s* r0 = p->runs[g.members[0]];
+    size_t blocks = 0, most = 0;
+    for (int a = 0; a < 3; ++a) {
+      size_t b = 0;
+      for (const auto& e : registry())
+        if (e.n == r0->ax[a].n && e.prec == r0->prec) b = std::max(b, (size_t)((r0->ax[a].npencils + e.W - 1) / e.W));
+      blocks += b;
+      most = std::max(most, b);
+    }
+    g.e_cap = (blocks + 2 * most) * g.members.size();
+    if ((st = dev_alloc(p, (void**)&g.e_part, g.e_cap * sizeof(double))) != GP_OK) return alloc_failed(st);
+  }
+  if ((st = dev_alloc(p, (void**)&p->d_eptrs, nruns * sizeof(RunPtrs))) != GP_OK) return alloc_failed(st);
+  if ((st = dev_alloc(p, (void**)&p->d_sums, 5 * (size_t)nruns * sizeof(double))) != GP_OK) return alloc_failed(st);
+  if (hipHostMalloc((void**)&p->h_result, 5 * (size_t)nruns * sizeof(double), hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&p->h_eptrs, nruns * sizeof(RunPtrs), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return alloc_failed(fail(GP_ERR_NOMEM, "hipHostMalloc failed"));
+  }
   // one capture branch per further size group, so the groups' launches of a step
   // graph are independent nodes that may run side by side
   for (size_t g = 1; g < p->groups.size(); ++g) {
@@ -1843,15 +1882,85 @@ gp_status gp_energies_batch(gp_plan_t* p, void* const* psis, void* work, double*
   if (st != GP_OK) return st;
   if (!p->is_batch) return fail(GP_ERR_STATE, "not a batch plan");
   if (!psis || !work || !out) return fail(GP_ERR_ARG, "null argument");
-  for (size_t i = 0; i < p->runs.size(); ++i) {
+  for (size_t i = 0; i < p->runs.size(); ++i)
     if (!psis[i]) return fail(GP_ERR_ARG, "null state of run %zu", i);
-    gp_energy e{};
-    if ((st = diagnose(p->runs[i], psis[i], work)) != GP_OK) { p->broken = p->runs[i]->broken; return st; }
-    if ((st = copy_energies(p->runs[i], &e)) != GP_OK) return st;
-    out[2 * i] = e.mass;
-    out[2 * i + 1] = e.energy;
+  // Mass and energy need no 3-D transform: one pass per axis that only reads, transforms along
+  // its axis and sums k^2 |F psi|^2 (and, on the first axis, |psi|^2 and (|psi|^2 - 1)^2),
+  // for all runs of a size at once, and one wait at the end.
+  const bool same = p->graph_key.size() == p->runs.size() &&
+                    std::equal(p->graph_key.begin(), p->graph_key.end(), psis);
+  if (!same) {
+    size_t at = 0;
+    for (const auto& g : p->groups)
+      for (int i : g.members) p->h_eptrs[at++] = RunPtrs{psis[i], nullptr, nullptr, nullptr, 0.0};
+    HIPCHK(p, hipMemcpyAsync(p->d_eptrs, p->h_eptrs, at * sizeof(RunPtrs), hipMemcpyHostToDevice, p->stream));
   }
-  return GP_OK;
+  size_t at = 0;
+  for (const auto& g : p->groups) {
+    const gp_plan_s* r0 = p->runs[g.members[0]];
+    const unsigned m = (unsigned)g.members.size();
+    const RunPtrs* ptrs = same ? g.d_ptrs : p->d_eptrs + at;   // the tables begin with the states
+    double* sums = p->d_sums + 5 * at;                         // [quantity][member]
+    at += m;
+    const int c = first_real_axis(r0);
+    if (c < 0) {                       // a single point has no axis to sum along
+      for (unsigned k = 0; k < m; ++k) {
+        const int i = g.members[k];
+        gp_energy e{};
+        if ((st = diagnose(p->runs[i], psis[i], work)) != GP_OK) { p->broken = p->runs[i]->broken; return st; }
+        if ((st = copy_energies(p->runs[i], &e)) != GP_OK) return st;
+        out[2 * i] = e.mass;
+        out[2 * i + 1] = e.energy;
+      }
+      continue;
+    }
+    double* part = g.e_part;
+    SegLens lens{};
+    for (int a = 0; a < 3; ++a) {
+      const Axis& A = r0->ax[a];
+      lens.first[a] = part - g.e_part;
+      if (A.n == 1) continue;
+      lens.len[a] = A.blocks;
+      PassArgs pa{};
+      pa.batch = ptrs; pa.tw = A.tw; pa.ksq = A.ksq; pa.kin_partial = part;
+      pa.npencils = A.npencils; pa.inner = A.inner; pa.outer = A.outer; pa.es = A.es;
+      part += (size_t)A.blocks * m;
+      if (a == c) {
+        pa.point_partial = part;
+        for (int q = 0; q < 2; ++q) {
+          lens.first[3 + q] = part - g.e_part;
+          lens.len[3 + q] = A.blocks;
+          part += (size_t)A.blocks * m;
+        }
+      }
+      A.e->fn[A.kind][V_ENERGY](pa, A.blocks, m, p->stream);
+      if ((st = check_launch(p)) != GP_OK) return st;
+    }
+    launch_segsums(g.e_part, lens, m, sums, p->stream);
+    if ((st = check_launch(p)) != GP_OK) return st;
+  }
+  HIPCHK(p, hipMemcpyAsync(p->h_result, p->d_sums, 5 * p->runs.size() * sizeof(double), hipMemcpyDeviceToHost,
+                           p->stream));
+  HIPCHK(p, hipStreamSynchronize(p->stream));
+  at = 0;
+  for (const auto& g : p->groups) {
+    const double* s = p->h_result + 5 * at;
+    const size_t m = g.members.size();
+    at += m;
+    if (first_real_axis(p->runs[g.members[0]]) < 0) continue;
+    for (size_t k = 0; k < m; ++k) {
+      const int i = g.members[k];
+      const gp_plan_s* r = p->runs[i];
+      const double nt = (double)r->ntot;
+      double kin = 0.0;
+      for (int a = 0; a < 3; ++a) kin += s[a * m + k] * (1.0 / (nt * r->ax[a].n));
+      out[2 * i] = s[3 * m + k] / nt;
+      out[2 * i + 1] = 2.0 * r->d.alpha * r->d.alpha * kin + r->d.alpha * r->d.beta * s[4 * m + k] / nt;
+      if (!std::isfinite(out[2 * i]) || !std::isfinite(out[2 * i + 1]))
+        st = fail(GP_ERR_NONFINITE, "mass or energy of run %d is not finite", i);
+    }
+  }
+  return st;
 }
 
 // ----------------------------------------------------------------- autotuner
