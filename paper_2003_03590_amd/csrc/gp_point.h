@@ -71,8 +71,11 @@ void launch_argle_energy(int prec, const void* phi, const void* dx, const void* 
                          long n, double alpha, double beta, double* partial, unsigned blocks, hipStream_t st);
 void launch_axis_power(int prec, const void* F, long n, long div, int nj, unsigned blocks, long chunk,
                        double* part, hipStream_t st);
-void launch_init_rvr(int prec, const void* pairs, int npairs, double xi, double a1, double a2, double b1, int nx,
-                     int ny, int nz, void* psi, hipStream_t st);
+// table: npairs * 3 * max(nx, ny, nz) doubles of scratch memory; far: core width, a radius or a
+// separation above kFarRing
+constexpr double kFarRing = 100.0;
+void launch_init_rvr(int prec, const void* pairs, void* table, int npairs, double xi, double a1, double a2, double b1,
+                     bool far, int nx, int ny, int nz, void* psi, hipStream_t st);
 size_t ringpar_bytes();
 void launch_structure_final(const double* pk, int nj, double ntot, double* out, hipStream_t st);
 

@@ -1043,86 +1043,146 @@ void launch_structure_final(const double* pk, int nj, double ntot, double* out, 
 // Initial condition of the random-vortex-ring construction (RVR section): product over
 // pairs of the periodised ring-pair ansatz, evaluated at translated, axis-permuted
 // coordinates.
+//
+// A ring factor is f(r) (dr + i zt)/r with f the Pade profile of r^2 = dr^2 + zt^2.  With
+// u = xi^2, f^2 / r^2 = (a1 u + a2 r^2) / (u^2 + b1 u r^2 + a2 r^4), so the 14 factors of a
+// pair need no root or division of their own: their complex parts, the numerators and the
+// denominators are multiplied up and one root of one quotient closes the pair.  The two
+// rings of a pair meet as (dr + i z1)(dr - i z2) = (dr^2 + z1 z2) - i d dr, z2 = z1 + d.
+// dr depends on two of the three coordinates: a workgroup takes a brick of 8^3 points and
+// keeps the 5 x 64 roots that its points share in LDS (five (x, y) images).  Translated
+// coordinates depend on one, and come from a table.  Bound by FP64 arithmetic: 128^3
+// complex128 with 200 pairs 19.6 ms with three roots and four divisions for each factor.
 struct RingPar { double R, d, X, Y, Z; int perm; };
 
-__device__ __forceinline__ void ring_eval(double x, double y, double z, double R, double xi, double pa1, double pa2,
-                                          double pb1, double* re, double* im) {
-  const double pi = 3.141592653589793238462643383279502884;
-  const double xt = x - pi, yt = y - pi, zt = z - pi;
-  const double dr = sqrt(xt * xt + yt * yt) - R;
-  const double dist = sqrt(dr * dr + zt * zt);
-  if (dist == 0.0) { *re = 0.0; *im = 0.0; return; }
-  const double e2 = (dist / xi) * (dist / xi), e4 = e2 * e2;
-  const double f = sqrt((pa1 * e2 + pa2 * e4) / (1.0 + pb1 * e2 + pa2 * e4));
-  // f exp(i atan2(zt, dr)) = f (dr + i zt) / dist
-  *re = f * dr / dist;
-  *im = f * zt / dist;
-}
-
-// pair ring(z - d/2) * conj(ring(z + d/2))
-__device__ __forceinline__ void pair_eval(double x, double y, double z, double R, double d, double xi, double a1,
-                                          double a2, double b1, double* re, double* im) {
-  double ar, ai, br, bi;
-  ring_eval(x, y, z - 0.5 * d, R, xi, a1, a2, b1, &ar, &ai);
-  ring_eval(x, y, z + 0.5 * d, R, xi, a1, a2, b1, &br, &bi);
-  *re = ar * br + ai * bi;
-  *im = ai * br - ar * bi;
-}
-
-template <class Real>
-__global__ __launch_bounds__(256) void k_init_rvr(const RingPar* __restrict__ pairs, int npairs, double xi, double a1,
-                                                  double a2, double b1, int nx, int ny, int nz, void* psi) {
-  const double two_pi = 6.283185307179586476925286766559;
-  const long n = (long)nx * ny * nz;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long)gridDim.x * blockDim.x) {
-    int ix, iy, iz;
-    grid_xyz(i, nx, ny, ix, iy, iz);
-    const double c[3] = {two_pi * ix / nx, two_pi * iy / ny, two_pi * iz / nz};
-    double pr = 1.0, pim = 0.0;
-    for (int q = 0; q < npairs; ++q) {
-      const RingPar P = pairs[q];
-      // permuted coordinates (x, y, z) -> (c[o0], c[o1], c[o2])
-      int o0, o1, o2;
-      switch (P.perm) {
-        case 0: o0 = 0; o1 = 1; o2 = 2; break;
-        case 1: o0 = 0; o1 = 2; o2 = 1; break;
-        case 2: o0 = 1; o1 = 0; o2 = 2; break;
-        case 3: o0 = 1; o1 = 2; o2 = 0; break;
-        case 4: o0 = 2; o1 = 0; o2 = 1; break;
-        default: o0 = 2; o1 = 1; o2 = 0; break;
-      }
-      double sx = fmod(c[o0] - P.X, two_pi), sy = fmod(c[o1] - P.Y, two_pi), sz = fmod(c[o2] - P.Z, two_pi);
-      if (sx < 0) sx += two_pi;
-      if (sy < 0) sy += two_pi;
-      if (sz < 0) sz += two_pi;
-      // periodised pair: the pair times the conjugates of its six mirror images
-      double tr, ti;
-      pair_eval(sx, sy, sz, P.R, P.d, xi, a1, a2, b1, &tr, &ti);
-      const double L2 = 2.0 * two_pi;
-      const double img[6][3] = {{L2 - sx, sy, sz}, {-sx, sy, sz}, {sx, L2 - sy, sz},
-                                {sx, -sy, sz},     {sx, sy, L2 - sz}, {sx, sy, -sz}};
-#pragma unroll
-      for (int m = 0; m < 6; ++m) {
-        double ur, ui;
-        pair_eval(img[m][0], img[m][1], img[m][2], P.R, P.d, xi, a1, a2, b1, &ur, &ui);
-        const double nr = tr * ur + ti * ui, ni = ti * ur - tr * ui;     // t * conj(u)
-        tr = nr; ti = ni;
-      }
-      const double nr = pr * tr - pim * ti, ni = pr * ti + pim * tr;
-      pr = nr; pim = ni;
-    }
-    stc<Real>(psi, i, pr, pim);
+__device__ __forceinline__ void ring_axes(int perm, int& o0, int& o1, int& o2) {
+  switch (perm) {                  // (x, y, z) -> coordinates (o0, o1, o2) of the pair
+    case 0: o0 = 0; o1 = 1; o2 = 2; break;
+    case 1: o0 = 0; o1 = 2; o2 = 1; break;
+    case 2: o0 = 1; o1 = 0; o2 = 2; break;
+    case 3: o0 = 1; o1 = 2; o2 = 0; break;
+    case 4: o0 = 2; o1 = 0; o2 = 1; break;
+    default: o0 = 2; o1 = 1; o2 = 0; break;
   }
 }
 
-void launch_init_rvr(int prec, const void* pairs, int npairs, double xi, double a1, double a2, double b1, int nx,
-                     int ny, int nz, void* psi, hipStream_t st) {
-  const long n = (long)nx * ny * nz;
+// tab[pair][k][i]: the pair's k-th coordinate (translated, modulo 2 pi) at grid index i of
+// the axis it lies along
+__global__ __launch_bounds__(256) void k_ring_table(const RingPar* __restrict__ pairs, int nx, int ny, int nz, int nmax,
+                                                    double* __restrict__ tab) {
+  const double two_pi = 6.283185307179586476925286766559;
+  const RingPar P = pairs[blockIdx.y];
+  int o[3];
+  ring_axes(P.perm, o[0], o[1], o[2]);
+  const int k = blockIdx.z, i = (int)(blockIdx.x * 256 + threadIdx.x);
+  const int n = o[k] == 0 ? nx : o[k] == 1 ? ny : nz;
+  if (i >= n) return;
+  double s = fmod(two_pi * i / n - (k == 0 ? P.X : k == 1 ? P.Y : P.Z), two_pi);
+  if (s < 0) s += two_pi;
+  tab[((long)blockIdx.y * 3 + k) * nmax + i] = s;
+}
+
+// profile coefficients: f^2/r^2 = (n0 + n1 r^2)/(d0 + d1 r^2 + d2 r^4)
+struct RingProfile { double n0, n1, d0, d1, d2; };
+
+// FAR: lengths so large that products of 14 numerators or denominators may leave the range
+// of FP64; every image then takes its root by itself
+template <class Real, bool FAR>
+__global__ __launch_bounds__(256) void k_init_rvr(const RingPar* __restrict__ pairs, const double* __restrict__ tab,
+                                                  int npairs, RingProfile c, int nx, int ny, int nz, int nmax,
+                                                  void* psi) {
+  constexpr int BR = 8, PL = BR * BR;                 // brick edge, points of one of its planes
+  __shared__ double dr_sh[2][5][PL];
+  const double pi = 3.141592653589793238462643383279502884, four_pi = 4.0 * pi;
+  const int tid = threadIdx.x;
+  const int b0[3] = {(int)blockIdx.x * BR, (int)blockIdx.y * BR, (int)blockIdx.z * BR};
+  const int n[3] = {nx, ny, nz};
+  // points of this thread: (lx, ly, lz) and (lx, ly, lz + 4) of the brick
+  const int lx = tid % BR, ly = (tid / BR) % BR, lz = tid / PL;
+  double pr[2] = {1.0, 1.0}, pim[2] = {0.0, 0.0};
+  for (int q = 0; q < npairs; ++q) {
+    const RingPar P = pairs[q];
+    int o0, o1, o2;
+    ring_axes(P.perm, o0, o1, o2);
+    const double* tx = tab + (long)q * 3 * nmax;
+    const double* ty = tx + nmax;
+    const double* tz = ty + nmax;
+    double (*dr)[PL] = dr_sh[q & 1];
+    // distance to the ring's circle in the plane, for the (x, y) of the point itself and of
+    // its images in x and in y (indices past the grid's end take its last point)
+    for (int w = tid; w < 5 * PL; w += 256) {
+      const int im = w / PL, e = w % PL;
+      const double sx = tx[min(b0[o0] + e % BR, n[o0] - 1)], sy = ty[min(b0[o1] + e / BR, n[o1] - 1)];
+      const double x = (im == 1 ? four_pi - sx : im == 2 ? -sx : sx) - pi;
+      const double y = (im == 3 ? four_pi - sy : im == 4 ? -sy : sy) - pi;
+      dr[im][e] = sqrt(x * x + y * y) - P.R;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int l[3] = {lx, ly, lz + 4 * h};
+      const int e = (o0 == 0 ? l[0] : o0 == 1 ? l[1] : l[2]) + BR * (o1 == 0 ? l[0] : o1 == 1 ? l[1] : l[2]);
+      const int i2 = o2 == 0 ? b0[0] + l[0] : o2 == 1 ? b0[1] + l[1] : b0[2] + l[2];
+      const double sz = tz[min(i2, n[o2] - 1)], hd = 0.5 * P.d;
+      double num = 1.0, den = 1.0, tr = 1.0, ti = 0.0;
+      // one (x, y) image with its two rings at heights z1 and z2 = z1 + d; the factor of the
+      // point itself, or the conjugates of the images
+      auto factor = [&](double r, double z1, double z2, bool image) {
+        const double r2 = r * r, s1 = r2 + z1 * z1, s2 = r2 + z2 * z2;
+        const double n1 = c.n0 + c.n1 * s1, n2 = c.n0 + c.n1 * s2;
+        const double d1 = c.d0 + s1 * (c.d1 + c.d2 * s1), d2 = c.d0 + s2 * (c.d1 + c.d2 * s2);
+        double re = r2 + z1 * z2, im = image ? r * (z2 - z1) : r * (z1 - z2);
+        if constexpr (FAR) {
+          const double g = sqrt(n1 / d1) * sqrt(n2 / d2);
+          re *= g;
+          im *= g;
+        } else {
+          num *= n1 * n2;
+          den *= d1 * d2;
+        }
+        const double a = tr * re - ti * im;
+        ti = tr * im + ti * re;
+        tr = a;
+      };
+      const double z = sz - pi, zu = four_pi - sz - pi, zd = -sz - pi;
+#pragma unroll
+      for (int im = 0; im < 5; ++im) factor(dr[im][e], z - hd, z + hd, im > 0);
+      factor(dr[0][e], zu - hd, zu + hd, true);
+      factor(dr[0][e], zd - hd, zd + hd, true);
+      const double g = FAR ? 1.0 : sqrt(num / den);
+      const double a = g * (pr[h] * tr - pim[h] * ti);
+      pim[h] = g * (pr[h] * ti + pim[h] * tr);
+      pr[h] = a;
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int x = b0[0] + lx, y = b0[1] + ly, z = b0[2] + lz + 4 * h;
+    if (x < nx && y < ny && z < nz) stc<Real>(psi, ((long)z * ny + y) * nx + x, pr[h], pim[h]);
+  }
+}
+
+void launch_init_rvr(int prec, const void* pairs, void* table, int npairs, double xi, double a1, double a2, double b1,
+                     bool far, int nx, int ny, int nz, void* psi, hipStream_t st) {
   const RingPar* pp = reinterpret_cast<const RingPar*>(pairs);
-  if (prec == P_C128)
-    hipLaunchKernelGGL(k_init_rvr<double>, dim3(grid_for(n, 256, 1u << 20)), dim3(256), 0, st, pp, npairs, xi, a1, a2, b1, nx, ny, nz, psi);
-  else
-    hipLaunchKernelGGL(k_init_rvr<float>, dim3(grid_for(n, 256, 1u << 20)), dim3(256), 0, st, pp, npairs, xi, a1, a2, b1, nx, ny, nz, psi);
+  double* tab = reinterpret_cast<double*>(table);
+  const int nmax = std::max(nx, std::max(ny, nz));
+  const double u = std::max(xi * xi, 1e-150);      // u^2 must not vanish at a core
+  const RingProfile c{a1 * u, a2, u * u, b1 * u, a2};
+  for (int q = 0; q < npairs; q += 65535)
+    hipLaunchKernelGGL(k_ring_table, dim3((nmax + 255) / 256, std::min(npairs - q, 65535), 3), dim3(256), 0, st, pp + q,
+                       nx, ny, nz, nmax, tab + (long)q * 3 * nmax);
+  const dim3 grid((nx + 7) / 8, (ny + 7) / 8, (nz + 7) / 8);
+#define GPK_RVR(FAR)                                                                                                   \
+  do {                                                                                                                 \
+    if (prec == P_C128)                                                                                                \
+      hipLaunchKernelGGL((k_init_rvr<double, FAR>), grid, dim3(256), 0, st, pp, tab, npairs, c, nx, ny, nz, nmax, psi); \
+    else                                                                                                               \
+      hipLaunchKernelGGL((k_init_rvr<float, FAR>), grid, dim3(256), 0, st, pp, tab, npairs, c, nx, ny, nz, nmax, psi);  \
+  } while (0)
+  if (far) GPK_RVR(true);
+  else GPK_RVR(false);
+#undef GPK_RVR
 }
 size_t ringpar_bytes() { return sizeof(RingPar); }
 

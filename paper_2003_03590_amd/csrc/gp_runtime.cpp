@@ -1110,19 +1110,23 @@ gp_status gp_init_rvr(gp_plan_t* p, const double* pairs, int32_t npairs, double 
   struct RP { double R, d, X, Y, Z; int perm; };
   if (ringpar_bytes() != sizeof(RP)) return fail(GP_ERR_STATE, "ring parameter layout mismatch");
   std::vector<RP> h(std::max(1, npairs));
+  bool far = !(xi <= kFarRing);
   for (int q = 0; q < npairs; ++q) {
     const double* v = pairs + 6 * q;
     const int perm = (int)v[5];
     if (perm < 0 || perm > 5 || !(v[0] > 0.0)) return fail(GP_ERR_ARG, "pair %d: radius must be > 0, perm in 0..5", q);
     h[q] = RP{v[0], v[1], v[2], v[3], v[4], perm};
+    far = far || !(v[0] <= kFarRing && std::fabs(v[1]) <= kFarRing);
   }
   void* d = nullptr;
-  HIPCHK(p, hipMalloc(&d, h.size() * sizeof(RP)));
+  // the pairs and, after them, their coordinate tables
+  const size_t nmax = (size_t)std::max(p->d.n[0], std::max(p->d.n[1], p->d.n[2]));
+  HIPCHK(p, hipMalloc(&d, h.size() * (sizeof(RP) + 3 * nmax * sizeof(double))));
   hipError_t e = hipMemcpyAsync(d, h.data(), h.size() * sizeof(RP), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) {
     const double s201 = std::sqrt(201.0);
-    launch_init_rvr(p->prec, d, npairs, xi, (73.0 + 3.0 * s201) / 352.0, (6.0 + s201) / 528.0, (21.0 + s201) / 96.0,
-                    p->d.n[0], p->d.n[1], p->d.n[2], psi, p->stream);
+    launch_init_rvr(p->prec, d, (RP*)d + h.size(), npairs, xi, (73.0 + 3.0 * s201) / 352.0, (6.0 + s201) / 528.0, (21.0 + s201) / 96.0,
+                    far, p->d.n[0], p->d.n[1], p->d.n[2], psi, p->stream);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);
