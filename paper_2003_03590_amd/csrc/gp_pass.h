@@ -7,8 +7,8 @@
 //   INV : v <- scale * F_j^-1 v     (natural frequency order in, unnormalised inverse)
 //   TURN: v <- S_2 P S_1 v, S_1 and S_2 two propagator sub-steps along the same axis and P
 //         the pointwise sub-step between them (see below)
-// with optional pointwise prologues (the nonlinear sub-step S(dt, N), its adjoint, the
-// density rho - 1) fused in front of the transform.
+// with optional pointwise prologues (the nonlinear sub-step S(dt, N), its adjoint) fused in
+// front of the transform, and passes that only sum what they transform.
 //
 // Transform structure (time-evolution section: each S(s, L_j) is exact in Fourier space):
 // N = R_0 R_1 ... R_{S-1}; T threads per pencil each hold E = N/T points in registers.
@@ -82,8 +82,11 @@ enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
 // store the state there as well, then rotate it).  PRO_SWAP: none; the pass exchanges the
 // two outer axes of the layout (see pencil_pair).  PRO_ENERGY (FWD): sums only, nothing is
 // stored: k_j^2 |F_j v|^2 and, where point_partial is given, |v|^2 and (|v|^2 - 1)^2.
-enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DENSITY = 3, PRO_DERIV = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
-                PRO_TAPE = 7, PRO_SWAP = 8, PRO_ENERGY = 9 };
+// PRO_POWER, PRO_VPOWER (FWD): power sums only, sum over the tile's pencils of |F_j f|^2 per
+// frequency, f = |v|^2 - 1 or the velocity 2 alpha Im(conj(v) d_j v)/|v|^2 along the axis,
+// whose derivative is taken in the same pass; PRO_VPOWER also sums f^2 (point_partial).
+enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DERIV = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
+                PRO_TAPE = 7, PRO_SWAP = 8, PRO_ENERGY = 9, PRO_POWER = 10, PRO_VPOWER = 11 };
 
 // per-run pointers of a grouped (ensemble) launch: run = blockIdx.y
 struct RunPtrs {
@@ -469,12 +472,22 @@ template <class Real, class S, int KIND, int MODE, int PRO>
 __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
   using C = cplx<Real>;
   constexpr int T = S::T, W = S::W, E = S::E;
-  __shared__ C lds[Lds<S, (int)sizeof(C), KIND>::ELEMS];
+  // (power sums use the buffer for a double per point of the tile)
+  constexpr bool POWER = PRO == PRO_POWER || PRO == PRO_VPOWER;
+  constexpr int EXCH = Lds<S, (int)sizeof(C), KIND>::ELEMS, SUMS = S::N * W * 8 / (int)sizeof(C);
+  __shared__ C lds[POWER && SUMS > EXCH ? SUMS : EXCH];
   __shared__ double red[S::THREADS / 64 + 1];
 
   if (a.batch) {                          // uniform per workgroup
     const RunPtrs r = a.batch[blockIdx.y];
     a.in = r.in; a.out = r.out; a.mult = r.mult; a.mult2 = r.mult2; a.nl_coef = r.nl_coef;
+  }
+  if constexpr (MODE == FWD && PRO == PRO_NONE) {
+    if (!a.batch) {                       // fields that follow one another in memory
+      const long skip = (long)blockIdx.y * a.npencils * S::N * (long)sizeof(C);
+      a.in = (const char*)a.in + skip;
+      a.out = (char*)a.out + skip;
+    }
   }
   const int tid = threadIdx.x;
   int t, col;
@@ -575,9 +588,6 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     if constexpr (MODE == PROP || MODE == FWD) {
       if constexpr (PRO == PRO_NL || PRO == PRO_ADJ_NL) {
         rotate(v, cur);
-      } else if constexpr (PRO == PRO_DENSITY) {
-#pragma unroll
-        for (int e = 0; e < E; ++e) v[e] = mk(cabs2(v[e]) - Real(1), Real(0));
       }
     }
 
@@ -712,6 +722,58 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
 
   C v[E];
   const Where w = where(tile);
+  if constexpr (POWER) {
+    constexpr int L = S::NS - 1, B = E / S::rad(L), RL = S::RL;
+    load(v, w);
+    if constexpr (PRO == PRO_POWER) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) v[e] = mk(cabs2(v[e]) - Real(1), Real(0));
+    } else {
+      forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
+#pragma unroll
+      for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+        for (int j = 0; j < B; ++j)
+          v[j + B * r] = pmul(v[j + B * r], tab_at(mult, r * (S::N / S::rad(L)) + t + T * j));
+      inverse_all<Real, S, KIND, L>(v, lds, t, col, tw);
+      // the points again (from the cache: beside the derivatives they do not fit the registers)
+      const auto inb = gptr<char>(reload(a.in)) + w.bbase * (long)sizeof(C);
+      double v2 = 0.0;
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const C p = *(const GPK_GLOBAL C*)(inb + e * estep + w.loff);
+        const double pr = p.x, pi = p.y, rho = pr * pr + pi * pi;
+        const double f = rho > 0.0 ? a.scale / rho : 0.0;
+        const double vel = f * (pr * (double)v[e].y - pi * (double)v[e].x);
+        v2 += vel * vel;
+        v[e] = mk(Real(vel), Real(0));
+      }
+      const double s = block_sum(w.active ? v2 : 0.0);
+      if (tid == 0) gptr_mut<double>(a.point_partial)[blockIdx.x] = s;
+    }
+    const auto tw2 = gptr<Tab<Real>>(reload(a.tw));
+    forward_all<Real, S, KIND, 0>(v, lds, t, col, tw2);
+    // |F f|^2 of every pencil to LDS, row = position, the columns of a row turned by the
+    // position's group and, in the sums, by the frequency, so that lanes meet in no bank
+    double* sums = reinterpret_cast<double*>(lds);
+    __syncthreads();                        // the last exchange has been read
+#pragma unroll
+    for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const double x = v[j + B * r].x, y = v[j + B * r].y;
+        const int g = t + T * j;
+        sums[(g * RL + r) * W + (col + g) % W] = w.active ? x * x + y * y : 0.0;
+      }
+    __syncthreads();
+    for (int k = tid; k < S::N; k += S::THREADS) {
+      const double* row = sums + freq_pos<S>(k) * W;
+      double s = 0.0;
+      for (int c = 0; c < W; ++c) s += row[(c + k) % W];
+      gptr_mut<double>(a.kin_partial)[(long)blockIdx.x * S::N + k] = s;
+    }
+    return;
+  }
   if constexpr (PRO == PRO_ENERGY) {
     load(v, w);
     Neu rho_acc, int_acc;
@@ -766,7 +828,7 @@ void launch_pass(const PassArgs& a, unsigned grid, unsigned runs, hipStream_t st
 }
 
 // kernel variants compiled for every schedule
-enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_DERIV, V_FWD, V_FWD_DENSITY, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
-               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_ENERGY, V_COUNT };
+enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_DERIV, V_FWD, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
+               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_ENERGY, V_POWER, V_VPOWER, V_COUNT };
 
 }  // namespace gpk

@@ -17,9 +17,6 @@ void launch_spectral(int prec, const void* F0, const void* F1, const void* F2, c
 // out[0] = max over the field of |a - b|^2 (partial: blocks doubles)
 void launch_sup_diff2(int prec, const void* a, const void* b, long n, double* partial, unsigned blocks, double* out,
                       hipStream_t st);
-// in place: d_a <- v_a + 0i (superfluid velocity); partial[3][blocks] = sum v_a^2
-void launch_velocity_fields(int prec, const void* psi, void* d0, void* d1, void* d2, long n, double alpha,
-                            double* partial, unsigned blocks, hipStream_t st);
 // psum, pmax: `blocks` doubles each (sum and max of |w|^2 per block)
 void launch_mach_partials(int prec, const void* psi, const void* d0, const void* d1, const void* d2, long n,
                           double alpha, double* psum, double* pmax, unsigned blocks, hipStream_t st);
@@ -52,8 +49,16 @@ void launch_segsum(const double* in, long len, int nseg, double* out, hipStream_
 // from in + first[q] on; out[q][run] (len 0: the sum is 0)
 struct SegLens { long first[5], len[5]; };
 void launch_segsums(const double* in, const SegLens& s, unsigned m, double* out, hipStream_t st);
-void launch_finalize_diag(const double* red, double w0, double w1, double w2, int nshell, double alpha, double beta,
-                          double ntot, double* out, hipStream_t st);
+// out[chunk][cols]: sums of the columns of in[rows][cols] over `chunks` runs of rows
+unsigned colsum_chunks(long rows);                      // 1 .. 16
+void launch_colsum(const double* in, long rows, int cols, unsigned chunks, double* out, hipStream_t st);
+// the reductions of the diagnostics in one launch: red[0..4] = the five segment sums of one run,
+// red[5] = a sixth over in6[0 .. len6), red[6 ..] = column sums of bins[rows][cols] by chunks
+void launch_diag_reduce(const double* in, const SegLens& s, const double* in6, long len6, const double* bins, long rows,
+                        int cols, unsigned chunks, double* red, hipStream_t st);
+// energies and spectra from red (bin sums still by chunks); out may be pinned host memory
+void launch_finalize_diag(const double* red, unsigned chunks, double w0, double w1, double w2, int nshell, double alpha,
+                          double beta, double ntot, double* out, hipStream_t st);
 void launch_loss_fields(int prec, const void* psi, const void* d0, const void* d1, const void* d2, void* f0,
                         void* f1, long n, double alpha, hipStream_t st);
 void launch_loss_spectral(int prec, void* F0, void* F1, int nx, int ny, int nz, int smin, int smax,
@@ -69,8 +74,6 @@ void launch_argle_solve(int prec, void* P, const void* Q, int nx, int ny, int nz
                         hipStream_t st);
 void launch_argle_energy(int prec, const void* phi, const void* dx, const void* dy, const void* dz, const void* v,
                          long n, double alpha, double beta, double* partial, unsigned blocks, hipStream_t st);
-void launch_axis_power(int prec, const void* F, long n, long div, int nj, unsigned blocks, long chunk,
-                       double* part, hipStream_t st);
 // table: npairs * 3 * max(nx, ny, nz) doubles of scratch memory; far: core width, a radius or a
 // separation above kFarRing
 constexpr double kFarRing = 100.0;

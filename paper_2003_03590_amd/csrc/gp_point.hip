@@ -363,7 +363,7 @@ __global__ __launch_bounds__(64) void k_spectral(const void* F0, const void* F1,
     for (int q = 0; q < 4; ++q) atomicAdd(&bins[q * nshell + cur], acc[q]);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 4 * nshell; i += 64) bins_partial[(long)i * gridDim.x + blockIdx.x] = bins[i];
+  for (int i = threadIdx.x; i < 4 * nshell; i += 64) bins_partial[(long)blockIdx.x * 4 * nshell + i] = bins[i];
 }
 
 // Deterministic segmented sum: out[q] = sum_{b < len} in[q * len + b] for q < nseg.
@@ -389,24 +389,81 @@ __global__ __launch_bounds__(256) void k_segsums(const double* __restrict__ in, 
   if (threadIdx.x == 0) out[q * gridDim.x + blockIdx.x] = v;
 }
 
+// Column sums of in[rows][cols] for rows r0 .. r1 and columns c0 .. c0 + 31 into out[c0 ..]: lane c
+// of 32 row groups takes every 32nd row (compensated), then the groups in order.
+__device__ __forceinline__ void column_sums(const double* __restrict__ in, long r0, long r1, int cols, int c0,
+                                            double* __restrict__ out, double* sh) {
+  const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
+  Neu a;
+  if (c0 + c < cols)
+    for (long r = r0 + g; r < r1; r += 32) a.add(in[r * cols + c0 + c]);
+  sh[g * 33 + c] = a.val();
+  __syncthreads();
+  if (g == 0 && c0 + c < cols) {
+    Neu b;
+    for (int k = 0; k < 32; ++k) b.add(sh[k * 33 + c]);
+    out[c0 + c] = b.val();
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_colsum(const double* __restrict__ in, long rows, int cols,
+                                                 double* __restrict__ out) {
+  __shared__ double sh[32 * 33];
+  const long per = (rows + gridDim.y - 1) / gridDim.y, r0 = blockIdx.y * per, r1 = r0 + per < rows ? r0 + per : rows;
+  column_sums(in, r0, r1, cols, (int)blockIdx.x * 32, out + (long)blockIdx.y * cols, sh);
+}
+
+// the diagnostics' reductions (launch_diag_reduce): blocks 0 .. 5 the scalars, the rest the bins
+__global__ __launch_bounds__(1024) void k_diag_reduce(const double* __restrict__ in, SegLens s,
+                                                      const double* __restrict__ in6, long len6,
+                                                      const double* __restrict__ bins, long rows, int cols, int chunks,
+                                                      double* __restrict__ red) {
+  __shared__ double sh[32 * 33];
+  if (blockIdx.x < 6) {
+    const int q = blockIdx.x;
+    const double* seg = q < 5 ? in + s.first[q] : in6;
+    const long len = q < 5 ? s.len[q] : len6;
+    Neu a;
+    for (long b = threadIdx.x; b < len; b += 1024) a.add(seg[b]);
+    const double v = wave_sum(a.val());
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      Neu t;
+      for (int w = 0; w < 16; ++w) t.add(sh[w]);
+      red[q] = t.val();
+    }
+    return;
+  }
+  const int tiles = (cols + 31) / 32, b = (int)blockIdx.x - 6, chunk = b / tiles;
+  const long per = (rows + chunks - 1) / chunks, r0 = chunk * per, r1 = r0 + per < rows ? r0 + per : rows;
+  column_sums(bins, r0, r1, cols, (b % tiles) * 32, red + 6 + (long)chunk * cols, sh);
+}
+
 // Energies from the reduced sums.  red = [kin_x, kin_y, kin_z, sum rho, sum (rho-1)^2,
-// sum |w|^2, spectra[4][nshell]]; out[0..6] = gp_energy, out[7..] = spectra.
-__global__ __launch_bounds__(256) void k_finalize_diag(const double* __restrict__ red, double kin_w0, double kin_w1,
-                                                       double kin_w2, int nshell, double alpha, double beta,
-                                                       double ntot, double* __restrict__ out) {
-  const double* spec = red + 6;
-  for (int q = threadIdx.x; q < 4 * nshell; q += 256) out[7 + q] = spec[q];
+// sum |w|^2, spectra[chunks][4][nshell]]; out[0..6] = gp_energy, out[7..] = spectra.
+__global__ __launch_bounds__(256) void k_finalize_diag(const double* __restrict__ red, int chunks, double kin_w0,
+                                                       double kin_w1, double kin_w2, int nshell, double alpha,
+                                                       double beta, double ntot, double* __restrict__ out) {
+  extern __shared__ double spec[];            // [4][nshell]
+  for (int q = threadIdx.x; q < 4 * nshell; q += 256) {
+    Neu a;
+    for (int c = 0; c < chunks; ++c) a.add(red[6 + (long)c * 4 * nshell + q]);
+    spec[q] = a.val();
+    out[7 + q] = spec[q];
+  }
+  __syncthreads();
+  const int row = threadIdx.x >> 6, lane = threadIdx.x & 63;      // one wavefront per spectrum
+  Neu e;
+  for (int s = lane; s < nshell; s += 64) e.add(spec[row * nshell + s]);
+  const double sum = wave_sum(e.val());
+  if (lane == 0 && row < 3) out[3 + row] = sum;
   if (threadIdx.x == 0) {
-    Neu ei, ec, eq;
-    for (int s = 0; s < nshell; ++s) { ei.add(spec[s]); ec.add(spec[nshell + s]); eq.add(spec[2 * nshell + s]); }
     const double kin_grad = red[0] * kin_w0 + red[1] * kin_w1 + red[2] * kin_w2;
     const double e_int = alpha * beta * red[4] / ntot;
     out[0] = red[3] / ntot;                           // mass
     out[1] = 2.0 * alpha * alpha * kin_grad + e_int;  // energy
     out[2] = 0.5 * red[5] / ntot;                     // e_kin
-    out[3] = ei.val();
-    out[4] = ec.val();
-    out[5] = eq.val();
     out[6] = e_int;
   }
 }
@@ -538,78 +595,22 @@ __global__ void k_phase_grad(const void* psi0, const void* lam0, double* out, lo
 }
 
 // ----------------------------------------------------------------- structure function
-// Per-axis power sums P_j(k) = sum over pencils |F_j(rho - 1)|^2 (natural order along
-// axis j).  F holds the axis-j transform; axis j index of element i is (i / div) % nj.
-__global__ __launch_bounds__(64) void k_axis_power_c128(const void* F, long n, long div, int nj, long chunk,
-                                                        double* __restrict__ part);
-__global__ __launch_bounds__(64) void k_axis_power_c64(const void* F, long n, long div, int nj, long chunk,
-                                                       double* __restrict__ part);
-
-template <class Real>
-__device__ __forceinline__ void axis_power(const void* F, long n, long div, int nj, long chunk, double* part) {
-  extern __shared__ double bins[];
-  for (int i = threadIdx.x; i < nj; i += 64) bins[i] = 0.0;
-  __syncthreads();
-  const long i0 = (long)blockIdx.x * chunk;
-  const long i1 = (i0 + chunk < n) ? i0 + chunk : n;
-  for (long i = i0 + threadIdx.x; i < i1; i += 64) {
-    const cplx<Real> z = ldc<Real>(F, i);
-    atomicAdd(&bins[(i / div) % nj], (double)z.x * z.x + (double)z.y * z.y);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < nj; i += 64) part[(long)i * gridDim.x + blockIdx.x] = bins[i];
-}
-__global__ __launch_bounds__(64) void k_axis_power_c128(const void* F, long n, long div, int nj, long chunk, double* part) {
-  axis_power<double>(F, n, div, nj, chunk, part);
-}
-__global__ __launch_bounds__(64) void k_axis_power_c64(const void* F, long n, long div, int nj, long chunk, double* part) {
-  axis_power<float>(F, n, div, nj, chunk, part);
-}
-
 // S(m) = (1/3) sum_j 2/(Ntot N_j) sum_k P_j(k) (1 - cos(2 pi k m / N_j)), m = 1..N/2,
-// from the reduced power sums pk[axis][k].
+// from the reduced power sums pk[axis][k].  One block per lag.
 __global__ __launch_bounds__(256) void k_structure_final(const double* __restrict__ pk, int nj, double ntot,
                                                          double* __restrict__ out) {
-  for (int m = 1 + threadIdx.x; m <= nj / 2; m += 256) {
-    Neu a;
-    for (int ax = 0; ax < 3; ++ax)
-      for (int k = 0; k < nj; ++k) {
-        const long km = ((long)k * m) % nj;
-        a.add(pk[ax * nj + k] * (1.0 - cospi(2.0 * (double)km / (double)nj)));
-      }
-    out[m - 1] = a.val() * 2.0 / (3.0 * ntot * (double)nj);
+  __shared__ double sh[4];
+  const int m = (int)blockIdx.x + 1;
+  Neu a;
+  for (int q = threadIdx.x; q < 3 * nj; q += 256) {
+    const long km = ((long)(q % nj) * m) % nj;
+    a.add(pk[q] * (1.0 - cospi(2.0 * (double)km / (double)nj)));
   }
+  const double s = block_sum256(a.val(), sh);
+  if (threadIdx.x == 0) out[m - 1] = s * 2.0 / (3.0 * ntot * (double)nj);
 }
 
 // ----------------------------------------------------------------- velocity statistics
-// Superfluid velocity v = 2 alpha Im(conj(psi) grad psi)/|psi|^2 (0 where psi = 0).
-// In: d0, d1, d2 = spectral derivatives of psi along x, y, z.  Out (in place):
-// d_a = v_a + 0i for the transform along axis a; partial[a][block] = sum v_a^2.
-template <class Real>
-__global__ __launch_bounds__(256) void k_velocity_fields(const void* psi, void* d0, void* d1, void* d2, unsigned n,
-                                                         double alpha, double* __restrict__ partial) {
-  __shared__ double sh[4];
-  Neu acc[3];
-  void* d[3] = {d0, d1, d2};
-  for (unsigned i = blockIdx.x * 256u + threadIdx.x; i < n; i += gridDim.x * 256u) {
-    const cplx<Real> p = ldc<Real>(psi, i);
-    const double pr = p.x, pi = p.y, rho = pr * pr + pi * pi;
-    const double f = rho > 0.0 ? 2.0 * alpha / rho : 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const cplx<Real> g = ldc<Real>(d[a], i);
-      const double v = f * (pr * (double)g.y - pi * (double)g.x);
-      stc<Real>(d[a], i, v, 0.0);
-      acc[a].add(v * v);
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const double t = block_sum256(acc[a].val(), sh);
-    if (threadIdx.x == 0) partial[(long)a * gridDim.x + blockIdx.x] = t;
-  }
-}
-
 // Mach-number partials: sum |w|^2 and max |w|^2 per block, w = sqrt(rho) v.
 template <class Real>
 __global__ __launch_bounds__(256) void k_mach_partials(const void* psi, const void* d0, const void* d1, const void* d2,
@@ -641,19 +642,19 @@ __global__ __launch_bounds__(256) void k_mach_partials(const void* psi, const vo
 }
 
 // Per-axis structure functions S_a(m) = 2/(Ntot N) sum_k P_a(k) (1 - cos(2 pi k m / N)),
-// m = 1..N/2, from the reduced power sums pk[axis][k] of v_a transformed along axis a.
+// m = 1..N/2, from the reduced power sums pk[axis][k] of v_a transformed along axis a.  One
+// block per lag and axis.
 __global__ __launch_bounds__(256) void k_structure_axes(const double* __restrict__ pk, int nj, double ntot,
                                                         double* __restrict__ out) {
-  const int half = nj / 2;
-  for (int q = threadIdx.x; q < 3 * half; q += 256) {
-    const int ax = q / half, m = q % half + 1;
-    Neu a;
-    for (int k = 0; k < nj; ++k) {
-      const long km = ((long)k * m) % nj;
-      a.add(pk[ax * nj + k] * (1.0 - cospi(2.0 * (double)km / (double)nj)));
-    }
-    out[q] = a.val() * 2.0 / (ntot * (double)nj);
+  __shared__ double sh[4];
+  const int m = (int)blockIdx.x + 1, ax = blockIdx.y;
+  Neu a;
+  for (int k = threadIdx.x; k < nj; k += 256) {
+    const long km = ((long)k * m) % nj;
+    a.add(pk[ax * nj + k] * (1.0 - cospi(2.0 * (double)km / (double)nj)));
   }
+  const double s = block_sum256(a.val(), sh);
+  if (threadIdx.x == 0) out[ax * gridDim.x + m - 1] = s * 2.0 / (ntot * (double)nj);
 }
 
 // ----------------------------------------------------------------- helicity
@@ -835,7 +836,7 @@ __global__ __launch_bounds__(64) void k_hel_spectral(const void* V01, const void
     atomicAdd(&bins[nshell + s], hr);
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < 2 * nshell; i += 64) bins_partial[(long)i * gridDim.x + blockIdx.x] = bins[i];
+  for (int i = threadIdx.x; i < 2 * nshell; i += 64) bins_partial[(long)blockIdx.x * 2 * nshell + i] = bins[i];
 }
 
 // every point <- (re, im)
@@ -911,9 +912,19 @@ void launch_segsum(const double* in, long len, int nseg, double* out, hipStream_
 void launch_segsums(const double* in, const SegLens& s, unsigned m, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_segsums, dim3(m, 5), dim3(256), 0, st, in, s, out);
 }
-void launch_finalize_diag(const double* red, double w0, double w1, double w2, int nshell, double alpha, double beta,
-                          double ntot, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_finalize_diag, dim3(1), dim3(256), 0, st, red, w0, w1, w2, nshell, alpha, beta, ntot, out);
+unsigned colsum_chunks(long rows) { return (unsigned)std::min(16L, (rows + 31) / 32); }
+void launch_colsum(const double* in, long rows, int cols, unsigned chunks, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_colsum, dim3((cols + 31) / 32, chunks), dim3(1024), 0, st, in, rows, cols, out);
+}
+void launch_diag_reduce(const double* in, const SegLens& s, const double* in6, long len6, const double* bins, long rows,
+                        int cols, unsigned chunks, double* red, hipStream_t st) {
+  hipLaunchKernelGGL(k_diag_reduce, dim3(6 + chunks * (unsigned)((cols + 31) / 32)), dim3(1024), 0, st, in, s, in6, len6,
+                     bins, rows, cols, (int)chunks, red);
+}
+void launch_finalize_diag(const double* red, unsigned chunks, double w0, double w1, double w2, int nshell, double alpha,
+                          double beta, double ntot, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(k_finalize_diag, dim3(1), dim3(256), 4 * (size_t)nshell * sizeof(double), st, red, (int)chunks, w0, w1,
+                     w2, nshell, alpha, beta, ntot, out);
 }
 void launch_loss_fields(int prec, const void* psi, const void* d0, const void* d1, const void* d2, void* f0, void* f1,
                         long n, double alpha, hipStream_t st) {
@@ -961,19 +972,6 @@ void launch_argle_energy(int prec, const void* phi, const void* dx, const void* 
 void launch_phase_grad(int prec, const void* psi0, const void* lam0, double* out, long n, hipStream_t st) {
   if (prec == P_C128) hipLaunchKernelGGL(k_phase_grad<double>, dim3(grid_for(n, 256)), dim3(256), 0, st, psi0, lam0, out, n);
   else hipLaunchKernelGGL(k_phase_grad<float>, dim3(grid_for(n, 256)), dim3(256), 0, st, psi0, lam0, out, n);
-}
-void launch_axis_power(int prec, const void* F, long n, long div, int nj, unsigned blocks, long chunk, double* part,
-                       hipStream_t st) {
-  const size_t sh = sizeof(double) * (size_t)nj;
-  if (prec == P_C128) hipLaunchKernelGGL(k_axis_power_c128, dim3(blocks), dim3(64), sh, st, F, n, div, nj, chunk, part);
-  else hipLaunchKernelGGL(k_axis_power_c64, dim3(blocks), dim3(64), sh, st, F, n, div, nj, chunk, part);
-}
-void launch_velocity_fields(int prec, const void* psi, void* d0, void* d1, void* d2, long n, double alpha,
-                            double* partial, unsigned blocks, hipStream_t st) {
-  if (prec == P_C128)
-    hipLaunchKernelGGL(k_velocity_fields<double>, dim3(blocks), dim3(256), 0, st, psi, d0, d1, d2, (unsigned)n, alpha, partial);
-  else
-    hipLaunchKernelGGL(k_velocity_fields<float>, dim3(blocks), dim3(256), 0, st, psi, d0, d1, d2, (unsigned)n, alpha, partial);
 }
 void launch_mach_partials(int prec, const void* psi, const void* d0, const void* d1, const void* d2, long n,
                           double alpha, double* psum, double* pmax, unsigned blocks, hipStream_t st) {
@@ -1033,10 +1031,10 @@ void launch_segmax(const double* in, long len, double* out, hipStream_t st) {
   hipLaunchKernelGGL(k_segmax, dim3(1), dim3(256), 0, st, in, len, out);
 }
 void launch_structure_axes(const double* pk, int nj, double ntot, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_structure_axes, dim3(1), dim3(256), 0, st, pk, nj, ntot, out);
+  hipLaunchKernelGGL(k_structure_axes, dim3(nj / 2, 3), dim3(256), 0, st, pk, nj, ntot, out);
 }
 void launch_structure_final(const double* pk, int nj, double ntot, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_structure_final, dim3(1), dim3(256), 0, st, pk, nj, ntot, out);
+  hipLaunchKernelGGL(k_structure_final, dim3(nj / 2), dim3(256), 0, st, pk, nj, ntot, out);
 }
 
 // ----------------------------------------------------------------- random vortex rings

@@ -58,11 +58,12 @@ void fill(PassEntry& e) {
   e.fn[KIND][V_PROP_NL] = &launch_pass<Real, S, KIND, PROP, PRO_NL>;
   e.fn[KIND][V_DERIV] = &launch_pass<Real, S, KIND, PROP, PRO_DERIV>;
   e.fn[KIND][V_FWD] = &launch_pass<Real, S, KIND, FWD, PRO_NONE>;
-  e.fn[KIND][V_FWD_DENSITY] = &launch_pass<Real, S, KIND, FWD, PRO_DENSITY>;
   e.fn[KIND][V_INV] = &launch_pass<Real, S, KIND, INV, PRO_NONE>;
   e.fn[KIND][V_PROP_ARGLE] = &launch_pass<Real, S, KIND, PROP, PRO_ARGLE>;
   e.fn[KIND][V_FWD_MULT3] = &launch_pass<Real, S, KIND, FWD, PRO_MULT3>;
   e.fn[KIND][V_ENERGY] = &launch_pass<Real, S, KIND, FWD, PRO_ENERGY>;
+  e.fn[KIND][V_POWER] = &launch_pass<Real, S, KIND, FWD, PRO_POWER>;
+  e.fn[KIND][V_VPOWER] = &launch_pass<Real, S, KIND, FWD, PRO_VPOWER>;
   e.fn[KIND][V_TURN] = &launch_pass<Real, S, KIND, TURN, PRO_NL>;
   // the stage exchanges order a swapping tile's reads before its writes
   if constexpr (KIND == CONTIG && S::NS > 1) e.fn[KIND][V_PROP_SWAP] = &launch_pass<Real, S, KIND, PROP, PRO_SWAP>;

@@ -165,11 +165,9 @@ struct gp_plan_s {
   double* bins_part = nullptr;     // spec_blocks * 4 * nshell
   unsigned spec_blocks = 0;
   long spec_chunk = 0;
-  double* power_part = nullptr;    // 3 * pow_blocks * nx
-  unsigned pow_blocks = 0;
-  long pow_chunk = 0;
+  double* power_part = nullptr;    // 3 * 16 * nmax: power sums by chunks of tiles
   double* loss_part = nullptr;     // field_blocks
-  double* d_red = nullptr;         // 6 + 4 * nshell reduced sums
+  double* d_red = nullptr;         // 6 + 16 * 4 * nshell reduced sums
   double* d_pk = nullptr;          // 3 * nmax reduced axis power sums
   double* d_result = nullptr;      // 8 + 4 * nshell
   double* h_result = nullptr;      // pinned mirror
@@ -432,21 +430,20 @@ gp_status plan_init(gp_plan_s* p, const gp_desc* d, hipStream_t stream) {
   // reduction partials
   const long kin_n = (long)p->ax[0].blocks + p->ax[1].blocks + p->ax[2].blocks;
   if ((st = dev_alloc(p, (void**)&p->kin_part, std::max(1L, kin_n) * sizeof(double))) != GP_OK) return st;
-  p->field_blocks = (unsigned)std::min<long>(1024, std::max<long>(1, (p->ntot + 4095) / 4096));
+  // enough workgroups for small grids too: 8 of them took 18 and 46 us at 32^3
+  p->field_blocks = (unsigned)std::min<long>(1024, std::max<long>(1, (p->ntot + 511) / 512));
   if ((st = dev_alloc(p, (void**)&p->field_part, 3 * p->field_blocks * sizeof(double))) != GP_OK) return st;
   if ((st = dev_alloc(p, (void**)&p->loss_part, p->field_blocks * sizeof(double))) != GP_OK) return st;
-  p->spec_blocks = (unsigned)std::min<long>(2048, std::max<long>(1, (p->ntot + 4095) / 4096));
+  p->spec_blocks = (unsigned)std::min<long>(2048, std::max<long>(1, (p->ntot + 511) / 512));
   p->spec_chunk = (p->ntot + p->spec_blocks - 1) / p->spec_blocks;
   if ((st = dev_alloc(p, (void**)&p->bins_part, (size_t)p->spec_blocks * 4 * p->nshell * sizeof(double))) != GP_OK)
     return st;
-  p->pow_blocks = p->spec_blocks;
-  p->pow_chunk = p->spec_chunk;
   const int nmax = std::max(d->n[0], std::max(d->n[1], d->n[2]));
-  if ((st = dev_alloc(p, (void**)&p->power_part, 3 * (size_t)p->pow_blocks * nmax * sizeof(double))) != GP_OK)
+  if ((st = dev_alloc(p, (void**)&p->power_part, 3 * 16 * (size_t)nmax * sizeof(double))) != GP_OK)
     return st;
   if ((st = dev_alloc(p, (void**)&p->d_result, (8 + 4 * (size_t)p->nshell + nmax) * sizeof(double))) != GP_OK)
     return st;
-  if ((st = dev_alloc(p, (void**)&p->d_red, (6 + 4 * (size_t)p->nshell) * sizeof(double))) != GP_OK) return st;
+  if ((st = dev_alloc(p, (void**)&p->d_red, (6 + 16 * 4 * (size_t)p->nshell) * sizeof(double))) != GP_OK) return st;
   if ((st = dev_alloc(p, (void**)&p->d_pk, 3 * (size_t)nmax * sizeof(double))) != GP_OK) return st;
   hipError_t e = hipHostMalloc((void**)&p->h_result, (8 + 4 * (size_t)p->nshell + nmax) * sizeof(double),
                                hipHostMallocDefault);
@@ -510,15 +507,17 @@ gp_status usable_single(const gp_plan_s* p) {
 }
 
 // ----------------------------------------------------------------- pass launch
+constexpr size_t kLastLevelCache = (size_t)256 << 20;
+
 gp_status pass(gp_plan_s* p, int a, int var, const void* in, void* out, const void* mult, double nl_coef = 0.0,
-               const void* aux = nullptr, double scale = 1.0, double* kin = nullptr) {
+               const void* aux = nullptr, double scale = 1.0, double* kin = nullptr, unsigned fields = 1) {
   Axis& A = p->ax[a];
   if (A.n == 1) {
     // one point along the axis: the transform is the identity and k = 0, so the
     // propagator tables are 1 (derivatives are handled by the callers)
-    if (var == V_PROP_NL || var == V_PROP_ADJ || var == V_FWD_DENSITY)
+    if (var == V_PROP_NL || var == V_PROP_ADJ)
       return fail(GP_ERR_STATE, "internal: fused prologue on an axis of length 1");
-    if (in != out || scale != 1.0) launch_scale_copy(p->prec, in, out, p->ntot, scale, p->stream);
+    if (in != out || scale != 1.0) launch_scale_copy(p->prec, in, out, p->ntot * fields, scale, p->stream);
     return check_launch(p);
   }
   PassArgs g{};
@@ -526,7 +525,7 @@ gp_status pass(gp_plan_s* p, int a, int var, const void* in, void* out, const vo
   g.in = in; g.out = out; g.mult = mult; g.tw = A.tw; g.aux = aux;
   g.ksq = A.ksq; g.kin_partial = kin; g.nl_coef = nl_coef; g.scale = scale;
   g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
-  A.e->fn[A.kind][var](g, A.blocks, 1, p->stream);
+  A.e->fn[A.kind][var](g, A.blocks, fields, p->stream);
   return check_launch(p);
 }
 
@@ -615,7 +614,6 @@ gp_status stage_swap(gp_plan_s* p, void* psi, int tau) {
 // the z rows cost nothing extra and the scattered pencils do: 256^3 complex128 0.203 and
 // 0.205, 128^3 complex64 0.032 and 0.037.  Not where the caller took x as the carrier
 // (the x passes then turn).
-constexpr size_t kLastLevelCache = (size_t)256 << 20;
 bool swaps(const gp_plan_s* p) {
   const int n = p->ax[1].n;
   return (size_t)p->ntot * p->S > kLastLevelCache && !p->plane.on && p->nl_axis != 0 && p->ax[0].n > 1 && n > 1 &&
@@ -803,11 +801,18 @@ gp_status fft3(gp_plan_s* p, const void* in, void* out, int dir) {
   return GP_OK;
 }
 
-// unnormalised forward 3-D transform in place
-gp_status fwd3_unnorm(gp_plan_s* p, void* f) {
+// unnormalised forward 3-D transforms in place of `count` fields that follow one another:
+// all at once as long as they stay in the last-level cache together (a 32^3 pass takes
+// less than its launch), else one after another, so that each finds itself there
+gp_status fwd3_unnorm(gp_plan_s* p, void* f, unsigned count = 1) {
   gp_status st;
-  for (int a = 0; a < 3; ++a)
-    if ((st = pass(p, a, V_FWD, f, f, nullptr, 0.0, nullptr, 1.0)) != GP_OK) return st;
+  const size_t bytes = (size_t)p->ntot * p->S;
+  const unsigned group = count * bytes <= kLastLevelCache ? count : 1;
+  for (unsigned i = 0; i < count; i += group) {
+    void* g = (char*)f + i * bytes;
+    for (int a = 0; a < 3; ++a)
+      if ((st = pass(p, a, V_FWD, g, g, nullptr, 0.0, nullptr, 1.0, nullptr, group)) != GP_OK) return st;
+  }
   return GP_OK;
 }
 // unnormalised forward 3-D transform in place, the last pass multiplying by the 3-D
@@ -866,30 +871,30 @@ gp_status diagnose(gp_plan_s* p, const void* psi, void* work) {
   void* f3 = field(p, work, 3);
   launch_diag_fields(p->prec, psi, f0, f1, f2, f3, p->ntot, p->d.alpha, p->field_part, p->field_blocks, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  for (void* f : {f0, f1, f2, f3})
-    if ((st = fwd3_unnorm(p, f)) != GP_OK) return st;
+  if ((st = fwd3_unnorm(p, f0, 4)) != GP_OK) return st;
   launch_spectral(p->prec, f0, f1, f2, f3, p->d.n[0], p->d.n[1], p->d.n[2], p->d.alpha, p->d.beta, p->nshell,
                   p->spec_blocks, p->bins_part, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  // fixed-order reductions of every partial into red = [kin_x, kin_y, kin_z, field[3], spectra[4][nshell]]
+  // fixed-order reductions of every partial into red = [kin_x, kin_y, kin_z, field[3],
+  // spectra[chunks][4][nshell]]; the results go straight to the pinned host copy
   const double nt = (double)p->ntot;
-  double* red = p->d_red;
-  double* kp = p->kin_part;
+  SegLens lens{};
+  long at = 0;
   for (int a = 0; a < 3; ++a) {
-    if (p->ax[a].n > 1) {
-      launch_segsum(kp, p->ax[a].blocks, 1, red + a, p->stream);
-      kp += p->ax[a].blocks;
-    } else {
-      HIPCHK(p, hipMemsetAsync(red + a, 0, sizeof(double), p->stream));
-    }
+    lens.first[a] = at;
+    lens.len[a] = p->ax[a].n > 1 ? p->ax[a].blocks : 0;
+    at += lens.len[a];
   }
-  launch_segsum(p->field_part, p->field_blocks, 3, red + 3, p->stream);
-  launch_segsum(p->bins_part, p->spec_blocks, 4 * p->nshell, red + 6, p->stream);
-  launch_finalize_diag(red, 1.0 / (nt * p->ax[0].n), 1.0 / (nt * p->ax[1].n), 1.0 / (nt * p->ax[2].n), p->nshell,
-                       p->d.alpha, p->d.beta, nt, p->d_result, p->stream);
+  for (int q = 0; q < 2; ++q) {      // sum rho, sum (rho - 1)^2
+    lens.first[3 + q] = (p->field_part - p->kin_part) + (long)q * p->field_blocks;
+    lens.len[3 + q] = p->field_blocks;
+  }
+  const unsigned chunks = colsum_chunks(p->spec_blocks);
+  launch_diag_reduce(p->kin_part, lens, p->field_part + 2 * (size_t)p->field_blocks, p->field_blocks, p->bins_part,
+                     p->spec_blocks, 4 * p->nshell, chunks, p->d_red, p->stream);
+  launch_finalize_diag(p->d_red, chunks, 1.0 / (nt * p->ax[0].n), 1.0 / (nt * p->ax[1].n), 1.0 / (nt * p->ax[2].n),
+                       p->nshell, p->d.alpha, p->d.beta, nt, p->h_result, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  const size_t bytes = (7 + 4 * (size_t)p->nshell) * sizeof(double);
-  HIPCHK(p, hipMemcpyAsync(p->h_result, p->d_result, bytes, hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));
   return GP_OK;
 }
@@ -1235,6 +1240,23 @@ gp_status gp_spectra(gp_plan_t* p, const void* psi, void* work, double* out, int
   return st;
 }
 
+// d_pk[axis] = power sums along the axis over all pencils (V_POWER, V_VPOWER); rows of n sums
+// per tile in the caller's workspace (8 n bytes for every W pencils); sq: per-tile sums of
+// the velocity squared
+static gp_status power_sums(gp_plan_s* p, int a, int var, const void* psi, void* work, double* sq) {
+  const Axis& A = p->ax[a];
+  double* rows = (double*)work;
+  PassArgs g{};
+  g.in = psi; g.tw = A.tw; g.mult = A.deriv; g.scale = 2.0 * p->d.alpha; g.kin_partial = rows; g.point_partial = sq;
+  g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
+  A.e->fn[A.kind][var](g, A.blocks, 1, p->stream);
+  const unsigned chunks = colsum_chunks(A.blocks);
+  double* part = p->power_part + (size_t)a * 16 * A.n;
+  launch_colsum(rows, A.blocks, A.n, chunks, chunks > 1 ? part : p->d_pk + (size_t)a * A.n, p->stream);
+  if (chunks > 1) launch_colsum(part, chunks, A.n, 1, p->d_pk + (size_t)a * A.n, p->stream);
+  return check_launch(p);
+}
+
 gp_status gp_structure_fn(gp_plan_t* p, const void* psi, void* work, int32_t p_order, double* out) {
   gp_status st = usable_single(p);
   if (st != GP_OK) return st;
@@ -1243,20 +1265,11 @@ gp_status gp_structure_fn(gp_plan_t* p, const void* psi, void* work, int32_t p_o
   const int n = p->d.n[0];
   if (p->d.n[1] != n || p->d.n[2] != n) return fail(GP_ERR_UNSUPPORTED, "structure function needs a cubic grid");
   if (n < 2) return fail(GP_ERR_UNSUPPORTED, "structure function needs n >= 2");
-  void* f = field(p, work, 0);
-  const long div[3] = {1, n, (long)n * n};
-  for (int a = 0; a < 3; ++a) {
-    // F_a(|psi|^2 - 1), natural order along axis a
-    if ((st = pass(p, a, V_FWD_DENSITY, psi, f, nullptr, 0.0, nullptr, 1.0)) != GP_OK) return st;
-    launch_axis_power(p->prec, f, p->ntot, div[a], n, p->pow_blocks, p->pow_chunk,
-                      p->power_part + (size_t)a * p->pow_blocks * n, p->stream);
-    if ((st = check_launch(p)) != GP_OK) return st;
-  }
-  // power_part = [axis][k][block] -> reduced pk[axis][k] (in d_red, which holds >= 3 n doubles)
-  launch_segsum(p->power_part, p->pow_blocks, 3 * n, p->d_pk, p->stream);
-  launch_structure_final(p->d_pk, n, (double)p->ntot, p->d_result, p->stream);
+  // power sums of |psi|^2 - 1 along each axis, nothing stored but one row of n per tile
+  for (int a = 0; a < 3; ++a)
+    if ((st = power_sums(p, a, V_POWER, psi, work, nullptr)) != GP_OK) return st;
+  launch_structure_final(p->d_pk, n, (double)p->ntot, p->h_result, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  HIPCHK(p, hipMemcpyAsync(p->h_result, p->d_result, (n / 2) * sizeof(double), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));
   memcpy(out, p->h_result, (n / 2) * sizeof(double));
   return GP_OK;
@@ -1272,25 +1285,20 @@ gp_status gp_structure_fn_velocity(gp_plan_t* p, const void* psi, void* work, in
   const int n = p->d.n[0];
   if (p->d.n[1] != n || p->d.n[2] != n) return fail(GP_ERR_UNSUPPORTED, "structure function needs a cubic grid");
   if (n < 2) return fail(GP_ERR_UNSUPPORTED, "structure function needs n >= 2");
-  if ((st = derivatives(p, psi, work, false)) != GP_OK) return st;
-  void* f[3] = {field(p, work, 0), field(p, work, 1), field(p, work, 2)};
-  launch_velocity_fields(p->prec, psi, f[0], f[1], f[2], p->ntot, p->d.alpha, p->field_part, p->field_blocks, p->stream);
-  if ((st = check_launch(p)) != GP_OK) return st;
-  const long div[3] = {1, n, (long)n * n};
+  // per axis one pass: v_a from the derivative along a, its transform along a, power sums
+  // and sum v_a^2
+  SegLens lens{};
+  double* sq = p->kin_part;
   for (int a = 0; a < 3; ++a) {
-    // F_a(v_a), natural order along axis a
-    if ((st = pass(p, a, V_FWD, f[a], f[a], nullptr, 0.0, nullptr, 1.0)) != GP_OK) return st;
-    launch_axis_power(p->prec, f[a], p->ntot, div[a], n, p->pow_blocks, p->pow_chunk,
-                      p->power_part + (size_t)a * p->pow_blocks * n, p->stream);
-    if ((st = check_launch(p)) != GP_OK) return st;
+    if ((st = power_sums(p, a, V_VPOWER, psi, work, sq)) != GP_OK) return st;
+    lens.first[a] = sq - p->kin_part;
+    lens.len[a] = p->ax[a].blocks;
+    sq += p->ax[a].blocks;
   }
   const int half = n / 2;
-  launch_segsum(p->power_part, p->pow_blocks, 3 * n, p->d_pk, p->stream);
-  launch_structure_axes(p->d_pk, n, (double)p->ntot, p->d_result, p->stream);
-  launch_segsum(p->field_part, p->field_blocks, 3, p->d_result + 3 * half, p->stream);
+  launch_structure_axes(p->d_pk, n, (double)p->ntot, p->h_result, p->stream);
+  launch_segsums(p->kin_part, lens, 1, p->h_result + 3 * half, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  HIPCHK(p, hipMemcpyAsync(p->h_result, p->d_result, (3 * half + 3) * sizeof(double), hipMemcpyDeviceToHost,
-                           p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));
   memcpy(out, p->h_result, 3 * half * sizeof(double));
   if (mean_v2)
@@ -1385,7 +1393,9 @@ gp_status gp_helicity(gp_plan_t* p, const void* psi, void* work, double* out, do
     launch_hel_spectral(p->prec, S[0], S[1], S[3], S[4], S[6], S[7], p->d.n[0], p->d.n[1], p->d.n[2], p->nshell,
                         p->spec_blocks, p->spec_chunk, p->bins_part, p->stream);
     if ((st = check_launch(p)) != GP_OK) return st;
-    launch_segsum(p->bins_part, p->spec_blocks, 2 * p->nshell, p->d_result + 2, p->stream);
+    const unsigned chunks = colsum_chunks(p->spec_blocks);
+    launch_colsum(p->bins_part, p->spec_blocks, 2 * p->nshell, chunks, p->d_red, p->stream);
+    launch_colsum(p->d_red, chunks, 2 * p->nshell, 1, p->d_result + 2, p->stream);
     if ((st = check_launch(p)) != GP_OK) return st;
   }
   const size_t cnt = 2 + (spec ? 2 * (size_t)p->nshell : 0);
