@@ -75,9 +75,16 @@ enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
 // of a spectral derivative, i k_j / N_j, and sum k_j^2 |F_j v|^2 is accumulated for the
 // kinetic energy;
 // PRO_ARGLE: none, but turn the derivative after the inverse transform into the
-// explicit part of the imaginary-time step; PRO_MULT3: none, but multiply the
+// explicit part of the imaginary-time step and that into its transform, stored in lane
+// order; PRO_MULT3: none, but multiply the
 // forward transform by the separable 3-D propagator m_x(k_x) m_y(k_y) m_z(k_z) before
 // it is stored -- the last forward pass of the literal 3-D form)
+// Lane order: the coefficients along an axis as the lanes hold them after the forward stages,
+// the entry of table index li at li.  Between passes that agree on the schedule it needs no
+// reordering exchange, and it is as coalesced as the natural order.  PRO_LANE (FWD, INV): such
+// output, such input.  PRO_SOLVE (FWD): the diagonal solve of the imaginary-time step and the
+// inverse transform after the forward one.  PRO_LANE_D (INV): PRO_LANE, and the derivative
+// along the axis from the same coefficients.
 // In a TURN pass: the work between its two sub-steps (PRO_NL, PRO_ADJ_NL, or PRO_TAPE:
 // store the state there as well, then rotate it).  PRO_SWAP: none; the pass exchanges the
 // two outer axes of the layout (see pencil_pair).  PRO_ENERGY (FWD): sums only, nothing is
@@ -86,7 +93,8 @@ enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
 // frequency, f = |v|^2 - 1 or the velocity 2 alpha Im(conj(v) d_j v)/|v|^2 along the axis,
 // whose derivative is taken in the same pass; PRO_VPOWER also sums f^2 (point_partial).
 enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DERIV = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
-                PRO_TAPE = 7, PRO_SWAP = 8, PRO_ENERGY = 9, PRO_POWER = 10, PRO_VPOWER = 11 };
+                PRO_TAPE = 7, PRO_SWAP = 8, PRO_ENERGY = 9, PRO_POWER = 10, PRO_VPOWER = 11,
+                PRO_LANE = 12, PRO_SOLVE = 13, PRO_LANE_D = 14 };
 
 // per-run pointers of a grouped (ensemble) launch: run = blockIdx.y
 struct RunPtrs {
@@ -108,9 +116,11 @@ struct PassArgs {
                            // PRO_MULT3: m_x in natural frequency order (FP64 complex)
   const void* aux2;        // PRO_ARGLE: d phi / dx and d phi / dy at the same points;
   const void* aux3;        // PRO_MULT3: m_y and m_z
-  void* tape;              // PRO_TAPE: where the state between the sub-steps is stored
+                           // PRO_SOLVE: k_x^2 and k_z^2 in lane order (aux, aux2)
+  void* tape;              // PRO_TAPE: where the state between the sub-steps is stored;
+                           // PRO_SOLVE: the transform of phi, in and out; PRO_LANE_D: d_j v
   const void* vel;         // PRO_ARGLE: velocity planes v_x, v_y, v_z (Real, one field each)
-  double q4a;              // PRO_ARGLE: 1 / (4 alpha)
+  double q4a;              // PRO_ARGLE: 1 / (4 alpha); PRO_SOLVE: dtau alpha / 2 (nl_coef: dtau)
   const double* ksq;       // k_j^2 in position order (kinetic accumulation)
   double* kin_partial;     // per-workgroup partial sum of k_j^2 |F_j v|^2 (or null)
   double* point_partial;   // PRO_ENERGY: per-workgroup sums of |v|^2, then of (|v|^2 - 1)^2, or null
@@ -540,6 +550,30 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     for (int e = 0; e < E; ++e) v[e] = *(const GPK_GLOBAL C*)(inb + e * estep + w.loff);
   };
 
+  // the same addresses in lane order: register j + B r holds entry t + T j + r N/R_last
+  auto lane_off = [&](int r, int j) { return (long)(T * j + r * (S::N / S::RL)) * es * (long)sizeof(C); };
+  auto load_lane = [&](C* v, const void* from, const Where& w) {
+    constexpr int L = S::NS - 1, B = E / S::rad(L);
+    const auto inb = gptr<char>(from) + w.bbase * (long)sizeof(C);
+#pragma unroll
+    for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+      for (int j = 0; j < B; ++j) v[j + B * r] = *(const GPK_GLOBAL C*)(inb + lane_off(r, j) + w.loff);
+  };
+  auto store_lane = [&](const C* v, void* to, const Where& w) {
+    constexpr int L = S::NS - 1, B = E / S::rad(L);
+    const auto outb = gptr_mut<char>(to) + w.bbase * (long)sizeof(C);
+#pragma unroll
+    for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+      for (int j = 0; j < B; ++j) *(GPK_GLOBAL C*)(outb + lane_off(r, j) + w.loff) = v[j + B * r];
+  };
+  auto store = [&](const C* v, void* to, const Where& w) {
+    const auto outb = gptr_mut<char>(to) + w.bbase * (long)sizeof(C);
+#pragma unroll
+    for (int e = 0; e < E; ++e) *(GPK_GLOBAL C*)(outb + e * estep + w.loff) = v[e];
+  };
+
   // x pencils of complex64 propagator passes: whole tiles of contiguous pencils,
   // moved with 16-byte accesses (a pencil past the last one takes the last one, as
   // the lanes do, so the duplicate stores write equal bytes)
@@ -669,6 +703,10 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
             const double c = a.nl_coef - (ux * ux + uy * uy + uz * uz) * a.q4a - a.nl_coef * (pr * pr + pi * pi);
             v[e] = mk(Real(gi + c * pr), Real(-gr + c * pi));
           }
+          const auto tw2 = gptr<Tab<Real>>(reload(a.tw));
+          forward_all<Real, S, KIND, 0>(v, lds, t, col, tw2);
+          store_lane(v, a.out, cur);
+          return;
         }
       } else {  // FWD: reorder to natural frequency order
         if constexpr (S::NS > 1) exchange<Real, S, KIND, L, -1>(lds, v, t, col);
@@ -701,9 +739,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
 #pragma unroll
       for (int e = 0; e < E; ++e) dst[T * e] = v[e];
     } else {
-      const auto outb = gptr_mut<char>(a.out) + cur.bbase * (long)sizeof(C);
-#pragma unroll
-      for (int e = 0; e < E; ++e) *(GPK_GLOBAL C*)(outb + e * estep + cur.loff) = v[e];
+      store(v, a.out, cur);
     }
   };
 
@@ -722,6 +758,65 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
 
   C v[E];
   const Where w = where(tile);
+  if constexpr (PRO == PRO_LANE && MODE == FWD) {
+    load(v, w);
+    forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
+    store_lane(v, a.out, w);
+    return;
+  }
+  if constexpr (PRO == PRO_LANE && MODE == INV) {
+    load_lane(v, a.in, w);
+    inverse_all<Real, S, KIND, S::NS - 1>(v, lds, t, col, tw);
+    store(v, a.out, w);
+    return;
+  }
+  if constexpr (PRO == PRO_LANE_D) {
+    constexpr int L = S::NS - 1, B = E / S::rad(L);
+    load_lane(v, a.in, w);
+    inverse_all<Real, S, KIND, L>(v, lds, t, col, tw);
+    store(v, a.out, w);
+    // the coefficients again (from the cache), times i k: the derivative table holds k/N
+    load_lane(v, reload(a.in), w);
+#pragma unroll
+    for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const double k = (double)S::N * gptr<double>(a.mult)[(unsigned)(2 * (r * (S::N / S::rad(L)) + t + T * j) + 1)];
+        const C x = v[j + B * r];
+        v[j + B * r] = mk(Real(-k * (double)x.y), Real(k * (double)x.x));
+      }
+    const auto tw2 = gptr<Tab<Real>>(reload(a.tw));
+    inverse_all<Real, S, KIND, L>(v, lds, t, col, tw2);
+    store(v, a.tape, w);
+    return;
+  }
+  if constexpr (PRO == PRO_SOLVE) {
+    // P <- ((1 - h k^2) P + dtau Q)/(1 + h k^2), h = dtau alpha / 2, Q the transform of the
+    // explicit part, all in lane order (a y pass: pencil (z, x)); then P/N^3 back along y
+    constexpr int L = S::NS - 1, B = E / S::rad(L);
+    load(v, w);
+    forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
+    const unsigned nx = (unsigned)a.inner, p = (unsigned)(w.pstart / a.outer) * nx + (unsigned)(w.pstart % a.outer);
+    const double kxz = gptr<double>(a.aux)[p % nx] + gptr<double>(a.aux2)[p / nx];
+    const auto pb = gptr_mut<char>(a.tape) + w.bbase * (long)sizeof(C);
+#pragma unroll
+    for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+      for (int j = 0; j < B; ++j) {
+        const double hk = a.q4a * (kxz + gptr<double>(a.ksq)[(unsigned)(r * (S::N / S::rad(L)) + t + T * j)]);
+        const double num = 1.0 - hk, den = 1.0 / (1.0 + hk);
+        const auto at = (GPK_GLOBAL C*)(pb + lane_off(r, j) + w.loff);
+        const C f = *at, q = v[j + B * r];
+        const double re = (num * (double)f.x + a.nl_coef * (double)q.x) * den;
+        const double im = (num * (double)f.y + a.nl_coef * (double)q.y) * den;
+        *at = mk(Real(re), Real(im));
+        v[j + B * r] = mk(Real(re * a.scale), Real(im * a.scale));
+      }
+    const auto tw2 = gptr<Tab<Real>>(reload(a.tw));
+    inverse_all<Real, S, KIND, L>(v, lds, t, col, tw2);
+    store(v, a.out, w);
+    return;
+  }
   if constexpr (POWER) {
     constexpr int L = S::NS - 1, B = E / S::rad(L), RL = S::RL;
     load(v, w);
@@ -829,6 +924,7 @@ void launch_pass(const PassArgs& a, unsigned grid, unsigned runs, hipStream_t st
 
 // kernel variants compiled for every schedule
 enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_DERIV, V_FWD, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
-               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_ENERGY, V_POWER, V_VPOWER, V_COUNT };
+               V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_ENERGY, V_POWER, V_VPOWER,
+               V_FWD_LANE, V_INV_LANE, V_INV_LANE_D, V_SOLVE, V_COUNT };
 
 }  // namespace gpk

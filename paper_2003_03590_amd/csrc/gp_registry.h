@@ -59,7 +59,13 @@ void fill(PassEntry& e) {
   e.fn[KIND][V_DERIV] = &launch_pass<Real, S, KIND, PROP, PRO_DERIV>;
   e.fn[KIND][V_FWD] = &launch_pass<Real, S, KIND, FWD, PRO_NONE>;
   e.fn[KIND][V_INV] = &launch_pass<Real, S, KIND, INV, PRO_NONE>;
-  e.fn[KIND][V_PROP_ARGLE] = &launch_pass<Real, S, KIND, PROP, PRO_ARGLE>;
+  // the imaginary-time step on grids with three real axes: z forms the explicit part, y solves,
+  // x ends it
+  e.fn[KIND][V_FWD_LANE] = &launch_pass<Real, S, KIND, FWD, PRO_LANE>;
+  e.fn[KIND][V_INV_LANE] = &launch_pass<Real, S, KIND, INV, PRO_LANE>;
+  if constexpr (KIND == STRIDED) e.fn[KIND][V_PROP_ARGLE] = &launch_pass<Real, S, KIND, PROP, PRO_ARGLE>;
+  if constexpr (KIND == STRIDED) e.fn[KIND][V_SOLVE] = &launch_pass<Real, S, KIND, FWD, PRO_SOLVE>;
+  if constexpr (KIND == CONTIG) e.fn[KIND][V_INV_LANE_D] = &launch_pass<Real, S, KIND, INV, PRO_LANE_D>;
   e.fn[KIND][V_FWD_MULT3] = &launch_pass<Real, S, KIND, FWD, PRO_MULT3>;
   e.fn[KIND][V_ENERGY] = &launch_pass<Real, S, KIND, FWD, PRO_ENERGY>;
   e.fn[KIND][V_POWER] = &launch_pass<Real, S, KIND, FWD, PRO_POWER>;

@@ -1408,62 +1408,87 @@ gp_status gp_helicity(gp_plan_t* p, const void* psi, void* work, double* out, do
   return GP_OK;
 }
 
-// the z-derivative pass with the explicit part of the imaginary-time step fused after
-// its inverse transform: out = n(phi, d/dx phi, d/dy phi, d/dz phi, v)
-static gp_status argle_z_pass(gp_plan_s* p, const void* phi, const void* d0, const void* d1, const void* v,
-                              void* out) {
-  Axis& A = p->ax[2];
-  PassArgs g{};
-  g.in = phi; g.out = out; g.mult = A.deriv; g.tw = A.tw; g.aux = phi; g.aux2 = d0; g.aux3 = d1; g.vel = v;
-  g.ksq = A.ksq; g.nl_coef = p->d.beta; g.q4a = 1.0 / (4.0 * p->d.alpha); g.scale = 1.0;
-  g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
-  A.e->fn[A.kind][V_PROP_ARGLE](g, A.blocks, 1, p->stream);
-  return check_launch(p);
-}
+// what the workspace holds for the current phi: slot 0 and 1 its x and y derivatives, slot 3
+// its transform in lane order
+struct ArgleHave { bool d0 = false, d1 = false, transform = false; };
 
-// nsteps steps of the semi-implicit backward Euler scheme; work slots 0..2.  With a
-// z axis the explicit part n comes out of the z-derivative pass (d/dz never reaches
-// memory); otherwise a pointwise kernel forms it and overwrites d/dz in place.
-static gp_status argle_steps(gp_plan_s* p, void* phi, const void* v, double dtau, int64_t nsteps, void* work) {
+// nsteps steps of the semi-implicit backward Euler scheme; work slots 0..3.
+// With three real axes a step is seven passes and 18.5 states of traffic: the y derivative;
+// the z pass that takes d/dz, forms the explicit part n and transforms it along z; n along x;
+// the y pass that ends the transform, solves in Fourier space and goes back along y; back along
+// z; back along x, with the x derivative of the new phi from the same coefficients.  The
+// transform of phi is what the last step's solve left, so it is taken once a call.
+// Otherwise derivatives, a pointwise kernel and 3-D transforms.
+static gp_status argle_steps(gp_plan_s* p, void* phi, const void* v, double dtau, int64_t nsteps, void* work,
+                             ArgleHave& have, bool keep_d0 = false) {
   gp_status st;
   void* d0 = field(p, work, 0);
   void* d1 = field(p, work, 1);
-  void* d2 = field(p, work, 2);
-  void* q = d2;
-  const bool fused = p->ax[2].n > 1;
+  void* q = field(p, work, 2);
   const double a = 0.5 * dtau * p->d.alpha, inv_n = 1.0 / (double)p->ntot;
-  for (int64_t s = 0; s < nsteps; ++s) {
-    if (fused) {
-      for (int ax = 0; ax < 2; ++ax) {
-        void* out = field(p, work, ax);
-        if (p->ax[ax].n == 1) HIPCHK(p, hipMemsetAsync(out, 0, p->ntot * p->S, p->stream));
-        else if ((st = pass(p, ax, V_PROP, phi, out, p->ax[ax].deriv)) != GP_OK) return st;
-      }
-      if ((st = argle_z_pass(p, phi, d0, d1, v, q)) != GP_OK) return st;
-    } else {
+  if (nsteps <= 0) return GP_OK;
+  if (p->ax[0].n == 1 || p->ax[1].n == 1 || p->ax[2].n == 1) {
+    have = ArgleHave{};
+    for (int64_t s = 0; s < nsteps; ++s) {
       if ((st = derivatives(p, phi, work, false)) != GP_OK) return st;
-      launch_argle_explicit(p->prec, phi, d0, d1, d2, v, q, p->ntot, p->d.alpha, p->d.beta, p->stream);
+      launch_argle_explicit(p->prec, phi, d0, d1, q, v, q, p->ntot, p->d.alpha, p->d.beta, p->stream);
       if ((st = check_launch(p)) != GP_OK) return st;
+      if ((st = fwd3_unnorm(p, phi)) != GP_OK) return st;
+      if ((st = fwd3_unnorm(p, q)) != GP_OK) return st;
+      launch_argle_solve(p->prec, phi, q, p->d.n[0], p->d.n[1], p->d.n[2], a, dtau, inv_n, p->stream);
+      if ((st = check_launch(p)) != GP_OK) return st;
+      if ((st = inv3_unnorm(p, phi)) != GP_OK) return st;
     }
-    if ((st = fwd3_unnorm(p, phi)) != GP_OK) return st;
-    if ((st = fwd3_unnorm(p, q)) != GP_OK) return st;
-    launch_argle_solve(p->prec, phi, q, p->d.n[0], p->d.n[1], p->d.n[2], a, dtau, inv_n, p->stream);
-    if ((st = check_launch(p)) != GP_OK) return st;
-    if ((st = inv3_unnorm(p, phi)) != GP_OK) return st;
+    return GP_OK;
+  }
+  void* P = field(p, work, 3);
+  // a pass of axis `ax` with the arguments every variant shares
+  auto run = [&](int ax, int var, const void* in, void* out, const std::function<void(PassArgs&)>& more) {
+    const Axis& A = p->ax[ax];
+    PassArgs g{};
+    g.in = in; g.out = out; g.tw = A.tw; g.mult = A.deriv; g.ksq = A.ksq; g.scale = 1.0;
+    g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
+    if (more) more(g);
+    A.e->fn[A.kind][var](g, A.blocks, 1, p->stream);
+    return check_launch(p);
+  };
+  if (!have.transform)
+    for (int ax = 0; ax < 3; ++ax)
+      if ((st = run(ax, V_FWD_LANE, ax == 0 ? phi : P, P, nullptr)) != GP_OK) return st;
+  have.transform = true;
+  for (int64_t s = 0; s < nsteps; ++s) {
+    if (!have.d0 && (st = run(0, V_PROP, phi, d0, nullptr)) != GP_OK) return st;
+    if (!have.d1 && (st = run(1, V_PROP, phi, d1, nullptr)) != GP_OK) return st;
+    have.d0 = have.d1 = false;
+    if ((st = run(2, V_PROP_ARGLE, phi, q, [&](PassArgs& g) {
+           g.aux = phi; g.aux2 = d0; g.aux3 = d1; g.vel = v; g.nl_coef = p->d.beta; g.q4a = 1.0 / (4.0 * p->d.alpha);
+         })) != GP_OK)
+      return st;
+    if ((st = run(0, V_FWD_LANE, q, q, nullptr)) != GP_OK) return st;
+    if ((st = run(1, V_SOLVE, q, q, [&](PassArgs& g) {
+           g.tape = P; g.aux = p->ax[0].ksq; g.aux2 = p->ax[2].ksq; g.q4a = a; g.nl_coef = dtau; g.scale = inv_n;
+         })) != GP_OK)
+      return st;
+    if ((st = run(2, V_INV_LANE, q, q, nullptr)) != GP_OK) return st;
+    have.d0 = keep_d0 || s + 1 < nsteps;
+    if ((st = run(0, have.d0 ? V_INV_LANE_D : V_INV_LANE, q, phi, [&](PassArgs& g) { g.tape = d0; })) != GP_OK) return st;
   }
   return GP_OK;
 }
 
-// E_v (synchronizes); work slots 0..2
-static gp_status argle_energy(gp_plan_s* p, const void* phi, const void* v, void* work, double* energy_v) {
+// E_v (synchronizes); work slots 0..2, of which `have` says what is there already
+static gp_status argle_energy(gp_plan_s* p, const void* phi, const void* v, void* work, double* energy_v,
+                              ArgleHave& have) {
   gp_status st;
-  if ((st = derivatives(p, phi, work, false)) != GP_OK) return st;
+  const bool there[3] = {have.d0, have.d1, false};
+  for (int a = 0; a < 3; ++a)
+    if (!there[a] && (st = deriv_pass(p, a, phi, field(p, work, a))) != GP_OK) return st;
+  have.d0 = have.d1 = true;
   launch_argle_energy(p->prec, phi, field(p, work, 0), field(p, work, 1), field(p, work, 2), v, p->ntot, p->d.alpha,
                       p->d.beta, p->loss_part, p->field_blocks, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  launch_segsum(p->loss_part, p->field_blocks, 1, p->d_result, p->stream);
+  launch_segsum(p->loss_part, p->field_blocks, 1, p->h_result, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  HIPCHK(p, hipMemcpyAsync(p->h_result, p->d_result, sizeof(double), hipMemcpyDeviceToHost, p->stream));
   HIPCHK(p, hipStreamSynchronize(p->stream));
   *energy_v = 2.0 * p->d.alpha * p->h_result[0] / (double)p->ntot;
   if (!std::isfinite(*energy_v)) return fail(GP_ERR_NONFINITE, "E_v is not finite");
@@ -1483,14 +1508,16 @@ gp_status gp_argle_step(gp_plan_t* p, void* phi, const void* v, double dtau, int
   if (st != GP_OK) return st;
   if (!std::isfinite(dtau) || dtau <= 0.0) return fail(GP_ERR_ARG, "dtau must be finite and positive");
   if (nsteps < 0) return fail(GP_ERR_ARG, "nsteps must be >= 0");
-  return argle_steps(p, phi, v, dtau, nsteps, work);
+  ArgleHave have;
+  return argle_steps(p, phi, v, dtau, nsteps, work, have);
 }
 
 gp_status gp_argle_energy(gp_plan_t* p, const void* phi, const void* v, void* work, double* energy_v) {
   gp_status st = argle_args(p, phi, v, work);
   if (st != GP_OK) return st;
   if (!energy_v) return fail(GP_ERR_ARG, "null argument");
-  return argle_energy(p, phi, v, work, energy_v);
+  ArgleHave have;
+  return argle_energy(p, phi, v, work, energy_v, have);
 }
 
 gp_status gp_argle_run(gp_plan_t* p, void* phi, const void* v, double dtau, int64_t max_steps, int64_t check_every,
@@ -1506,19 +1533,19 @@ gp_status gp_argle_run(gp_plan_t* p, void* phi, const void* v, double dtau, int6
   void* old = field(p, work, 4);
   const size_t bytes = (size_t)p->ntot * p->S;
   bool have_e = false;
+  ArgleHave have;
   while (r.steps < max_steps) {
     const int64_t next = std::min<int64_t>((r.steps / check_every + 1) * check_every, max_steps);   // check step
-    if ((st = argle_steps(p, phi, v, dtau, next - r.steps - 1, work)) != GP_OK) return st;
+    if ((st = argle_steps(p, phi, v, dtau, next - r.steps - 1, work, have, true)) != GP_OK) return st;
     double e_old, e_new, sup2;
-    if ((st = argle_energy(p, phi, v, work, &e_old)) != GP_OK) return st;
+    if ((st = argle_energy(p, phi, v, work, &e_old, have)) != GP_OK) return st;
     HIPCHK(p, hipMemcpyAsync(old, phi, bytes, hipMemcpyDeviceToDevice, p->stream));
-    if ((st = argle_steps(p, phi, v, dtau, 1, work)) != GP_OK) return st;
-    launch_sup_diff2(p->prec, phi, old, p->ntot, p->field_part, p->field_blocks, p->d_result, p->stream);
+    if ((st = argle_steps(p, phi, v, dtau, 1, work, have, true)) != GP_OK) return st;
+    launch_sup_diff2(p->prec, phi, old, p->ntot, p->field_part, p->field_blocks, p->h_result, p->stream);
     if ((st = check_launch(p)) != GP_OK) return st;
-    HIPCHK(p, hipMemcpyAsync(p->h_result, p->d_result, sizeof(double), hipMemcpyDeviceToHost, p->stream));
     HIPCHK(p, hipStreamSynchronize(p->stream));
     sup2 = p->h_result[0];
-    if ((st = argle_energy(p, phi, v, work, &e_new)) != GP_OK) return st;
+    if ((st = argle_energy(p, phi, v, work, &e_new, have)) != GP_OK) return st;
     r.steps = next;
     r.crit_sup = std::sqrt(sup2) / dtau;
     r.crit_energy = std::fabs(e_new - e_old) / (dtau * e_old);
@@ -1527,7 +1554,7 @@ gp_status gp_argle_run(gp_plan_t* p, void* phi, const void* v, double dtau, int6
     if (!std::isfinite(r.crit_sup)) return fail(GP_ERR_NONFINITE, "ARGLE update is not finite at step %lld", (long long)next);
     if (r.crit_sup <= eps) { r.converged = 1; break; }
   }
-  if (!have_e && (st = argle_energy(p, phi, v, work, &r.e_v)) != GP_OK) return st;
+  if (!have_e && (st = argle_energy(p, phi, v, work, &r.e_v, have)) != GP_OK) return st;
   *report = r;
   return GP_OK;
 }
