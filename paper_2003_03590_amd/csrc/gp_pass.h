@@ -79,6 +79,7 @@ enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
 // order; PRO_MULT3: none, but multiply the
 // forward transform by the separable 3-D propagator m_x(k_x) m_y(k_y) m_z(k_z) before
 // it is stored -- the last forward pass of the literal 3-D form)
+// PRO_HESS (FWD): J = Im sum_j conj(F_j) d F_j along the axis, F_j the three fields in, aux, aux2.
 // Lane order: the coefficients along an axis as the lanes hold them after the forward stages,
 // the entry of table index li at li.  Between passes that agree on the schedule it needs no
 // reordering exchange, and it is as coalesced as the natural order.  PRO_LANE (FWD, INV): such
@@ -94,7 +95,7 @@ enum PassMode { PROP = 0, FWD = 1, INV = 2, TURN = 3 };
 // whose derivative is taken in the same pass; PRO_VPOWER also sums f^2 (point_partial).
 enum Prologue { PRO_NONE = 0, PRO_NL = 1, PRO_ADJ_NL = 2, PRO_DERIV = 4, PRO_ARGLE = 5, PRO_MULT3 = 6,
                 PRO_TAPE = 7, PRO_SWAP = 8, PRO_ENERGY = 9, PRO_POWER = 10, PRO_VPOWER = 11,
-                PRO_LANE = 12, PRO_SOLVE = 13, PRO_LANE_D = 14 };
+                PRO_LANE = 12, PRO_SOLVE = 13, PRO_LANE_D = 14, PRO_HESS = 15 };
 
 // per-run pointers of a grouped (ensemble) launch: run = blockIdx.y
 struct RunPtrs {
@@ -544,8 +545,8 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     w.loff = (unsigned)(((long)(q / inner) * a.outer + (long)(q % inner) - w.bbase + (long)t * es) * (long)sizeof(C));
     return w;
   };
-  auto load = [&](C* v, const Where& w) {
-    const auto inb = gptr<char>(a.in) + w.bbase * (long)sizeof(C);
+  auto load = [&](C* v, const Where& w, const void* from) {
+    const auto inb = gptr<char>(from) + w.bbase * (long)sizeof(C);
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = *(const GPK_GLOBAL C*)(inb + e * estep + w.loff);
   };
@@ -758,8 +759,45 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
 
   C v[E];
   const Where w = where(tile);
+  if constexpr (PRO == PRO_HESS) {
+    // Bound by registers and exchanges: three derivatives of the points a lane holds, their
+    // products with the undifferentiated points summed here.  128^3 complex128: 6 derivative
+    // passes and 6 passes that summed their products through memory took 268 us, these three
+    // take 92 us (256 VGPRs at 16 points a lane, no scratch memory).
+    constexpr int L = S::NS - 1, B = E / S::rad(L);
+    Real J[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) J[e] = Real(0);
+#pragma unroll 1
+    for (int j = 0; j < 3; ++j) {
+      const void* f = j == 0 ? a.in : j == 1 ? a.aux : a.aux2;
+      load(v, w, f);
+      const auto tw1 = gptr<Tab<Real>>(reload(a.tw));
+      const void* table = reload(a.mult);
+      forward_all<Real, S, KIND, 0>(v, lds, t, col, tw1);
+#pragma unroll
+      for (int r = 0; r < S::rad(L); ++r)
+#pragma unroll
+        for (int i = 0; i < B; ++i) {
+          const double k = gptr<double>(table)[(unsigned)(2 * (r * (S::N / S::rad(L)) + t + T * i) + 1)];
+          const C x = v[i + B * r];
+          v[i + B * r] = mk(Real(-(double)x.y * k), Real((double)x.x * k));
+        }
+      inverse_all<Real, S, KIND, L>(v, lds, t, col, tw1);
+      const auto inb = gptr<char>(f) + w.bbase * (long)sizeof(C);
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const C x = *(const GPK_GLOBAL C*)(inb + e * estep + w.loff);    // again, from the cache
+        J[e] = Real((double)J[e] + ((double)x.x * (double)v[e].y - (double)x.y * (double)v[e].x));
+      }
+    }
+    const auto outb = gptr_mut<char>(a.out) + w.bbase * (long)sizeof(Real);
+#pragma unroll
+    for (int e = 0; e < E; ++e) *(GPK_GLOBAL Real*)(outb + (e * estep + (long)w.loff) / 2) = J[e];
+    return;
+  }
   if constexpr (PRO == PRO_LANE && MODE == FWD) {
-    load(v, w);
+    load(v, w, a.in);
     forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
     store_lane(v, a.out, w);
     return;
@@ -794,7 +832,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     // P <- ((1 - h k^2) P + dtau Q)/(1 + h k^2), h = dtau alpha / 2, Q the transform of the
     // explicit part, all in lane order (a y pass: pencil (z, x)); then P/N^3 back along y
     constexpr int L = S::NS - 1, B = E / S::rad(L);
-    load(v, w);
+    load(v, w, a.in);
     forward_all<Real, S, KIND, 0>(v, lds, t, col, tw);
     const unsigned nx = (unsigned)a.inner, p = (unsigned)(w.pstart / a.outer) * nx + (unsigned)(w.pstart % a.outer);
     const double kxz = gptr<double>(a.aux)[p % nx] + gptr<double>(a.aux2)[p / nx];
@@ -819,7 +857,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
   }
   if constexpr (POWER) {
     constexpr int L = S::NS - 1, B = E / S::rad(L), RL = S::RL;
-    load(v, w);
+    load(v, w, a.in);
     if constexpr (PRO == PRO_POWER) {
 #pragma unroll
       for (int e = 0; e < E; ++e) v[e] = mk(cabs2(v[e]) - Real(1), Real(0));
@@ -870,7 +908,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     return;
   }
   if constexpr (PRO == PRO_ENERGY) {
-    load(v, w);
+    load(v, w, a.in);
     Neu rho_acc, int_acc;
     if (a.point_partial && w.active) {
 #pragma unroll
@@ -905,7 +943,7 @@ __global__ __launch_bounds__(S::THREADS) void axis_pass(PassArgs a) {
     const auto src = gptr<C>(a.in) + tile_pencil(col) + t;
 #pragma unroll
     for (int e = 0; e < E; ++e) v[e] = src[T * e];
-  } else load(v, w);
+  } else load(v, w, a.in);
   process(v, w);
 
   if constexpr (PRO == PRO_DERIV) {
@@ -925,6 +963,6 @@ void launch_pass(const PassArgs& a, unsigned grid, unsigned runs, hipStream_t st
 // kernel variants compiled for every schedule
 enum Variant { V_PROP = 0, V_PROP_NL, V_PROP_ADJ, V_DERIV, V_FWD, V_INV, V_PROP_ARGLE, V_FWD_MULT3,
                V_TURN, V_TURN_TAPE, V_TURN_ADJ, V_PROP_SWAP, V_ENERGY, V_POWER, V_VPOWER,
-               V_FWD_LANE, V_INV_LANE, V_INV_LANE_D, V_SOLVE, V_COUNT };
+               V_FWD_LANE, V_INV_LANE, V_INV_LANE_D, V_SOLVE, V_HESS, V_COUNT };
 
 }  // namespace gpk

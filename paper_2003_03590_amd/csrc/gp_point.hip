@@ -708,40 +708,20 @@ __global__ __launch_bounds__(256) void k_hel_omega(const void* t3, const void* t
   stc<Real>(s7, i, oz, 0.0);
 }
 
-// J_i = Im(sum_j (d_i d_j psi)(d_j psi)*), accumulated from one Hessian entry H_ij:
-// J[t1] += Im(conj(F1) H), and when t2 >= 0, J[t2] += Im(conj(F2) H).  J is packed as
-// J0 = J_x + i J_y, J1 = J_z; `first` starts the sums from zero.
-template <class Real>
-__global__ __launch_bounds__(256) void k_hel_acc(const void* H, const void* F1, int t1, const void* F2, int t2,
-                                                 int first, void* J0, void* J1, unsigned n) {
-  const unsigned i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= n) return;
-  double j[3] = {0.0, 0.0, 0.0};
-  if (!first) {
-    const cplx<Real> a = ldc<Real>(J0, i), b = ldc<Real>(J1, i);
-    j[0] = a.x; j[1] = a.y; j[2] = b.x;
-  }
-  const cplx<Real> h = ldc<Real>(H, i), f = ldc<Real>(F1, i);
-  j[t1] += (double)f.x * (double)h.y - (double)f.y * (double)h.x;
-  if (t2 >= 0) {
-    const cplx<Real> g = ldc<Real>(F2, i);
-    j[t2] += (double)g.x * (double)h.y - (double)g.y * (double)h.x;
-  }
-  stc<Real>(J0, i, j[0], j[1]);
-  stc<Real>(J1, i, j[2], 0.0);
-}
-
 // v_reg = v_par W/|W|, W = 4 alpha grad(Re psi) x grad(Im psi),
 // v_par = 2 alpha W.J/(|W| |grad psi|^2); v_reg = 0 where |W| = 0 or where
 // |grad psi|^2 <= g2_floor = 1e-12 <|grad psi|^2> (critical points of psi, where the
 // denominator vanishes; g2_sum[0] / n is the mean).
-// Out: S3 = vreg_x + i vreg_y, S4 = vreg_z (S4 held J_x + i J_y: read first);
-// partial[0][block] = sum v.omega, partial[1][block] = sum v_reg.omega.
+// J_i = Im(sum_j (d_i d_j psi)(d_j psi)*), three real fields.  Out, where the spectra are wanted:
+// s0 = v_x + i v_y, s1 = v_z, s2 = vreg_z (in the places of d0, d1, d2: read first) and
+// s3 = vreg_x + i vreg_y (v is singular at the zeros of psi and v_reg is not: no transform
+// holds both); partial[0][block] = sum v.omega, partial[1][block] = sum v_reg.omega.
 template <class Real>
 __global__ __launch_bounds__(256) void k_hel_vreg(const void* psi, const void* d0, const void* d1, const void* d2,
-                                                  const void* j01, const void* j2, const void* w01, const void* w2,
-                                                  void* s3, void* s4, unsigned n, double alpha,
-                                                  const double* __restrict__ g2_sum, double* __restrict__ partial) {
+                                                  const Real* Jx, const Real* Jy, const Real* Jz, const void* w01,
+                                                  const void* w2, void* s0, void* s1, void* s2, void* s3,
+                                                  unsigned n, double alpha, const double* __restrict__ g2_sum,
+                                                  double* __restrict__ partial) {
   __shared__ double sh[4];
   Neu hv, hr;
   const double g2_floor = 1e-12 * g2_sum[0] / (double)n;
@@ -751,9 +731,8 @@ __global__ __launch_bounds__(256) void k_hel_vreg(const void* psi, const void* d
     const double gr[3] = {g[0].x, g[1].x, g[2].x}, gi[3] = {g[0].y, g[1].y, g[2].y};
     double v[3];
     vel_at(p.x, p.y, gr, gi, alpha, v);
-    const cplx<Real> ja = ldc<Real>(j01, i), jb = ldc<Real>(j2, i);
     const cplx<Real> oa = ldc<Real>(w01, i), ob = ldc<Real>(w2, i);
-    const double J[3] = {ja.x, ja.y, jb.x}, om[3] = {oa.x, oa.y, ob.x};
+    const double J[3] = {Jx[i], Jy[i], Jz[i]}, om[3] = {oa.x, oa.y, ob.x};
     const double W[3] = {4.0 * alpha * (gr[1] * gi[2] - gr[2] * gi[1]), 4.0 * alpha * (gr[2] * gi[0] - gr[0] * gi[2]),
                          4.0 * alpha * (gr[0] * gi[1] - gr[1] * gi[0])};
     const double wn = sqrt(W[0] * W[0] + W[1] * W[1] + W[2] * W[2]);
@@ -766,8 +745,12 @@ __global__ __launch_bounds__(256) void k_hel_vreg(const void* psi, const void* d
 #pragma unroll
       for (int a = 0; a < 3; ++a) vr[a] = vpar * (W[a] / wn);
     }
-    stc<Real>(s3, i, vr[0], vr[1]);
-    stc<Real>(s4, i, vr[2], 0.0);
+    if (s0) {
+      stc<Real>(s0, i, v[0], v[1]);
+      stc<Real>(s1, i, v[2], 0.0);
+      stc<Real>(s2, i, vr[2], 0.0);
+      stc<Real>(s3, i, vr[0], vr[1]);
+    }
     hv.add(v[0] * om[0] + v[1] * om[1] + v[2] * om[2]);
     hr.add(vr[0] * om[0] + vr[1] * om[1] + vr[2] * om[2]);
   }
@@ -776,24 +759,11 @@ __global__ __launch_bounds__(256) void k_hel_vreg(const void* psi, const void* d
   if (threadIdx.x == 0) { partial[blockIdx.x] = a; partial[gridDim.x + blockIdx.x] = b; }
 }
 
-// in place: S0 = v_x + i v_y, S1 = v_z (from psi and its derivatives S0, S1, S2)
-template <class Real>
-__global__ __launch_bounds__(256) void k_hel_vpack(const void* psi, void* d0, void* d1, const void* d2, unsigned n,
-                                                   double alpha) {
-  const unsigned i = blockIdx.x * 256u + threadIdx.x;
-  if (i >= n) return;
-  const cplx<Real> p = ldc<Real>(psi, i);
-  const cplx<Real> g[3] = {ldc<Real>(d0, i), ldc<Real>(d1, i), ldc<Real>(d2, i)};
-  const double gr[3] = {g[0].x, g[1].x, g[2].x}, gi[3] = {g[0].y, g[1].y, g[2].y};
-  double v[3];
-  vel_at(p.x, p.y, gr, gi, alpha, v);
-  stc<Real>(d0, i, v[0], v[1]);
-  stc<Real>(d1, i, v[2], 0.0);
-}
-
 // Helicity spectra: from the unnormalised transforms of the packed real fields
 // V01 = v_x + i v_y, V2 = v_z, R01, R2 (v_reg), O01, O2 (omega), per k
-// Re(conj(v_k) . omega_k) and Re(conj(vreg_k) . omega_k) into shell round(|k|).
+// Re(conj(v_k) . omega_k) and Re(conj(vreg_k) . omega_k) into shell round(|k|).  The density and
+// the shell of a point and of its mirror are the same (Nyquist entries included: only k^2
+// counts), so each pair is visited once, as in k_spectral, and counts twice.
 template <class Real>
 __device__ __forceinline__ void unpack2(const void* F, long i, long m, double inv, double* ar, double* ai, double* br,
                                         double* bi) {
@@ -809,14 +779,17 @@ __global__ __launch_bounds__(64) void k_hel_spectral(const void* V01, const void
   extern __shared__ double bins[];            // [2][nshell]
   for (int i = threadIdx.x; i < 2 * nshell; i += 64) bins[i] = 0.0;
   __syncthreads();
-  const long n = (long)nx * ny * nz;
+  const long n = (long)nx * ny * nz, nh = (long)(nz / 2 + 1) * nx * ny;
   const double inv = 1.0 / (double)n;
   const long i0 = (long)blockIdx.x * chunk;
-  const long i1 = (i0 + chunk < n) ? i0 + chunk : n;
+  const long i1 = (i0 + chunk < nh) ? i0 + chunk : nh;
+  double acc[2] = {0.0, 0.0};
+  int cur = -1;
   for (long i = i0 + threadIdx.x; i < i1; i += 64) {
     int ix, iy, iz;
     grid_xyz(i, nx, ny, ix, iy, iz);
     const long m = (long)mirror_of(iz, nz) * nx * ny + (long)mirror_of(iy, ny) * nx + mirror_of(ix, nx);
+    if (m < i) continue;                      // counted with its mirror
     double v[6], r[6], o[6], t0, t1;     // [x re, x im, y re, y im, z re, z im]
     unpack2<Real>(V01, i, m, inv, &v[0], &v[1], &v[2], &v[3]);
     unpack2<Real>(V2, i, m, inv, &v[4], &v[5], &t0, &t1);
@@ -830,11 +803,18 @@ __global__ __launch_bounds__(64) void k_hel_spectral(const void* V01, const void
       hv += v[2 * a] * o[2 * a] + v[2 * a + 1] * o[2 * a + 1];
       hr += r[2 * a] * o[2 * a] + r[2 * a + 1] * o[2 * a + 1];
     }
+    if (m != i) { hv *= 2.0; hr *= 2.0; }
     const int kx = kfreq(ix, nx), ky = kfreq(iy, ny), kz = kfreq(iz, nz);
     const int s = shell_of((long)kx * kx + (long)ky * ky + (long)kz * kz);
-    atomicAdd(&bins[s], hv);
-    atomicAdd(&bins[nshell + s], hr);
+    if (s != cur) {
+      if (cur >= 0) { atomicAdd(&bins[cur], acc[0]); atomicAdd(&bins[nshell + cur], acc[1]); }
+      cur = s;
+      acc[0] = acc[1] = 0.0;
+    }
+    acc[0] += hv;
+    acc[1] += hr;
   }
+  if (cur >= 0) { atomicAdd(&bins[cur], acc[0]); atomicAdd(&bins[nshell + cur], acc[1]); }
   __syncthreads();
   for (int i = threadIdx.x; i < 2 * nshell; i += 64) bins_partial[(long)blockIdx.x * 2 * nshell + i] = bins[i];
 }
@@ -994,26 +974,24 @@ void launch_hel_omega(int prec, const void* t3, const void* t4, const void* t5, 
                       hipStream_t st) {
   GPK_PREC_LAUNCH(k_hel_omega, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, t3, t4, t5, s6, s7, (unsigned)n);
 }
-void launch_hel_acc(int prec, const void* H, const void* F1, int t1, const void* F2, int t2, int first, void* J0,
-                    void* J1, long n, hipStream_t st) {
-  GPK_PREC_LAUNCH(k_hel_acc, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, H, F1, t1, F2, t2, first, J0, J1,
-                  (unsigned)n);
-}
-void launch_hel_vreg(int prec, const void* psi, const void* d0, const void* d1, const void* d2, const void* j01,
-                     const void* j2, const void* w01, const void* w2, void* s3, void* s4, long n, double alpha,
-                     const double* g2_sum, double* partial, unsigned blocks, hipStream_t st) {
-  GPK_PREC_LAUNCH(k_hel_vreg, dim3(blocks), dim3(256), 0, st, psi, d0, d1, d2, j01, j2, w01, w2, s3, s4,
-                  (unsigned)n, alpha, g2_sum, partial);
-}
-void launch_hel_vpack(int prec, const void* psi, void* d0, void* d1, const void* d2, long n, double alpha,
-                      hipStream_t st) {
-  GPK_PREC_LAUNCH(k_hel_vpack, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, psi, d0, d1, d2, (unsigned)n,
-                  alpha);
+void launch_hel_vreg(int prec, const void* psi, const void* d0, const void* d1, const void* d2, const void* Jx,
+                     const void* Jy, const void* Jz, const void* w01, const void* w2, void* s0, void* s1, void* s2,
+                     void* s3, long n, double alpha, const double* g2_sum, double* partial, unsigned blocks,
+                     hipStream_t st) {
+  if (prec == P_C128)
+    hipLaunchKernelGGL(k_hel_vreg<double>, dim3(blocks), dim3(256), 0, st, psi, d0, d1, d2, (const double*)Jx,
+                       (const double*)Jy, (const double*)Jz, w01, w2, s0, s1, s2, s3, (unsigned)n, alpha, g2_sum,
+                       partial);
+  else
+    hipLaunchKernelGGL(k_hel_vreg<float>, dim3(blocks), dim3(256), 0, st, psi, d0, d1, d2, (const float*)Jx,
+                       (const float*)Jy, (const float*)Jz, w01, w2, s0, s1, s2, s3, (unsigned)n, alpha, g2_sum,
+                       partial);
 }
 void launch_hel_spectral(int prec, const void* V01, const void* V2, const void* R01, const void* R2, const void* O01,
-                         const void* O2, int nx, int ny, int nz, int nshell, unsigned blocks, long chunk,
-                         double* bins, hipStream_t st) {
+                         const void* O2, int nx, int ny, int nz, int nshell, unsigned blocks, double* bins, hipStream_t st) {
   const size_t sh = sizeof(double) * 2 * (size_t)nshell;
+  // the planes iz = 0 .. nz/2 only (mirror pairs), in `blocks` chunks
+  const long nh = (long)(nz / 2 + 1) * nx * ny, chunk = (nh + blocks - 1) / blocks;
   GPK_PREC_LAUNCH(k_hel_spectral, dim3(blocks), dim3(64), sh, st, V01, V2, R01, R2, O01, O2, nx, ny, nz, nshell,
                   chunk, bins);
 }

@@ -70,6 +70,7 @@ void fill(PassEntry& e) {
   e.fn[KIND][V_ENERGY] = &launch_pass<Real, S, KIND, FWD, PRO_ENERGY>;
   e.fn[KIND][V_POWER] = &launch_pass<Real, S, KIND, FWD, PRO_POWER>;
   e.fn[KIND][V_VPOWER] = &launch_pass<Real, S, KIND, FWD, PRO_VPOWER>;
+  e.fn[KIND][V_HESS] = &launch_pass<Real, S, KIND, FWD, PRO_HESS>;
   e.fn[KIND][V_TURN] = &launch_pass<Real, S, KIND, TURN, PRO_NL>;
   // the stage exchanges order a swapping tile's reads before its writes
   if constexpr (KIND == CONTIG && S::NS > 1) e.fn[KIND][V_PROP_SWAP] = &launch_pass<Real, S, KIND, PROP, PRO_SWAP>;

@@ -435,7 +435,6 @@ gp_status plan_init(gp_plan_s* p, const gp_desc* d, hipStream_t stream) {
   if ((st = dev_alloc(p, (void**)&p->field_part, 3 * p->field_blocks * sizeof(double))) != GP_OK) return st;
   if ((st = dev_alloc(p, (void**)&p->loss_part, p->field_blocks * sizeof(double))) != GP_OK) return st;
   p->spec_blocks = (unsigned)std::min<long>(2048, std::max<long>(1, (p->ntot + 511) / 512));
-  p->spec_chunk = (p->ntot + p->spec_blocks - 1) / p->spec_blocks;
   if ((st = dev_alloc(p, (void**)&p->bins_part, (size_t)p->spec_blocks * 4 * p->nshell * sizeof(double))) != GP_OK)
     return st;
   const int nmax = std::max(d->n[0], std::max(d->n[1], d->n[2]));
@@ -1367,31 +1366,35 @@ gp_status gp_helicity(gp_plan_t* p, const void* psi, void* work, double* out, do
   if ((st = deriv_pass(p, 0, S[5], S[5])) != GP_OK) return st;
   launch_hel_omega(p->prec, S[3], S[4], S[5], S[6], S[7], n, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
-  // J_i = Im(sum_j (d_i d_j psi)(d_j psi)*) into S4 (J_x + i J_y), S5 (J_z), one Hessian
-  // entry at a time in S3: H_ij = d_i (d_j psi)
-  struct Entry { int i, j; };
-  const Entry hess[6] = {{0, 0}, {1, 1}, {2, 2}, {1, 0}, {2, 0}, {2, 1}};
-  for (int e = 0; e < 6; ++e) {
-    const int i = hess[e].i, j = hess[e].j;
-    if ((st = deriv_pass(p, i, S[j], S[3])) != GP_OK) return st;
-    // H_ij adds conj(d_j psi) H_ij to J_i and, off the diagonal, conj(d_i psi) H_ij to J_j
-    launch_hel_acc(p->prec, S[3], S[j], i, i != j ? S[i] : S[j], i != j ? j : -1, e == 0, S[4], S[5], n, p->stream);
+  // J_i = Im(sum_j (d_i d_j psi)(d_j psi)*), three real fields in S5 (x, y) and S4 (z): one pass
+  // along axis i differentiates the three first derivatives and sums in registers
+  const size_t rb = (size_t)n * p->S / 2;
+  void* J[3] = {S[5], (char*)S[5] + rb, S[4]};
+  for (int i = 0; i < 3; ++i) {
+    const Axis& A = p->ax[i];
+    if (A.n == 1) {
+      HIPCHK(p, hipMemsetAsync(J[i], 0, rb, p->stream));
+      continue;
+    }
+    PassArgs g{};
+    g.in = S[0]; g.aux = S[1]; g.aux2 = S[2]; g.out = J[i]; g.tw = A.tw; g.mult = A.deriv;
+    g.npencils = A.npencils; g.inner = A.inner; g.outer = A.outer; g.es = A.es;
+    A.e->fn[A.kind][V_HESS](g, A.blocks, 1, p->stream);
     if ((st = check_launch(p)) != GP_OK) return st;
   }
-  // v_reg into S3 (x + i y), S4 (z); physical-space sums of v.omega and v_reg.omega
-  launch_hel_vreg(p->prec, psi, S[0], S[1], S[2], S[4], S[5], S[6], S[7], S[3], S[4], n, al, g2_sum,
-                  p->field_part, p->field_blocks, p->stream);
+  // physical-space sums of v.omega and v_reg.omega; for the spectra v_x + i v_y into S0,
+  // v_z into S1, vreg_z into S2, vreg_x + i vreg_y into S3
+  launch_hel_vreg(p->prec, psi, S[0], S[1], S[2], J[0], J[1], J[2], S[6], S[7], spec ? S[0] : nullptr,
+                  spec ? S[1] : nullptr, spec ? S[2] : nullptr, spec ? S[3] : nullptr, n, al, g2_sum, p->field_part,
+                  p->field_blocks, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
   launch_segsum(p->field_part, p->field_blocks, 2, p->d_result, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
   if (spec) {
-    // spectra: v into S0 (x + i y), S1 (z); transforms of v, v_reg, omega; shell bins
-    launch_hel_vpack(p->prec, psi, S[0], S[1], S[2], n, al, p->stream);
-    if ((st = check_launch(p)) != GP_OK) return st;
-    for (int k : {0, 1, 3, 4, 6, 7})
-      if ((st = fwd3_unnorm(p, S[k])) != GP_OK) return st;
-    launch_hel_spectral(p->prec, S[0], S[1], S[3], S[4], S[6], S[7], p->d.n[0], p->d.n[1], p->d.n[2], p->nshell,
-                        p->spec_blocks, p->spec_chunk, p->bins_part, p->stream);
+    if ((st = fwd3_unnorm(p, S[0], 4)) != GP_OK) return st;
+    if ((st = fwd3_unnorm(p, S[6], 2)) != GP_OK) return st;
+    launch_hel_spectral(p->prec, S[0], S[1], S[3], S[2], S[6], S[7], p->d.n[0], p->d.n[1], p->d.n[2], p->nshell,
+                        p->spec_blocks, p->bins_part, p->stream);
     if ((st = check_launch(p)) != GP_OK) return st;
     const unsigned chunks = colsum_chunks(p->spec_blocks);
     launch_colsum(p->bins_part, p->spec_blocks, 2 * p->nshell, chunks, p->d_red, p->stream);

@@ -95,3 +95,24 @@ def test_vortex_rings_in_bricks(shape, far):
         ref = ref * I._pair_periodic(*s, r, d, xi)
     assert np.max(np.abs(got - ref)) <= (1e-11 if far else 2e-13)
     plan.close()
+
+
+@pytest.mark.parametrize("shape", [(96, 3, 6), (6, 48, 12), (3, 2, 24), (64, 12, 8)])
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+def test_helicity_at_tile_remainders(shape, prec):
+    """The Hessian passes with a last tile of few pencils, odd extents (mirror pairs without a
+    Nyquist plane) and short axes.  Tolerances as for the sizes with whole tiles: round-off
+    amplified by the divisions by |psi|^2 and |grad psi|^2 near cores and stagnation points."""
+    import paper_2003_03590_amd as gp
+    from oracle import helicity as OH
+    psi = I.random_field(shape[::-1], seed=71)
+    base = psi.astype(np.complex64).astype(np.complex128) if prec == "c64" else psi
+    ref = OH.helicity(base, 0.3)
+    v, om = O.velocity(base, 0.3), OH.curl(O.velocity(base, 0.3))
+    scale = float(np.mean(np.sqrt(sum(c * c for c in v)) * np.sqrt(sum(c * c for c in om))))
+    plan = gp.Plan(shape, 0.3, 2.0, 1e-3, prec)
+    H, Hreg, spec = plan.helicity(torch.from_numpy(psi).to(DEV).to(plan.dtype).contiguous())
+    tol = 1e-10 if prec == "c128" else 1e-3
+    assert abs(H - ref["H"]) < tol * scale and abs(Hreg - ref["H_reg"]) < tol * scale
+    assert np.abs(spec - ref["spec"]).max() < tol * scale
+    plan.close()
