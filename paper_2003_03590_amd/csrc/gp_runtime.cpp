@@ -164,7 +164,6 @@ struct gp_plan_s {
   unsigned field_blocks = 0;
   double* bins_part = nullptr;     // spec_blocks * 4 * nshell
   unsigned spec_blocks = 0;
-  long spec_chunk = 0;
   double* power_part = nullptr;    // 3 * 16 * nmax: power sums by chunks of tiles
   double* loss_part = nullptr;     // field_blocks
   double* d_red = nullptr;         // 6 + 16 * 4 * nshell reduced sums
@@ -2063,35 +2062,12 @@ static std::string tune_key(const std::string& arch, const gp_plan_s* p, int axi
   return b;
 }
 
-// time `reps` in-place propagator passes of the selected schedule (microseconds per launch)
-static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, double* us) {
-  hipEvent_t a, b;
-  HIPCHK(p, hipEventCreate(&a));
-  HIPCHK(p, hipEventCreate(&b));
-  gp_status st = pass(p, axis, V_PROP, scratch, scratch, p->ax[axis].mult[TAU_DT]);
-  if (st == GP_OK) {
-    (void)hipEventRecord(a, p->stream);
-    for (int r = 0; r < reps && st == GP_OK; ++r) st = pass(p, axis, V_PROP, scratch, scratch, p->ax[axis].mult[TAU_DT]);
-    (void)hipEventRecord(b, p->stream);
-  }
-  float ms = 0.f;
-  if (st == GP_OK) {
-    hipError_t e = hipEventSynchronize(b);
-    if (e == hipSuccess) e = hipEventElapsedTime(&ms, a, b);
-    if (e != hipSuccess) { p->broken = true; st = fail(GP_ERR_HIP, "event timing: %s", hipGetErrorString(e)); }
-  }
-  (void)hipEventDestroy(a);
-  (void)hipEventDestroy(b);
-  *us = 1e3 * ms / std::max(1, reps);
-  return st;
-}
-
 // time `reps` calls of launch() on the plan's stream (microseconds per call)
-static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::function<void()>& launch) {
+static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::function<void()>& launch, bool warm = true) {
   hipEvent_t a, b;
   HIPCHK(p, hipEventCreate(&a));
   HIPCHK(p, hipEventCreate(&b));
-  launch();                                    // warm-up
+  if (warm) launch();
   (void)hipEventRecord(a, p->stream);
   for (int r = 0; r < reps; ++r) launch();
   (void)hipEventRecord(b, p->stream);
@@ -2103,6 +2079,35 @@ static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::funct
   if (e != hipSuccess) { p->broken = true; return fail(GP_ERR_HIP, "event timing: %s", hipGetErrorString(e)); }
   *us = 1e3 * ms / std::max(1, reps);
   return check_launch(p);
+}
+
+// time the selected schedule of an axis: microseconds of one in-place propagator pass plus one
+// turning pass (a plan runs both, and a schedule with many points a lane may do well in the
+// first and run out of registers in the second: 48^3 runs took 65 to 90 us a turning pass
+// with most schedules and 197 us with one that a propagator pass alone could choose).
+// `plain`: the fastest propagator pass of the axis so far; a schedule 15 % slower than that
+// is not timed further, which pays for the turning passes.
+static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, double* plain, double* us) {
+  const double nl = p->d.beta * p->d.dt;
+  gp_status st, inner = GP_OK;
+  auto run = [&](StageMode mode, int n, bool warm, double* t) {
+    const gp_status e = time_calls(p, n, t, [&] {
+      if (inner == GP_OK) inner = stage(p, axis, mode, scratch, TAU_DT, TAU_DT, nl);
+    }, warm);
+    return e != GP_OK ? e : inner;
+  };
+  double t = 0, more = 0, turn = 0;
+  *us = 1e300;
+  if ((st = run(S_PLAIN, 1, true, &t)) != GP_OK) return st;
+  if (t > 1.15 * *plain) return GP_OK;
+  if (reps > 2) {
+    if ((st = run(S_PLAIN, reps - 2, false, &more)) != GP_OK) return st;
+    t = (t + (reps - 2) * more) / (reps - 1);
+  }
+  *plain = std::min(*plain, t);
+  if ((st = run(S_TURN, 1, true, &turn)) != GP_OK) return st;
+  *us = t + turn;
+  return GP_OK;
 }
 
 // Timings within 1 % count as ties, resolved to the candidate tried first (the lower
@@ -2268,14 +2273,14 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
       continue;
     }
     const int nv = gp_variant_count(p->ax[a].n, p->prec);
-    double best = 1e300;
+    double best = 1e300, plain = 1e300;
     int bestv = 0;
     for (int v = 0; v < nv; ++v) {
       if (!find_entry(p->ax[a].n, p->prec, v)) continue;
       if ((st = gp_select_variant(p, a, v)) != GP_OK) return st;
       double us = 0;
-      if ((st = time_axis(p, a, scratch, reps, &us)) != GP_OK) return st;
-      tune_note(p, "schedule", a, v, us);
+      if ((st = time_axis(p, a, scratch, reps, &plain, &us)) != GP_OK) return st;
+      if (us < 1e299) tune_note(p, "schedule", a, v, us);
       if (us < TUNE_TIE * best) { best = us; bestv = v; }
     }
     if ((st = gp_select_variant(p, a, bestv)) != GP_OK) return st;
