@@ -2100,9 +2100,9 @@ static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, doub
   *us = 1e300;
   if ((st = run(S_PLAIN, 1, true, &t)) != GP_OK) return st;
   if (t > 1.15 * *plain) return GP_OK;
-  if (reps > 2) {
-    if ((st = run(S_PLAIN, reps - 2, false, &more)) != GP_OK) return st;
-    t = (t + (reps - 2) * more) / (reps - 1);
+  if (reps > 3) {
+    if ((st = run(S_PLAIN, reps - 3, false, &more)) != GP_OK) return st;
+    t = (t + (reps - 3) * more) / (reps - 2);
   }
   *plain = std::min(*plain, t);
   if ((st = run(S_TURN, 1, true, &turn)) != GP_OK) return st;
