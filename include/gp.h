@@ -311,7 +311,8 @@ GP_API const char* gp_schedule_name(const gp_plan_t* p, int32_t axis);
  * z-plane (both sub-steps on chip, psi read and written once; the x and y factors
  * commute, time-evolution section); a step is then one sweep.  Variant 1 needs nx == ny with a compiled
  * plane length (complex64: 16..96, complex128: 16..64); otherwise
- * GP_ERR_UNSUPPORTED.  axis 4 (single plans, separate passes) selects the axis pass
+ * GP_ERR_UNSUPPORTED.  Single plans start with variant 1 up to 32 points (complex128)
+ * or 64 (complex64), until a variant of another axis is selected.  axis 4 (single plans, separate passes) selects the axis pass
  * that comes first and carries the first nonlinear rotations (variant 0, 1, 2 = x, y,
  * z; the linear sub-steps commute, so any order is the same split step): the
  * rotations lie in the passes of that axis and of the last of the others in x, y, z

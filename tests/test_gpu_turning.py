@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 
 import gp_inputs as I
+from oracle import gp as O
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -92,4 +93,26 @@ def test_swapping_x_pass(shape, prec):
         plan.select_variant(0, v)
         for n in (1, 2, -3):
             _check(plan, psi0, n, 1.5e-13 if prec == "c128" else 5e-6)
+    plan.close()
+
+
+@pytest.mark.parametrize("shape,prec,plane", [((16, 16, 1), "c128", True), ((32, 32, 6), "c128", True),
+                                              ((48, 48, 4), "c128", False), ((64, 64, 2), "c64", True),
+                                              ((96, 96, 2), "c64", False), ((32, 16, 32), "c64", False)])
+def test_default_xy_form(shape, prec, plane):
+    """Single plans up to the compiled limit start with the xy-plane pass; choosing for the
+    separate passes ends it.  Both forms against the oracle's literal steps, at the tolerance
+    of the plane pass chosen by hand (round-off of three steps)."""
+    import paper_2003_03590_amd as gp
+    plan = gp.Plan(shape, 0.3, 4.0, 0.01, prec)
+    psi0 = I.random_field(shape[::-1], seed=33)
+    base = psi0.astype(np.complex64).astype(np.complex128) if prec == "c64" else psi0
+    ref, tol = O.evolve(base, 0.3, 4.0, 0.01, 3), 1e-12 if prec == "c128" else 5e-6
+    for on in (plane, False):
+        assert plan.schedule(3).startswith("xy: plane" if on else "xy: separate")
+        psi = torch.from_numpy(psi0).to(DEV).to(plan.dtype).contiguous()
+        plan.step_n(psi, 3)
+        got = psi.cpu().numpy().astype(np.complex128)
+        assert np.linalg.norm(got - ref) < tol * np.linalg.norm(ref)
+        plan.select_variant(4, 0)
     plan.close()
