@@ -57,6 +57,15 @@ def pass_traffic(name="axis_pass_tg256_traffic.json", schedules=None):
         return None
 
 
+def chain_passes(plan, steps):
+    """Passes of one step_n call: with the layout-rotating forms three per linear step; else
+    each nonlinear rotation sits in a pass between the two linear sub-steps of one axis
+    (turning pass), which leaves one middle pass per linear step and the two ends."""
+    if plan.schedule(5).startswith("layout: rotating"):
+        return 3 * (steps + 1)
+    return 2 * (steps + 1) + 1
+
+
 def cpu_model() -> str:
     try:
         for line in open("/proc/cpuinfo"):
@@ -99,7 +108,7 @@ def run_form(gp, torch, psi0_np, w, prec, steps, warmup, tune=True):
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     step_ms = [a.elapsed_time(b) for a, b in ev]
-    passes_per_call = 3 * (DIAG_EVERY + 1)
+    passes_per_call = chain_passes(plan, DIAG_EVERY)
     mean_pass_ms = sum(step_ms) / (passes_per_call * steps)
     E0 = e0["energy"]
     N0 = e0["mass"]
@@ -116,7 +125,7 @@ def literal_form(torch, plan, psi0_np, step_ms_merged, steps=10):
     plan and field: per step two 3-D linear half steps, each a forward 3-D FFT
     (3 passes, the last applying the 3-D multiplier before it stores) and an
     inverse 3-D FFT (3 passes), with the nonlinear rotation between them: 13 sweeps,
-    26 N^3 S bytes per step against the merged form's 6 N^3 S."""
+    26 N^3 S bytes per step against the merged form's 4 N^3 S."""
     S = 16 if plan.prec == 0 else 8
     dt = torch.complex128 if S == 16 else torch.complex64
     psi = torch.from_numpy(psi0_np).to("cuda").to(dt).contiguous()
@@ -162,11 +171,11 @@ def ensemble_form(gp, torch, I):
     el = time.perf_counter() - t
     e1 = bp.energies(states)
     pts = sum(float(r["n"]) ** 3 for r in runs)
-    # algorithmic bytes: a run on the xy-plane pass reads and writes its state twice per
-    # step (plane pass + z pass), otherwise three times (x, y, z passes); the call's
-    # opening half step adds one more step's worth
+    # algorithmic bytes: a run on the xy-plane pass reads and writes its state once per step
+    # (z turning pass and plane turning pass in turn), otherwise twice (a middle and a turning
+    # pass); the call's opening half step adds one more step's worth
     plane = [bp.schedule(i, 3).startswith("xy: plane") for i in range(len(runs))]
-    nbytes = sum((4.0 if pl else 6.0) * float(r["n"]) ** 3 * 8 for r, pl in zip(runs, plane)) * (w["steps"] + 1)
+    nbytes = sum((2.0 if pl else 4.0) * float(r["n"]) ** 3 * 8 for r, pl in zip(runs, plane)) * (w["steps"] + 1)
     return {"value": pts * w["steps"] / el, "unit": "grid-point.steps/s (summed over runs)",
             "runs": len(runs), "steps": w["steps"], "seconds": el,
             "hbm_GBs": nbytes / el / 1e9, "bytes": nbytes,
@@ -203,7 +212,7 @@ def large_form(gp, torch, I, steps=5):
     b.record(st)
     torch.cuda.synchronize()
     ms = a.elapsed_time(b)
-    launches = 3 * (steps + 1)
+    launches = chain_passes(plan, steps)
     per_launch = 2.0 * float(n) ** 3 * 8
     gbs = per_launch * launches / (ms / 1e3) / 1e9
     # each axis pass alone (the propagator sub-step), and a device copy of the same
@@ -231,8 +240,8 @@ def large_form(gp, torch, I, steps=5):
         copies[name] = per_launch / (a.elapsed_time(b) / 3 / 1e3) / 1e9
     copy_gbs = copies["gp_copy_state"]
     del x
-    # both forms of the linear steps, whichever the autotuner kept (fixed layout in
-    # place, or layout-rotating passes through one more state)
+    # all forms of the linear steps, whichever the autotuner kept (in place, or
+    # layout-rotating passes through one more state)
     chosen = plan.schedule(5)
     forms = {}
     for v, name in ((0, "fixed"), (1, "rotating"), (2, "rotating+contiguous")):
@@ -244,9 +253,8 @@ def large_form(gp, torch, I, steps=5):
         b.record(st)
         torch.cuda.synchronize()
         fms = a.elapsed_time(b)
-        forms[name] = {"ms_per_step": fms / steps,
-                       "axis_pass_gbs": per_launch * launches / (fms / 1e3) / 1e9,
-                       "frac": per_launch * launches / (fms / 1e3) / 1e9 / HBM_PEAK_GBS}
+        fgbs = per_launch * chain_passes(plan, steps) / (fms / 1e3) / 1e9
+        forms[name] = {"ms_per_step": fms / steps, "axis_pass_gbs": fgbs, "frac": fgbs / HBM_PEAK_GBS}
     rot = chosen.startswith("layout: rotating")
     mixed = chosen.startswith("layout: rotating+contiguous")
     plan.select_variant(5, 2 if mixed else 1 if rot else 0)
@@ -259,8 +267,8 @@ def large_form(gp, torch, I, steps=5):
                                    "the three (the nonlinear rotation fused into the first rot_pass)") if mixed else
                                   ("rot_pass (layout-rotating propagator pass; the nonlinear rotation fused "
                                    "into the first pass of each step)") if rot else
-                                  ("axis_pass (propagator; the nonlinear rotation fused into the carrier "
-                                   "axis's pass)"),
+                                  ("axis_pass: y turning pass (two propagators and the nonlinear rotation "
+                                   "between them) and x pass, which exchanges y and z in the layout, in turn"),
                         "per_launch": "one axis pass: reads and writes the whole state once (2 N^3 S bytes)",
                         "traffic": (pass_traffic("mixed_pass_rvr1024_traffic.json") if mixed else
                                     pass_traffic("rot_pass_rvr1024_traffic.json") if rot else
@@ -283,19 +291,19 @@ def large_form(gp, torch, I, steps=5):
     return out
 
 
-ARGLE_BYTES_PER_POINT = 30.5    # x S bytes per grid point and ARGLE step (see argle_form)
+ARGLE_BYTES_PER_POINT = 18.5    # x S bytes per grid point and ARGLE step (see argle_form)
 
 
 def argle_form(gp, torch, I, steps=200, warmup=20):
     """Imaginary-time (ARGLE) preparation at 256^3 complex128 in the configuration
     of the grid-convergence run TG_h (alpha = 0.05, beta = 40, dtau = 6.25e-3, Taylor-
     Green ansatz and flow): `steps` steps timed with HIP events on the plan's stream.
-    Algorithmic bytes per step, in units of S = 16 bytes per point: the x and y
-    derivative passes (read phi, write d_j: 4), the z-derivative pass that forms the
-    explicit part in place of d_z (read phi, d_x, d_y and the three real velocity
-    planes, write n: 5.5), forward 3-D transforms of phi and n (3 passes each, 12),
-    the diagonal solve (read both, write phi: 3) and the inverse 3-D transform (6):
-    30.5 S."""
+    Algorithmic bytes per step, in units of S = 16 bytes per point: the y derivative
+    (read phi, write d_y: 2), the z pass that takes d_z, forms the explicit part and
+    transforms it along z (read phi, d_x, d_y and the three real velocity planes, write:
+    5.5), the transform along x (2), the y pass that solves in Fourier space and goes back
+    along y (read and write both fields: 4), back along z (2), and back along x with the
+    x derivative of the new phi beside it (3): 18.5 S."""
     import numpy as np
     n, alpha, beta, dtau = 256, 0.05, 40.0, 6.25e-3
     plan = gp.Plan(n, alpha, beta, 1e-3, "c128")
@@ -522,15 +530,15 @@ def main(argv=None):
                    "bench_step": "100 Strang steps + gp_spectra; every 10 bench steps the workload "
                                  "restarts from its initial condition"},
         "value_step_only": step_only,
-        "hbm_gbs_per_split_step": 6.0 * npts * S / (sum(f64["step_ms"]) / 1e3 / split_steps) / 1e9,
-        "bytes_per_split_step_min": 6.0 * npts * S,
+        "hbm_gbs_per_split_step": 4.0 * npts * S / (sum(f64["step_ms"]) / 1e3 / split_steps) / 1e9,
+        "bytes_per_split_step_min": 4.0 * npts * S,
         "roofline_tg256_c128": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "cache_resident": "the 256 MiB state fits the 256 MB last-level cache; the HBM-bound "
                                        "form (the line's roofline) is the 1024^3 complex64 pass",
                      "traffic": pass_traffic(schedules=[f64["plan"].schedule(ax) for ax in range(3)]),
-                     "kernel": "axis_pass (propagator; the nonlinear rotation fused into the carrier axis's pass), "
-                               "mean of the three",
+                     "kernel": "axis_pass: middle pass (one propagator) and turning pass (two propagators and the "
+                               "nonlinear rotation between them), mean of both",
                      "per_launch_bytes": bytes_per_pass, "mean_launch_us": f64["mean_pass_ms"] * 1e3},
         "drift_f64": {"dE": f64["dE"], "dN": f64["dN"]},
         "schedule": [f64["plan"].schedule(ax) for ax in range(6)],
