@@ -1030,7 +1030,7 @@ int32_t gp_variant_count(int32_t n, int32_t prec) {
   return c;
 }
 
-gp_status gp_select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
+static gp_status select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
   gp_status st = usable(p);
   if (st != GP_OK) return st;
   if (p->is_batch) {   // the xy choice for every run that has a plane schedule
@@ -1056,8 +1056,6 @@ gp_status gp_select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
     p->plane.by_default = false;
     return GP_OK;
   }
-  // a choice for the separate passes ends a plane pass that was not chosen
-  if (p->plane.by_default) plane_off(p);
   if (axis == 5) {   // linear steps: 0 = fixed layout, in place; 1 = layout-rotating passes
     if (variant == 0) {
       if (p->rot.work) {
@@ -1120,6 +1118,13 @@ gp_status gp_select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
     if ((st = dev_alloc(p, (void**)&p->kin_part, kin_n * sizeof(double))) != GP_OK) return st;
   }
   return GP_OK;
+}
+
+gp_status gp_select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
+  const gp_status st = select_variant(p, axis, variant);
+  // a choice for the separate passes ends a plane pass that was not chosen
+  if (st == GP_OK && axis != 3 && p->plane.by_default) plane_off(p);
+  return st;
 }
 
 gp_status gp_init_phase(gp_plan_t* p, const double* theta, void* psi) {

@@ -108,6 +108,8 @@ def test_default_xy_form(shape, prec, plane):
     psi0 = I.random_field(shape[::-1], seed=33)
     base = psi0.astype(np.complex64).astype(np.complex128) if prec == "c64" else psi0
     ref, tol = O.evolve(base, 0.3, 4.0, 0.01, 3), 1e-12 if prec == "c128" else 5e-6
+    with pytest.raises(gp._lib.GPError):          # a refused choice changes nothing
+        plan.select_variant(4, 3)
     for on in (plane, False):
         assert plan.schedule(3).startswith("xy: plane" if on else "xy: separate")
         psi = torch.from_numpy(psi0).to(DEV).to(plan.dtype).contiguous()
