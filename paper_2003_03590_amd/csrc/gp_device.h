@@ -19,6 +19,14 @@ struct alignas(2 * sizeof(Real)) cplx {
   Real x, y;
 };
 
+// Which products of a sum are fused is written out in the arithmetic of the sub-steps
+// (fmadd), not left to the compiler, which decides for each kernel by itself: two linear
+// sub-steps and the rotation between them give the same bits in one pass as in two, so a
+// state does not depend on how the passes of its steps are cut.
+#define GPK_AS_WRITTEN _Pragma("clang fp contract(off)")
+__device__ __forceinline__ double fmadd(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float fmadd(float a, float b, float c) { return fmaf(a, b, c); }
+
 template <class Real>
 __device__ __forceinline__ cplx<Real> mk(Real a, Real b) { cplx<Real> r; r.x = a; r.y = b; return r; }
 template <class Real>
@@ -27,17 +35,25 @@ template <class Real>
 __device__ __forceinline__ cplx<Real> operator-(cplx<Real> a, cplx<Real> b) { return mk(a.x - b.x, a.y - b.y); }
 template <class Real>
 __device__ __forceinline__ cplx<Real> cmul(cplx<Real> a, cplx<Real> b) {
-  return mk(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+  GPK_AS_WRITTEN
+  return mk(fmadd(a.x, b.x, -(a.y * b.y)), fmadd(a.x, b.y, a.y * b.x));
 }
 // a * conj(b)
 template <class Real>
 __device__ __forceinline__ cplx<Real> cmulc(cplx<Real> a, cplx<Real> b) {
-  return mk(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+  GPK_AS_WRITTEN
+  return mk(fmadd(a.x, b.x, a.y * b.y), fmadd(a.y, b.x, -(a.x * b.y)));
 }
 template <class Real>
-__device__ __forceinline__ cplx<Real> cscale(cplx<Real> a, Real s) { return mk(a.x * s, a.y * s); }
+__device__ __forceinline__ cplx<Real> cscale(cplx<Real> a, Real s) {
+  GPK_AS_WRITTEN
+  return mk(a.x * s, a.y * s);
+}
 template <class Real>
-__device__ __forceinline__ Real cabs2(cplx<Real> a) { return a.x * a.x + a.y * a.y; }
+__device__ __forceinline__ Real cabs2(cplx<Real> a) {
+  GPK_AS_WRITTEN
+  return fmadd(a.x, a.x, a.y * a.y);
+}
 
 struct Neu {          // Neumaier compensated sum
   double s = 0.0, c = 0.0;
@@ -63,12 +79,14 @@ __device__ __forceinline__ cplx<double> tmul(cplx<double> a, const Tab<double>& 
 __device__ __forceinline__ cplx<double> tmulc(cplx<double> a, const Tab<double>& t) { return cmulc(a, t.v); }
 // a * (hi + lo), the small products added first
 __device__ __forceinline__ cplx<float> tmul(cplx<float> a, const Tab<float>& t) {
-  const float sr = a.x * t.lo.x - a.y * t.lo.y, si = a.x * t.lo.y + a.y * t.lo.x;
+  GPK_AS_WRITTEN
+  const float sr = fmaf(a.x, t.lo.x, -(a.y * t.lo.y)), si = fmaf(a.x, t.lo.y, a.y * t.lo.x);
   return mk(fmaf(a.x, t.hi.x, fmaf(-a.y, t.hi.y, sr)), fmaf(a.x, t.hi.y, fmaf(a.y, t.hi.x, si)));
 }
 // a * conj(hi + lo)
 __device__ __forceinline__ cplx<float> tmulc(cplx<float> a, const Tab<float>& t) {
-  const float sr = a.x * t.lo.x + a.y * t.lo.y, si = a.y * t.lo.x - a.x * t.lo.y;
+  GPK_AS_WRITTEN
+  const float sr = fmaf(a.x, t.lo.x, a.y * t.lo.y), si = fmaf(a.y, t.lo.x, -(a.x * t.lo.y));
   return mk(fmaf(a.x, t.hi.x, fmaf(a.y, t.hi.y, sr)), fmaf(a.y, t.hi.x, fmaf(-a.x, t.hi.y, si)));
 }
 
@@ -80,6 +98,7 @@ __device__ __forceinline__ cplx<float> tmulc(cplx<float> a, const Tab<float>& t)
 // drift over a run.
 __device__ __forceinline__ cplx<double> pmul(cplx<double> a, cplx<double> m) { return cmul(a, m); }
 __device__ __forceinline__ cplx<float> pmul(cplx<float> a, cplx<double> m) {
+  GPK_AS_WRITTEN
   const double x = a.x, y = a.y;
   return mk(float(fma(x, m.x, -y * m.y)), float(fma(x, m.y, y * m.x)));
 }
@@ -170,6 +189,7 @@ struct Root {
 // multiply v by exp(SGN * 2 pi i M / R), with exact special cases
 template <int M, int R, int SGN, class Real>
 __device__ __forceinline__ cplx<Real> rot(cplx<Real> v) {
+  GPK_AS_WRITTEN
   constexpr int m = ((M % R) + R) % R;
   if constexpr (m == 0) {
     return v;
@@ -184,11 +204,11 @@ __device__ __forceinline__ cplx<Real> rot(cplx<Real> v) {
     constexpr double cd = Root<m, R, SGN>::c, sd = Root<m, R, SGN>::s;
     constexpr float ch = float(cd), sh = float(sd);
     constexpr float cl = float(cd - double(ch)), sl = float(sd - double(sh));
-    const float sr = v.x * cl - v.y * sl, si = v.x * sl + v.y * cl;
+    const float sr = fmaf(v.x, cl, -(v.y * sl)), si = fmaf(v.x, sl, v.y * cl);
     return mk(fmaf(v.x, ch, fmaf(-v.y, sh, sr)), fmaf(v.x, sh, fmaf(v.y, ch, si)));
   } else {
     constexpr double c = Root<m, R, SGN>::c, s = Root<m, R, SGN>::s;
-    return mk(v.x * c - v.y * s, v.x * s + v.y * c);
+    return mk(fma(v.x, c, -(v.y * s)), fma(v.x, s, v.y * c));
   }
 }
 
@@ -209,6 +229,7 @@ constexpr double inv_fact(int n) { double f = 1.0; for (int i = 2; i <= n; ++i) 
 constexpr double kSmallAngle = 0.0625;
 
 __device__ __forceinline__ void sincos_small(double a, double* sn, double* cs) {
+  GPK_AS_WRITTEN
   const double r2 = a * a;
   double ps = ct::inv_fact(9);
   ps = fma(ps, r2, -ct::inv_fact(7));
@@ -223,6 +244,7 @@ __device__ __forceinline__ void sincos_small(double a, double* sn, double* cs) {
 }
 
 __device__ __forceinline__ void sincos_rot(double a, double* sn, double* cs) {
+  GPK_AS_WRITTEN
   if (fabs(a) <= kSmallAngle) {
     sincos_small(a, sn, cs);
   } else if (fabs(a) < 1024.0) {
@@ -260,6 +282,7 @@ __device__ __forceinline__ void sincos_rot(double a, double* sn, double* cs) {
 }
 
 __device__ __forceinline__ void sincos_rot(float a, float* sn, float* cs) {
+  GPK_AS_WRITTEN
   if (fabsf(a) <= 0.0625f) {
     const float r2 = a * a;
     const float ps = fmaf(float(ct::inv_fact(5)), r2, float(-ct::inv_fact(3)));
@@ -299,6 +322,7 @@ __device__ __forceinline__ void sincos_rot(float a, float* sn, float* cs) {
 // ~2.4e-4, fl(cos a) = 1 while sin a != 0 -- a gain that repeats at a point
 // every step with the slowly varying angle and so adds up coherently.
 __device__ __forceinline__ void sincos_m1_small(float a, float* sn, float* cm1) {
+  GPK_AS_WRITTEN
   const float r2 = a * a;
   const float ps = fmaf(float(ct::inv_fact(5)), r2, float(-ct::inv_fact(3)));
   *sn = fmaf(ps * r2, a, a);
@@ -306,6 +330,7 @@ __device__ __forceinline__ void sincos_m1_small(float a, float* sn, float* cm1) 
   *cm1 = pc * r2;
 }
 __device__ __forceinline__ void sincos_m1(float a, float* sn, float* cm1) {
+  GPK_AS_WRITTEN
   if (fabsf(a) <= float(kSmallAngle)) {
     sincos_m1_small(a, sn, cm1);
   } else {
@@ -345,28 +370,29 @@ struct Dft<2, SGN, Real> {
 template <int SGN, class Real>
 struct Dft<3, SGN, Real> {
   static __device__ __forceinline__ void run(cplx<Real>* x) {
+    GPK_AS_WRITTEN
     // c1 = cos(2pi/3) = -1/2, s1 = SGN*sin(2pi/3)
     constexpr Real h = Real(0.5);
     constexpr Real s = Real(SGN * 0.86602540378443864676372317075293618);
     cplx<Real> a = x[0], b = x[1], c = x[2];
     cplx<Real> t = b + c, d = b - c;
-    cplx<Real> m = mk(a.x - h * t.x, a.y - h * t.y);
+    cplx<Real> m = mk(fmadd(-h, t.x, a.x), fmadd(-h, t.y, a.y));
     x[0] = a + t;
     // X1 = a + b w + c w^2,  w = exp(SGN 2pi i/3) = -1/2 + i s
-    Real sdx, sdy;
     if constexpr (sizeof(Real) == 4) {
+      Real sdx, sdy;
       // s carried as hi + lo: an FP32-rounded s makes |w| != 1 by ~3e-8, a gain
       // on every mode not divisible by 3 that repeats in each radix-3 stage
       constexpr double sd = SGN * 0.86602540378443864676372317075293618;
       constexpr float shi = float(sd), slo = float(sd - double(shi));
       sdx = fmaf(shi, d.x, slo * d.x);
       sdy = fmaf(shi, d.y, slo * d.y);
+      x[1] = mk(m.x - sdy, m.y + sdx);
+      x[2] = mk(m.x + sdy, m.y - sdx);
     } else {
-      sdx = s * d.x;
-      sdy = s * d.y;
+      x[1] = mk(fmadd(-s, d.y, m.x), fmadd(s, d.x, m.y));
+      x[2] = mk(fmadd(s, d.y, m.x), fmadd(-s, d.x, m.y));
     }
-    x[1] = mk(m.x - sdy, m.y + sdx);
-    x[2] = mk(m.x + sdy, m.y - sdx);
   }
 };
 

@@ -395,6 +395,7 @@ __device__ __forceinline__ void pencil_pair(unsigned u, unsigned n, unsigned& i,
 // SMALL: the angle is known to be within the short series' range.
 template <bool SMALL>
 __device__ __forceinline__ cplx<double> nl_rotate(cplx<double> v, double coef) {
+  GPK_AS_WRITTEN
   double s, c;
   const double a = -coef * (cabs2(v) - 1.0);
   if constexpr (SMALL) sincos_small(a, &s, &c);
@@ -405,6 +406,7 @@ __device__ __forceinline__ cplx<double> nl_rotate(cplx<double> v, double coef) {
 // first, so the result carries one rounding at the size of v
 template <bool SMALL>
 __device__ __forceinline__ cplx<float> nl_rotate(cplx<float> v, double coef) {
+  GPK_AS_WRITTEN
   float s, cm1;
   const float a = -float(coef) * (cabs2(v) - 1.0f);
   if constexpr (SMALL) sincos_m1_small(a, &s, &cm1);
@@ -417,16 +419,17 @@ __device__ __forceinline__ cplx<float> nl_rotate(cplx<float> v, double coef) {
 //   lam <- conj(u) lam + 2 beta dt Im(conj(lam) u phi) phi,  u = exp(-i beta (|phi|^2-1) dt)
 template <bool SMALL, class Real>
 __device__ __forceinline__ cplx<Real> nl_adjoint(cplx<Real> lam, cplx<Real> phi, Real coef) {
+  GPK_AS_WRITTEN
   Real s, c;
   const Real a = -coef * (cabs2(phi) - Real(1));
   if constexpr (SMALL) sincos_small(a, &s, &c);
   else sincos_rot(a, &s, &c);
   const cplx<Real> u = mk(c, s);
   const cplx<Real> up = cmul(u, phi);
-  const Real im = lam.x * up.y - lam.y * up.x;          // Im(conj(lam) * up)
+  const Real im = fmadd(lam.x, up.y, -(lam.y * up.x));  // Im(conj(lam) * up)
   const cplx<Real> r = cmulc(lam, u);                    // conj(u) lam
   const Real f = Real(2) * coef * im;
-  return mk(r.x + f * phi.x, r.y + f * phi.y);
+  return mk(fmadd(f, phi.x, r.x), fmadd(f, phi.y, r.y));
 }
 
 // The rotations of all points a lane holds.  One branch for the lane: the angle
@@ -439,6 +442,7 @@ __device__ __forceinline__ cplx<Real> nl_adjoint(cplx<Real> lam, cplx<Real> phi,
 // at 1024^3 where the plain pass takes 3.6.)
 template <class Real>
 __device__ __forceinline__ bool angle_small(cplx<Real> v, Real coef) {
+  GPK_AS_WRITTEN
   return fabs(coef * (cabs2(v) - Real(1))) <= Real(kSmallAngle);    // false for a NaN
 }
 template <int E, class Real>
