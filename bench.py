@@ -171,11 +171,11 @@ def ensemble_form(gp, torch, I):
     el = time.perf_counter() - t
     e1 = bp.energies(states)
     pts = sum(float(r["n"]) ** 3 for r in runs)
-    # algorithmic bytes: a run on the xy-plane pass reads and writes its state once per step
-    # (z turning pass and plane turning pass in turn), otherwise twice (a middle and a turning
-    # pass); the call's opening half step adds one more step's worth
+    # algorithmic bytes: a run on the xy-plane pass reads and writes its state twice per step
+    # (plane pass, z pass), otherwise three times (x, y, z passes); the call's opening half
+    # step adds one more step's worth
     plane = [bp.schedule(i, 3).startswith("xy: plane") for i in range(len(runs))]
-    nbytes = sum((2.0 if pl else 4.0) * float(r["n"]) ** 3 * 8 for r, pl in zip(runs, plane)) * (w["steps"] + 1)
+    nbytes = sum((4.0 if pl else 6.0) * float(r["n"]) ** 3 * 8 for r, pl in zip(runs, plane)) * (w["steps"] + 1)
     return {"value": pts * w["steps"] / el, "unit": "grid-point.steps/s (summed over runs)",
             "runs": len(runs), "steps": w["steps"], "seconds": el,
             "hbm_GBs": nbytes / el / 1e9, "bytes": nbytes,

@@ -279,12 +279,12 @@ GP_API gp_status gp_argle_run(gp_plan_t* p, void* phi, const void* v, double dta
 
 /* Ensemble: advance run i's state psis[i] (host array of dev pointers) by nsteps
  * (negative: backward).  The merged sequence L(h) [N L(dt)]^(n-1) N L(h), in the
- * alternating order of gp_step_n, runs as recorded HIP graphs: its beginning, bodies
- * of 2^j steps (j = 0..7; the 128-step body repeated, the rest by the binary digits
- * of n - 2) and its end.  Each graph holds one grouped launch per size
+ * alternating order of gp_step_n, runs as recorded HIP graphs: the opening half step,
+ * bodies of 2^j applications (j = 0..7; the 128-application body repeated, the rest by
+ * the binary digits of n - 1) and the closing half step.  Each graph holds one grouped launch per size
  * group and pass, the size groups on parallel branches; a graph is recorded on
  * first use for the given states and replayed after, so a call launches at most
- * 2 + 7 + (n-2)/128 graphs of at most 2 x 128 launches per group, whatever n.
+ * 2 + 7 + (n-1)/128 graphs of at most 3 x 128 launches per group, whatever n.
  * New state pointers, gp_autotune or gp_select_variant drop the recorded graphs. */
 GP_API gp_status gp_step_n_batch(gp_plan_t* p, void* const* psis, int64_t nsteps);
 

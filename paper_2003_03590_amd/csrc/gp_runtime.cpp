@@ -210,8 +210,10 @@ struct gp_plan_s {
   RunPtrs* h_eptrs = nullptr;        // and their pinned source
   double* d_sums = nullptr;          // 5 sums per run
   std::vector<Group> groups;
-  // recorded step graphs, [sign: 0 forward, 1 backward][slot] (batch_record)
-  static constexpr int GPOW = 8, GBODY = 4, GSLOTS = GBODY + GPOW;
+  // recorded step graphs, [sign: 0 forward, 1 backward][slot]: slot 0 the opening half
+  // step L(h), 1 and 2 the closing [N, L(h)] with the stages in order and reversed,
+  // GBODY + j the body [N, L(dt)] x 2^j
+  static constexpr int GPOW = 8, GBODY = 3, GSLOTS = GBODY + GPOW;
   hipGraphExec_t gexec[2][GSLOTS] = {};
   std::vector<void*> graph_key;      // the states the recorded graphs and tables refer to
   std::vector<hipStream_t> side;     // capture branches of size groups 1, 2, ...
@@ -1801,13 +1803,8 @@ gp_status gp_plan_batch(const gp_desc* runs, int32_t nruns, void* hip_stream, gp
   return GP_OK;
 }
 
-// Multipliers of a grouped launch: one sub-step (half or full time step), or the two of a
-// turning pass.
-enum BatchTau { B_H = 0, B_DT, B_H_DT, B_DT_DT, B_DT_H, B_H_H, NBATCHTAU };
-static int batch_tau(int t, int t2) { return t == 0 ? (t2 == 0 ? B_H_H : B_H_DT) : (t2 == 0 ? B_DT_H : B_DT_DT); }
-
 // pointer tables of the grouped launches, both signs:
-// RunPtrs[sign][stage][BatchTau][member] per group
+// RunPtrs[sign][stage][tau: 0 half step, 1 full step][member] per group
 static gp_status batch_tables(gp_plan_s* p, void* const* psis) {
   // a launch of a recorded graph may still read the tables: let it finish
   HIPCHK(p, hipStreamSynchronize(p->stream));
@@ -1815,18 +1812,17 @@ static gp_status batch_tables(gp_plan_s* p, void* const* psis) {
   for (auto& g : p->groups) {
     const size_t m = g.members.size();
     const Stages q = stages_of(p->runs[g.members[0]]);    // every member made the same choices
-    std::vector<RunPtrs> h(2 * 3 * NBATCHTAU * m);
+    std::vector<RunPtrs> h(2 * 3 * 2 * m);
     for (int sg = 0; sg < 2; ++sg)
       for (int i = 0; i < q.n; ++i)
-        for (int t = 0; t < NBATCHTAU; ++t)
+        for (int t = 0; t < 2; ++t)
           for (size_t k = 0; k < m; ++k) {
             gp_plan_s* r = p->runs[g.members[k]];
-            const int half = sg ? TAU_MH : TAU_H, full = sg ? TAU_MDT : TAU_DT;
-            RunPtrs& e = h[((sg * 3 + i) * NBATCHTAU + t) * m + k];
+            RunPtrs& e = h[((sg * 3 + i) * 2 + t) * m + k];
             e.in = psis[g.members[k]];
             e.out = psis[g.members[k]];
-            e.mult = stage_mult(r, q.id[i], t == B_H || t == B_H_DT || t == B_H_H ? half : full);
-            e.mult2 = stage_mult(r, q.id[i], t == B_DT_H || t == B_H_H ? half : full);
+            e.mult = stage_mult(r, q.id[i], sg ? (t == 0 ? TAU_MH : TAU_MDT) : (t == 0 ? TAU_H : TAU_DT));
+            e.mult2 = nullptr;
             e.nl_coef = r->d.beta * (sg ? -r->d.dt : r->d.dt);
           }
     if (g.nptrs < h.size()) {
@@ -1842,39 +1838,17 @@ static gp_status batch_tables(gp_plan_s* p, void* const* psis) {
   return GP_OK;
 }
 
-// Launches of one size group for a stretch of the chain L(t_0) N L(t_1) ... N L(t_n)
-// (linear_chain), t = 0 a half step, 1 a full one.
-struct GroupChain {
-  const gp_plan_s* r0;
-  Stages q;
-  const RunPtrs* ptrs;     // of the sign
-  unsigned members;
-  hipStream_t st;
-  void put(int i, StageMode mode, int bt) const {
-    launch_stage(r0, q.id[i], mode, nullptr, nullptr, 0, 0, 0.0, ptrs + ((size_t)i * NBATCHTAU + bt) * members, members, st);
-  }
-  void begin() const { put(0, S_PLAIN, B_H); }
-  void middle(int t) const { for (int i = 1; i + 1 < q.n; ++i) put(i, S_PLAIN, t == 0 ? B_H : B_DT); }
-  // the rest of linear step k (odd: in reverse order), N and the first sub-step of the next
-  void element(bool odd, int t, int t2) const {
-    if (q.n == 1) { put(0, S_NL, t2 == 0 ? B_H : B_DT); return; }
-    middle(t);
-    put(odd ? 0 : q.n - 1, S_TURN, batch_tau(t, t2));
-  }
-  // the rest of the last linear step
-  void finish(bool odd) const {
-    if (q.n == 1) return;
-    middle(0);
-    put(odd ? 0 : q.n - 1, S_PLAIN, B_H);
-  }
-};
-
-// Record one step graph of the chain of n >= 2 steps: slot 0 = its beginning up to the first
-// sub-step of linear step 1; GBODY + j = 2^j elements from an odd linear step on; 2 and 3 =
-// from linear step n - 1 (even, odd) to the end.  Slot 1 = the whole chain of one step.
-// Size group g > 0 is captured on its own branch (fork from and join into the plan's stream).
+// record one step graph (gp_plan_s::gexec), with the nonlinear rotation fused into each
+// application's first pass.  The stages alternate as in linear_chain: the k-th linear step
+// (0 the opening one) takes them in order for even k and reversed for odd k, so a run of an
+// ensemble does the arithmetic of a single plan; a body starts after an even number of
+// steps.  Size group g > 0 is captured on its own branch (fork from and join into the
+// plan's stream).
 static gp_status batch_record(gp_plan_s* p, int sg, int slot) {
   constexpr int BODY = gp_plan_s::GBODY;
+  const int64_t reps = slot < BODY ? 1 : (int64_t)1 << (slot - BODY);
+  const int t = slot < BODY ? 0 : 1;
+  const int64_t first = slot < 2 ? 0 : 1;       // whether the first step's order is reversed
   HIPCHK(p, hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
   hipError_t ce = hipSuccess;
   if (p->groups.size() > 1) ce = hipEventRecord(p->fork_ev, p->stream);
@@ -1884,12 +1858,14 @@ static gp_status batch_record(gp_plan_s* p, int sg, int slot) {
     if (gi > 0) ce = hipStreamWaitEvent(st, p->fork_ev, 0);
     if (ce != hipSuccess) break;
     const gp_plan_s* r0 = p->runs[g.members[0]];
+    const Stages q = stages_of(r0);
     const size_t m = g.members.size();
-    const GroupChain c{r0, stages_of(r0), g.d_ptrs + (size_t)sg * 3 * NBATCHTAU * m, (unsigned)m, st};
-    if (slot == 0) { c.begin(); c.element(false, 0, 1); }
-    else if (slot == 1) { c.begin(); c.element(false, 0, 0); c.finish(true); }
-    else if (slot < BODY) { c.element(slot == 3, 1, 0); c.finish(slot == 2); }
-    else for (int64_t k = 0; k < (int64_t)1 << (slot - BODY); ++k) c.element(k % 2 == 0, 1, 1);
+    for (int64_t k = 0; k < reps; ++k)
+      for (int i = 0; i < q.n; ++i) {
+        const int j = (first + k) % 2 ? q.n - 1 - i : i;
+        launch_stage(r0, q.id[j], slot != 0 && i == 0 ? S_NL : S_PLAIN, nullptr, nullptr, 0, 0, 0.0,
+                     g.d_ptrs + ((size_t)(sg * 3 + j) * 2 + t) * m, (unsigned)m, st);
+      }
     if (gi > 0) {
       ce = hipEventRecord(p->join_ev[gi - 1], st);
       if (ce == hipSuccess) ce = hipStreamWaitEvent(p->stream, p->join_ev[gi - 1], 0);
@@ -1932,15 +1908,14 @@ gp_status gp_step_n_batch(gp_plan_t* p, void* const* psis, int64_t nsteps) {
   const bool same = p->graph_key.size() == p->runs.size() &&
                     std::equal(p->graph_key.begin(), p->graph_key.end(), psis);
   if (!same && (st = batch_tables(p, psis)) != GP_OK) return st;
-  // the chain's n - 2 inner elements as recorded graphs of 2^j elements each (the largest
-  // repeated, the rest by the binary digits, the single one last), so a call of any
-  // length launches a bounded set of graphs of bounded size
+  // L(h) [N L(dt)]^(n-1) N L(h): the body's n - 1 applications as recorded graphs of
+  // 2^j applications each (the largest repeated, the rest by the binary digits, the single
+  // one last), so a call of any length launches a bounded set of graphs of bounded size
   const int sg = nsteps < 0 ? 1 : 0;
   const int64_t n = nsteps < 0 ? -nsteps : nsteps;
-  if (n == 1) return batch_launch(p, sg, 1);
   if ((st = batch_launch(p, sg, 0)) != GP_OK) return st;
+  int64_t rem = n - 1;
   constexpr int BODY = gp_plan_s::GBODY, top = gp_plan_s::GPOW - 1;
-  int64_t rem = n - 2;
   while (rem >= ((int64_t)1 << top)) {
     if ((st = batch_launch(p, sg, BODY + top)) != GP_OK) return st;
     rem -= (int64_t)1 << top;
@@ -1948,7 +1923,7 @@ gp_status gp_step_n_batch(gp_plan_t* p, void* const* psis, int64_t nsteps) {
   for (int j = top - 1; j >= 0; --j)
     if (rem & ((int64_t)1 << j))
       if ((st = batch_launch(p, sg, BODY + j)) != GP_OK) return st;
-  return batch_launch(p, sg, (n - 1) % 2 ? 3 : 2);
+  return batch_launch(p, sg, n % 2 ? 2 : 1);
 }
 
 gp_status gp_energies_batch(gp_plan_t* p, void* const* psis, void* work, double* out) {
@@ -2112,13 +2087,13 @@ static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::funct
   return check_launch(p);
 }
 
-// time the selected schedule of an axis: microseconds of one in-place propagator pass plus one
-// turning pass (a plan runs both, and a schedule with many points a lane may do well in the
+// time the selected schedule of an axis: microseconds of one in-place propagator pass plus, for
+// single plans, one turning pass (they run both, and a schedule with many points a lane may do well in the
 // first and run out of registers in the second: 48^3 runs took 65 to 90 us a turning pass
 // with most schedules and 197 us with one that a propagator pass alone could choose).
 // `plain`: the fastest propagator pass of the axis so far; a schedule 15 % slower than that
 // is not timed further, which pays for the turning passes.
-static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, double* plain, double* us) {
+static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, bool batch, double* plain, double* us) {
   const double nl = p->d.beta * p->d.dt;
   gp_status st, inner = GP_OK;
   auto run = [&](StageMode mode, int n, bool warm, double* t) {
@@ -2138,7 +2113,7 @@ static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, doub
   *plain = std::min(*plain, t);
   // (in the swapping chain x never turns: 1024^3 complex64 has 3.6 ms propagator and 9.4 ms
   // turning passes with 4 pencils a tile, 4.0 and 6.3 with 8)
-  if (!(axis == 0 && swaps(p)) && (st = run(S_TURN, 1, true, &turn)) != GP_OK) return st;
+  if (!batch && !(axis == 0 && swaps(p)) && (st = run(S_TURN, 1, true, &turn)) != GP_OK) return st;
   *us = t + turn;
   return GP_OK;
 }
@@ -2156,9 +2131,9 @@ static void tune_note(const gp_plan_s* p, const char* what, int axis, int cand, 
 }
 
 // two steps of the running chain for `runs` states at once (ptrs: [x, y, z, plane][runs], or
-// null for the one state psi): every stage once plain or turning, as linear_chain
-// repeats them
-static gp_status chain_cycle(gp_plan_s* p, void* psi, const RunPtrs* ptrs, unsigned runs, double nl) {
+// null for the one state psi): every stage as linear_chain repeats them, or (batch) as the
+// ensemble graphs do
+static gp_status chain_cycle(gp_plan_s* p, void* psi, const RunPtrs* ptrs, unsigned runs, bool batch, double nl) {
   if (!ptrs && swaps(p)) {
     gp_status st = GP_OK;
     for (int k = 0; k < 2 && st == GP_OK; ++k)
@@ -2171,6 +2146,10 @@ static gp_status chain_cycle(gp_plan_s* p, void* psi, const RunPtrs* ptrs, unsig
                  p->stream);
   };
   for (int k = 0; k < 2; ++k) {
+    if (batch) {
+      for (int i = 0; i < q.n; ++i) put(k ? q.n - 1 - i : i, i == 0 ? S_NL : S_PLAIN);
+      continue;
+    }
     for (int i = 1; i + 1 < q.n; ++i) put(i, S_PLAIN);
     if (q.n > 0) put(k ? 0 : q.n - 1, q.n == 1 ? S_NL : S_TURN);
   }
@@ -2181,7 +2160,7 @@ static gp_status chain_cycle(gp_plan_s* p, void* psi, const RunPtrs* ptrs, unsig
 // and launched for `runs` copies of the scratch state at once (the ensemble launches a
 // size group together, which changes how well each option fills the GPU; the copies
 // all alias `scratch`, whose contents are undefined afterwards)
-static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, int* choice) {
+static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, bool batch, int* choice) {
   gp_status st;
   *choice = 0;
   if (!p->plane.e || p->ax[0].n == 1) return GP_OK;
@@ -2204,7 +2183,7 @@ static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, int* c
   for (int plane = 0; plane < 2; ++plane) {
     p->plane.on = plane == 1;
     st = time_calls(p, reps, &t[plane], [&] {
-      if (inner == GP_OK) inner = chain_cycle(p, scratch, p->d_tune_ptrs, (unsigned)runs, nl);
+      if (inner == GP_OK) inner = chain_cycle(p, scratch, p->d_tune_ptrs, (unsigned)runs, batch, nl);
     });
     p->plane.on = was;
     if (st != GP_OK) return st;
@@ -2232,7 +2211,7 @@ static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {
     double us = 0;
     gp_status inner = GP_OK;
     if ((st = time_calls(p, reps, &us, [&] {
-           if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, nl);
+           if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, false, nl);
          })) != GP_OK)
       return st;
     if (inner != GP_OK) return inner;
@@ -2261,7 +2240,7 @@ static gp_status tune_rot(gp_plan_s* p, void* scratch, int reps, int* choice) {
       double us = 0;
       if (v == 0) {
         if ((st = time_calls(p, (reps + 1) / 2, &us, [&] {       // two steps
-               if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, nl);
+               if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, false, nl);
              })) != GP_OK)
           return st;
         us *= 0.5;
@@ -2293,7 +2272,7 @@ static gp_status tune_rot(gp_plan_s* p, void* scratch, int reps, int* choice) {
 }
 
 static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::string, int>& cache,
-                           const std::string& arch, int chosen[5], int runs) {
+                           const std::string& arch, int chosen[5], int runs, bool batch) {
   gp_status st;
   for (int a = 0; a < 3; ++a) {
     chosen[a] = 0;
@@ -2312,7 +2291,7 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
       if (!find_entry(p->ax[a].n, p->prec, v)) continue;
       if ((st = gp_select_variant(p, a, v)) != GP_OK) return st;
       double us = 0;
-      if ((st = time_axis(p, a, scratch, reps, &plain, &us)) != GP_OK) return st;
+      if ((st = time_axis(p, a, scratch, reps, batch, &plain, &us)) != GP_OK) return st;
       if (us < 1e299) tune_note(p, "schedule", a, v, us);
       if (us < TUNE_TIE * best) { best = us; bestv = v; }
     }
@@ -2329,14 +2308,14 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
     if (it != cache.end() && (it->second == 0 || it->second == 1)) {
       chosen[3] = it->second;
     } else {
-      if ((st = tune_xy(p, scratch, reps, runs, &chosen[3])) != GP_OK) return st;
+      if ((st = tune_xy(p, scratch, reps, runs, batch, &chosen[3])) != GP_OK) return st;
       cache[key] = chosen[3];
     }
     if ((st = gp_select_variant(p, 3, chosen[3])) != GP_OK) return st;
   }
   // single plans with separate passes: the axis that carries the nonlinear prologue
   chosen[4] = first_real_axis(p);
-  if (runs == 1 && !p->plane.on && chosen[4] >= 0) {
+  if (!batch && !p->plane.on && chosen[4] >= 0) {
     const std::string key = tune_key(arch, p, 4);
     auto it = cache.find(key);
     if (it != cache.end() && it->second >= 0 && it->second <= 2 && p->ax[it->second].n > 1) {
@@ -2349,7 +2328,7 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
   }
   // single cubic plans with separate passes: fixed-layout or layout-rotating steps
   const int n0 = p->d.n[0];
-  if (runs == 1 && !p->plane.on && p->d.n[1] == n0 && p->d.n[2] == n0 && find_rot(n0, p->prec)) {
+  if (!batch && !p->plane.on && p->d.n[1] == n0 && p->d.n[2] == n0 && find_rot(n0, p->prec)) {
     const std::string key = tune_key(arch, p, 5);
     int c = 0;
     auto it = cache.find(key);
@@ -2374,12 +2353,12 @@ gp_status gp_autotune(gp_plan_t* p, void* scratch, int32_t reps, const char* cac
   const std::string arch = arch_name();
   if (!p->is_batch) {
     int chosen[5];
-    if ((st = tune_plan(p, scratch, reps, cache, arch, chosen, 1)) != GP_OK) return st;
+    if ((st = tune_plan(p, scratch, reps, cache, arch, chosen, 1, false)) != GP_OK) return st;
   } else {
     for (auto& g : p->groups) {
       gp_plan_s* r0 = p->runs[g.members[0]];
       int chosen[5];
-      if ((st = tune_plan(r0, scratch, reps, cache, arch, chosen, (int)g.members.size())) != GP_OK) return st;
+      if ((st = tune_plan(r0, scratch, reps, cache, arch, chosen, (int)g.members.size(), true)) != GP_OK) return st;
       for (size_t i = 1; i < g.members.size(); ++i)
         for (int a = 0; a < 4; ++a) {
           if (a == 3 && !p->runs[g.members[i]]->plane.e) continue;

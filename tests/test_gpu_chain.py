@@ -38,3 +38,27 @@ def test_step_is_bitwise_its_substeps(shape, prec, coef):
         plan.substep_linear(b, axis, 0.005)
     assert _same(a, b)
     plan.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+def test_ensemble_run_is_bitwise_a_single_plan(prec):
+    """Ensemble graphs (three size groups; even and odd counts, backward) against single plans
+    with separate passes."""
+    import paper_2003_03590_amd as gp
+    runs = [dict(n=48, alpha=0.2, beta=3.0, dt=0.01), dict(n=96, alpha=0.1, beta=20.0, dt=1e-3),
+            dict(n=48, alpha=0.3, beta=2.0, dt=0.01), dict(n=24, alpha=0.3, beta=50.0, dt=0.01)]
+    bp = gp.BatchPlan(runs, prec)
+    states = [_state((r["n"],) * 3, prec, 60 + i) for i, r in enumerate(runs)]
+    refs = [s.clone() for s in states]
+    plans = [gp.Plan(r["n"], r["alpha"], r["beta"], r["dt"], prec) for r in runs]
+    for p in plans:
+        p.select_variant(3, 0)
+    for n in (1, 2, 3, 8, -6):
+        bp.step_n(states, n)
+        for p, r in zip(plans, refs):
+            p.step_n(r, n)
+        torch.cuda.synchronize()
+        assert all(_same(s, r) for s, r in zip(states, refs)), n
+    for p in plans:
+        p.close()
+    bp.close()
