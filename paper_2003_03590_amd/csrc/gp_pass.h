@@ -432,10 +432,10 @@ __device__ __forceinline__ cplx<Real> nl_adjoint(cplx<Real> lam, cplx<Real> phi,
   return mk(fmadd(f, phi.x, r.x), fmadd(f, phi.y, r.y));
 }
 
-// The rotations of all points a lane holds.  One branch for the lane: the angle
-// beta (|v|^2 - 1) dt stays within the short series in every run of the method, and that
-// path is straight code for all points.  Otherwise the points take the general routine
-// one after another in a rolled loop that turns the register array by one place.
+// The rotations of all points a lane holds.  One branch for the lane: within the short
+// series (kSmallAngle, which covers the time steps of the method's workloads) straight code
+// for all points.  A lane with a larger angle takes the general routine point after point
+// in a rolled loop that turns the register array by one place, and its wavefront both paths.
 // (Unrolled with the general routine at every point, its code was 35 KB of a 43 KB
 // kernel at 256 points complex128, 45 of 65 KB at 1024 points complex64, beside a
 // 64 KB instruction cache that two compute units share: the turning pass took 13.7 ms

@@ -2195,7 +2195,7 @@ static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, bool b
 }
 
 // time the running chain with the first rotation on each real axis in turn (state:
-// psi = 1, the small-angle rotation of every real run); keep the fastest.  The carrier
+// psi = 1, whose rotation is the short series); keep the fastest.  The carrier
 // decides which axis lies between the turning ones: y for x, x for y, and x again for z,
 // which is therefore not timed on its own
 static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {

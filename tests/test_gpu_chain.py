@@ -1,6 +1,7 @@
 """How the passes of a step are cut does not change a state: the arithmetic of a sub-step is
 written out (which products are fused), so the running chain, single sub-steps and the
 ensemble's graphs give the same bits when they take the axes in the same order."""
+import numpy as np
 import pytest
 
 import gp_inputs as I
@@ -62,3 +63,25 @@ def test_ensemble_run_is_bitwise_a_single_plan(prec):
     for p in plans:
         p.close()
     bp.close()
+
+
+@pytest.mark.parametrize("lo,hi", [(0.0, 0.0625), (0.0625, 0.125), (0.1249, 0.1251), (0.125, 0.25)])
+def test_rotation_across_the_border_of_the_short_series(lo, hi):
+    """exp(-i beta (|psi|^2 - 1) dt) psi at angles around 1/16 and 1/8, both signs, beta dt = 1, in
+    complex64, where FP64 is an exact reference.  A point is rounded once per component and its angle by |psi|^2 times a few ulp: 8 ulp.  The
+    norm's relative change averages to sqrt(2) ulp / sqrt(points) = 1.7e-10 where
+    a truncated series would leave its own error at every point: 6 of those."""
+    import paper_2003_03590_amd as gp
+    n = 64
+    rng = np.random.default_rng(7)
+    a = rng.uniform(lo, hi, (n, n, n)) * rng.choice([-1.0, 1.0], (n, n, n))
+    psi0 = np.sqrt(1.0 - a) * np.exp(1j * rng.uniform(0.0, 2.0 * np.pi, (n, n, n)))
+    plan = gp.Plan(n, 0.3, 100.0, 0.01, "c64")
+    x = torch.from_numpy(psi0).to(DEV).to(plan.dtype).contiguous()
+    x0 = x.cpu().numpy().astype(np.complex128)
+    got = plan.substep_nonlinear(x, 0.01).cpu().numpy().astype(np.complex128)
+    ref = x0 * np.exp(-1j * (np.abs(x0) ** 2 - 1.0))
+    ulp = 2.0 ** -24
+    assert np.abs(got - ref).max() < 8 * ulp
+    assert abs(np.mean((np.abs(got) / np.abs(x0)) ** 2 - 1.0)) < 6 * np.sqrt(2.0) * ulp / n ** 1.5
+    plan.close()
