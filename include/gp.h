@@ -316,8 +316,10 @@ GP_API const char* gp_schedule_name(const gp_plan_t* p, int32_t axis);
  * that comes first and carries the first nonlinear rotations (variant 0, 1, 2 = x, y,
  * z; the linear sub-steps commute, so any order is the same split step): the
  * rotations lie in the passes of that axis and of the last of the others in x, y, z
- * order, in turn; default: the first axis of length > 1 (grids with ny = nz beyond the
- * last-level cache: y).  axis 5
+ * order, in turn; default: the first axis of length > 1, or y where the turning passes
+ * along x are the slower ones (and on grids with ny = nz beyond the last-level cache).
+ * Where turning passes are slower than the passes they replace (complex128 axes of 384 and
+ * 768 points at both ends) each sub-step is a pass of its own, with the same bits.  axis 5
  * (single cubic plans) selects the form of the linear steps of gp_step_n: variant
  * 0 (default) the fixed layout, every pass in place; variant v = 1..R (R compiled
  * rotating schedules for the length) the v-th rotating schedule: layout-rotating
@@ -339,12 +341,12 @@ GP_API gp_status gp_select_variant(gp_plan_t* p, int32_t axis, int32_t variant);
  * events, and keep the fastest (timings within 1 % count as ties, resolved to the
  * lower variant index, so repeated tunings agree); then the xy choice (axis 3), timed with as many
  * runs per launch as the size group holds; then, for single plans with separate
- * passes, the nonlinear carrier (axis 4), timed as whole linear steps, and for
- * cubic grids with a rotating schedule the layout form (axis 5), timed as whole
+ * passes, the nonlinear carrier (axis 4) with turning passes and without, timed as whole
+ * steps, and for cubic grids with a rotating schedule the layout form (axis 5), timed as whole
  * linear steps (the rotating form's workspace is released when it loses).  cache_path
  * (may be NULL): a JSON file of
- * earlier choices keyed by GPU architecture, precision, grid shape and axis;
- * cached choices are applied without timing and new ones are added.
+ * earlier choices keyed by GPU architecture, precision, grid shape, the kind of plan and
+ * axis (entries of files from before the turning passes are left alone); cached choices are applied without timing and new ones are added.
  * Synchronizes.  A batch plan re-records its graph on the next step call. */
 GP_API gp_status gp_autotune(gp_plan_t* p, void* scratch, int32_t reps, const char* cache_path);
 

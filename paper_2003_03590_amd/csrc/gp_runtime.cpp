@@ -148,6 +148,11 @@ struct Axis {
 
 using namespace gpk;
 
+// The running chain of gp_step_n in the fixed layout: passes that turn (two sub-steps and the
+// rotation between them), or every sub-step a pass of its own with the rotation in front
+// of the first (plain).  Both take the axes in alternating order and give the same bits.
+enum { FORM_RULE = -1, FORM_TURN = 0, FORM_PLAIN = 1 };
+
 struct gp_plan_s {
   gp_desc d{};
   hipStream_t stream = nullptr;
@@ -174,7 +179,8 @@ struct gp_plan_s {
   bool own_stream = false;         // stream created by the plan (batch plans on the null stream)
   std::string sched_name[6];       // x, y, z axis schedules; [3]: the xy-plane choice; [4]: the nonlinear
                                    // carrier; [5]: fixed-layout or layout-rotating linear steps
-  int nl_axis = -1;                // axis pass that carries the nonlinear prologue (-1: first real axis)
+  int nl_axis = -1;                // axis pass that carries the first rotation (-1: default_carrier)
+  int form = FORM_RULE;            // form of the running chain, fixed layout (chain_form)
   // xy-plane pass (x and y sub-steps fused; needs nx == ny with a compiled plane schedule)
   struct Plane {
     const PlaneEntry* e = nullptr;
@@ -534,7 +540,6 @@ gp_status usable_single(const gp_plan_s* p) {
 }
 
 // ----------------------------------------------------------------- pass launch
-constexpr size_t kLastLevelCache = (size_t)256 << 20;
 
 gp_status pass(gp_plan_s* p, int a, int var, const void* in, void* out, const void* mult, double nl_coef = 0.0,
                const void* aux = nullptr, double scale = 1.0, double* kin = nullptr, unsigned fields = 1) {
@@ -561,6 +566,43 @@ int first_real_axis(const gp_plan_s* p) {
   return -1;
 }
 
+// Which of a chain's end stages turn well.  A turning pass holds its points through two
+// propagators; complex128 schedules with three stages and 24 points a lane (384, 768) keep
+// 320 registers for it, one wavefront a SIMD, and take 2.2 to 2.8 times a propagator pass
+// where two are what it replaces.  Others take 1.3 (256) to 1.85 (96, 192).
+int lane_points(const Axis& A) { return A.e ? A.n / A.e->T : 0; }
+bool turns_badly(const gp_plan_s* p, int id) {
+  return id < 3 && p->prec == P_C128 && p->ax[id].n > 1 && p->ax[id].e->NS == 3 && lane_points(p->ax[id]) == 24;
+}
+bool turns_well(const gp_plan_s* p, int id) {
+  return id >= 3 || (p->ax[id].n > 1 && p->ax[id].e->NS <= 2 && lane_points(p->ax[id]) <= 16);
+}
+// Whether a chain between these ends turns.  Complex128, us a step turning and plain: 384^3
+// 1826 and 1519, 384x384x192 758 and 721, 512x384x384 1923 and 1872, 384x384x1 24.4 and 20.4;
+// with one such end and a good one 256x512x384 1157 and 1278, 64x32x384 28.4 and 29.7.
+bool ends_turn(const gp_plan_s* p, int a, int b) {
+  return !(turns_badly(p, a) && !turns_well(p, b)) && !(turns_badly(p, b) && !turns_well(p, a));
+}
+
+// The axis that comes first where none was selected.  z is always an end, so x or y lies in
+// the middle: x where it turns badly (complex128 384x192x96: 158 us a step against 181;
+// 384x128x128 115 and 138; 768x768x64, where y does too, 905 and 1019) or, in complex64, has 24 points or more a lane in two
+// stages, whose turning pass along x takes over twice a propagator pass (192^3 83 us and 95,
+// 1024x256x128 315 and 367, 512x384x256 595 and 614; shorter axes the other way, 96x48x24 17.7
+// and 17.0); y otherwise.  (Beyond the cache with ny = nz: swaps.)
+constexpr size_t kLastLevelCache = (size_t)256 << 20;
+bool swap_shape(const gp_plan_s* p) {
+  return (size_t)p->ntot * p->S > kLastLevelCache && p->ax[1].n > 1 && p->ax[2].n == p->ax[1].n;
+}
+int default_carrier(const gp_plan_s* p) {
+  const Axis& X = p->ax[0];
+  if (X.n == 1 || p->ax[1].n == 1 || p->ax[2].n == 1) return first_real_axis(p);
+  const bool y_first = turns_badly(p, 0) ||
+                       (p->prec == P_C64 && X.n >= 192 && X.e->NS == 2 && lane_points(X) >= 24 && !swap_shape(p));
+  if (ends_turn(p, y_first ? 1 : 0, 2)) return y_first ? 1 : 0;
+  return !y_first || !ends_turn(p, 0, 2) ? 1 : 0;
+}
+
 // The sub-steps that make up L(tau): axis passes (0 x, 1 y, 2 z) or the xy-plane pass.
 // They commute; the axis that carries the first rotation comes first, the others in
 // x, y, z order.
@@ -574,8 +616,7 @@ Stages stages_of(const gp_plan_s* p) {
     if (p->ax[2].n > 1) s.id[s.n++] = 2;
     return s;
   }
-  const int c = first_real_axis(p);
-  const int carrier = (p->nl_axis >= 0 && p->ax[p->nl_axis].n > 1) ? p->nl_axis : c;
+  const int carrier = (p->nl_axis >= 0 && p->ax[p->nl_axis].n > 1) ? p->nl_axis : default_carrier(p);
   for (int a : {carrier, carrier == 0 ? 1 : 0, carrier == 2 ? 1 : 2})
     if (a >= 0 && p->ax[a].n > 1) s.id[s.n++] = a;
   return s;
@@ -640,11 +681,20 @@ gp_status stage_swap(gp_plan_s* p, void* psi, int tau) {
 // 2.24, 768x256x256 complex64 0.84 and 0.76, 384^3 complex64 1.07 and 0.99.  In the cache
 // the z rows cost nothing extra and the scattered pencils do: 256^3 complex128 0.203 and
 // 0.205, 128^3 complex64 0.032 and 0.037.  Not where the caller took x as the carrier
-// (the x passes then turn).
+// (the x passes then turn), where y turns badly, or with 24 complex64 points a lane in two
+// stages (192x512x512 706 us a step swapping and 664 with x turning, 96x1024x1024 1348 and 1238).
 bool swaps(const gp_plan_s* p) {
-  const int n = p->ax[1].n;
-  return (size_t)p->ntot * p->S > kLastLevelCache && !p->plane.on && p->nl_axis != 0 && p->ax[0].n > 1 && n > 1 &&
-         n % 2 == 0 && p->ax[2].n == n && p->ax[0].e->fn[CONTIG][V_PROP_SWAP];
+  if (!swap_shape(p) || p->plane.on || p->nl_axis == 0 || p->form == FORM_PLAIN) return false;
+  const Axis& X = p->ax[0];
+  if (X.n == 1 || p->ax[1].n % 2 != 0 || !X.e->fn[CONTIG][V_PROP_SWAP]) return false;
+  return p->form == FORM_TURN ||
+         !(turns_badly(p, 1) || (p->prec == P_C64 && X.e->NS == 2 && lane_points(X) == 24));
+}
+
+// whether the chain of these stages turns: as timed by the autotuner, or by the rule
+bool turns(const gp_plan_s* p, const Stages& q) {
+  if (q.n < 2) return false;
+  return p->form != FORM_RULE ? p->form == FORM_TURN : ends_turn(p, q.id[0], q.id[q.n - 1]);
 }
 
 // linear_chain with the x passes swapping y and z in the layout: the other stage is always
@@ -666,7 +716,8 @@ gp_status swap_chain(gp_plan_s* p, void* psi, int64_t n, double nl, const std::f
 
 // L(t_0) N L(t_1) N ... N L(t_n) on psi in place, t_k = tau_of(k).  With two stages or more
 // the linear steps take them in alternating order, so that each rotation lies between
-// two sub-steps of one stage and the three run as one turning pass.
+// two sub-steps of one stage and the three run as one turning pass (or as two passes, the
+// second with the rotation in front, where that is faster).
 gp_status linear_chain(gp_plan_s* p, void* psi, int64_t n, double nl, const std::function<int(int64_t)>& tau_of) {
   if (swaps(p)) return swap_chain(p, psi, n, nl, tau_of);
   const Stages q = stages_of(p);
@@ -678,12 +729,16 @@ gp_status linear_chain(gp_plan_s* p, void* psi, int64_t n, double nl, const std:
     }
     return GP_OK;
   }
+  if (!turns(p, q)) {
+    for (int64_t k = 0; k <= n; ++k)
+      for (int i = 0; i < q.n; ++i) {
+        const int id = q.id[k % 2 ? q.n - 1 - i : i];
+        if ((st = stage(p, id, k > 0 && i == 0 ? S_NL : S_PLAIN, psi, tau_of(k), 0, nl)) != GP_OK) return st;
+      }
+    return GP_OK;
+  }
   if ((st = stage(p, q.id[0], S_PLAIN, psi, tau_of(0))) != GP_OK) return st;
   for (int64_t k = 0; k <= n; ++k) {
-    if (q.n == 1) {
-      if (k < n && (st = stage(p, q.id[0], S_NL, psi, tau_of(k + 1), 0, nl)) != GP_OK) return st;
-      continue;
-    }
     for (int i = 1; i + 1 < q.n; ++i)
       if ((st = stage(p, q.id[i], S_PLAIN, psi, tau_of(k))) != GP_OK) return st;
     const int last = k % 2 ? q.id[0] : q.id[q.n - 1];
@@ -1100,6 +1155,7 @@ static gp_status select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
     if (variant < 0 || variant > 2) return fail(GP_ERR_ARG, "nonlinear carrier %d (0, 1, 2 = x, y, z)", variant);
     if (p->ax[variant].n == 1) return fail(GP_ERR_ARG, "nonlinear carrier: axis %d has length 1", variant);
     p->nl_axis = variant;
+    p->form = FORM_RULE;
     p->sched_name[4] = std::string("nl: ") + "xyz"[variant] + " pass";
     return GP_OK;
   }
@@ -1659,8 +1715,11 @@ gp_status gp_adjoint_step_n(gp_plan_t* p, const void* psi_seg_start, void* lam, 
     A.e->fn[A.kind][var](g, A.blocks, 1, p->stream);
     return check_launch(p);
   };
+  // (y first where the step takes it first: V_TURN_ADJ needs more registers still, and
+  // 768x24x768 took 4.58 ms for five steps and back with x and z as ends)
   int q[3], m = 0;
-  for (int a = 0; a < 3; ++a) if (p->ax[a].n > 1) q[m++] = a;
+  const int first = default_carrier(p);
+  for (int a : {first, first == 0 ? 1 : 0, first == 2 ? 1 : 2}) if (a >= 0 && p->ax[a].n > 1) q[m++] = a;
   // forward recompute: phi_0 = L(h) psi_0, phi_{n+1} = L(dt) N(phi_n), stored in the tape.
   // The axes alternate as in the step itself, so the pass that completes phi_n stores it
   // and goes on with the rotation and the first sub-step of the next state.
@@ -2061,10 +2120,12 @@ static std::string arch_name() {
   return c == std::string::npos ? a : a.substr(0, c);
 }
 
-static std::string tune_key(const std::string& arch, const gp_plan_s* p, int axis) {
+// The tag names what the choices were timed for: t2 the chains of single plans (turning or
+// plain), t2b the ensemble's.  Entries without one were timed for three passes a step.
+static std::string tune_key(const std::string& arch, const gp_plan_s* p, int axis, bool batch) {
   char b[160];
-  snprintf(b, sizeof b, "%s/%s/%dx%dx%d/a%d", arch.c_str(), p->prec == P_C128 ? "c128" : "c64", p->d.n[0], p->d.n[1],
-           p->d.n[2], axis);
+  snprintf(b, sizeof b, "%s/%s/%dx%dx%d/%s/a%d", arch.c_str(), p->prec == P_C128 ? "c128" : "c64", p->d.n[0], p->d.n[1],
+           p->d.n[2], batch ? "t2b" : "t2", axis);
   return b;
 }
 
@@ -2086,6 +2147,8 @@ static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::funct
   *us = 1e3 * ms / std::max(1, reps);
   return check_launch(p);
 }
+
+constexpr size_t kSmallState = (size_t)16 << 20;
 
 // time the selected schedule of an axis: microseconds of one in-place propagator pass plus, for
 // single plans, one turning pass (they run both, and a schedule with many points a lane may do well in the
@@ -2146,12 +2209,12 @@ static gp_status chain_cycle(gp_plan_s* p, void* psi, const RunPtrs* ptrs, unsig
                  p->stream);
   };
   for (int k = 0; k < 2; ++k) {
-    if (batch) {
+    if (batch || !turns(p, q)) {
       for (int i = 0; i < q.n; ++i) put(k ? q.n - 1 - i : i, i == 0 ? S_NL : S_PLAIN);
       continue;
     }
     for (int i = 1; i + 1 < q.n; ++i) put(i, S_PLAIN);
-    if (q.n > 0) put(k ? 0 : q.n - 1, q.n == 1 ? S_NL : S_TURN);
+    put(k ? 0 : q.n - 1, S_TURN);
   }
   return check_launch(p);
 }
@@ -2194,29 +2257,48 @@ static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, bool b
   return GP_OK;
 }
 
-// time the running chain with the first rotation on each real axis in turn (state:
-// psi = 1, whose rotation is the short series); keep the fastest.  The carrier
-// decides which axis lies between the turning ones: y for x, x for y, and x again for z,
-// which is therefore not timed on its own
+// time the running chain in both forms with the first rotation on x and on y (state: psi = 1,
+// whose rotation is the short series); keep the fastest, as carrier + 3 form.  The carrier
+// decides which axis lies in the middle: y for x, x for y, and x again for z, which is
+// therefore not timed on its own.
+// Each candidate is timed twice at least (small states: half of `reps` cycles each time, so
+// that the events do not count; larger ones: one), those within 5 % of the best once more.
+// The form that the plan would take by itself comes first, so that it stays in a tie.
 static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {
-  gp_status st;
+  gp_status st, inner = GP_OK;
+  *choice = first_real_axis(p);
+  if (stages_of(p).n < 2) return GP_OK;
   launch_fill(p->prec, scratch, p->ntot, 1.0, 0.0, p->stream);
   if ((st = check_launch(p)) != GP_OK) return st;
   const double nl = p->d.beta * p->d.dt;
+  struct Cand { int v; double us; };
+  std::vector<Cand> cand;
+  const Stages q = stages_of(p);
+  const int own = swaps(p) ? 1 + 3 * FORM_TURN : q.id[0] + 3 * (turns(p, q) ? FORM_TURN : FORM_PLAIN);
+  for (int form : {FORM_TURN, FORM_PLAIN})
+    for (int a = 0; a < 2; ++a)
+      if (p->ax[a].n > 1) cand.insert(a + 3 * form == own ? cand.begin() : cand.end(), {a + 3 * form, 1e300});
+  const bool small = (size_t)p->ntot * p->S < kSmallState;
+  for (int round = 0; round < 3; ++round) {
+    double best = 1e300;
+    for (const auto& c : cand) best = std::min(best, c.us);
+    for (auto& c : cand) {
+      if (round == 2 && c.us > 1.05 * best) continue;
+      p->nl_axis = c.v % 3;
+      p->form = c.v / 3;
+      double us = 0;
+      if ((st = time_calls(p, small ? (reps + 1) / 2 : 1, &us, [&] {
+             if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, false, nl);
+           }, small && round == 0)) != GP_OK)
+        return st;
+      if (inner != GP_OK) return inner;
+      c.us = std::min(c.us, us);
+    }
+  }
   double best = 1e300;
-  *choice = first_real_axis(p);
-  for (int a = 0; a < 2; ++a) {
-    if (p->ax[a].n == 1) continue;
-    p->nl_axis = a;
-    double us = 0;
-    gp_status inner = GP_OK;
-    if ((st = time_calls(p, reps, &us, [&] {
-           if (inner == GP_OK) inner = chain_cycle(p, scratch, nullptr, 1, false, nl);
-         })) != GP_OK)
-      return st;
-    if (inner != GP_OK) return inner;
-    tune_note(p, "nonlinear on", a, a, us);
-    if (us < TUNE_TIE * best) { best = us; *choice = a; }
+  for (const auto& c : cand) {
+    tune_note(p, c.v < 3 ? "turning, first rotation on" : "plain, first rotation on", c.v % 3, c.v, c.us);
+    if (c.us < TUNE_TIE * best) { best = c.us; *choice = c.v; }
   }
   return GP_OK;
 }
@@ -2274,10 +2356,13 @@ static gp_status tune_rot(gp_plan_s* p, void* scratch, int reps, int* choice) {
 static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::string, int>& cache,
                            const std::string& arch, int chosen[5], int runs, bool batch) {
   gp_status st;
+  p->nl_axis = -1;               // an earlier choice does not count in what follows
+  p->form = FORM_RULE;
+  p->sched_name[4] = "nl: first axis";
   for (int a = 0; a < 3; ++a) {
     chosen[a] = 0;
     if (p->ax[a].n == 1) continue;
-    const std::string key = tune_key(arch, p, a);
+    const std::string key = tune_key(arch, p, a, batch);
     auto it = cache.find(key);
     if (it != cache.end() && find_entry(p->ax[a].n, p->prec, it->second)) {
       chosen[a] = it->second;
@@ -2303,7 +2388,7 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
   if (p->plane.e) {
     char b[32];
     snprintf(b, sizeof b, "/r%d", runs);
-    const std::string key = tune_key(arch, p, 3) + b;
+    const std::string key = tune_key(arch, p, 3, batch) + b;
     auto it = cache.find(key);
     if (it != cache.end() && (it->second == 0 || it->second == 1)) {
       chosen[3] = it->second;
@@ -2316,20 +2401,22 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
   // single plans with separate passes: the axis that carries the nonlinear prologue
   chosen[4] = first_real_axis(p);
   if (!batch && !p->plane.on && chosen[4] >= 0) {
-    const std::string key = tune_key(arch, p, 4);
+    const std::string key = tune_key(arch, p, 4, batch);
     auto it = cache.find(key);
-    if (it != cache.end() && it->second >= 0 && it->second <= 2 && p->ax[it->second].n > 1) {
+    if (it != cache.end() && it->second >= 0 && it->second < 6 && p->ax[it->second % 3].n > 1) {
       chosen[4] = it->second;
     } else {
       if ((st = tune_nl(p, scratch, reps, &chosen[4])) != GP_OK) return st;
       cache[key] = chosen[4];
     }
-    if ((st = gp_select_variant(p, 4, chosen[4])) != GP_OK) return st;
+    if ((st = gp_select_variant(p, 4, chosen[4] % 3)) != GP_OK) return st;
+    p->form = chosen[4] / 3;
+    if (p->form == FORM_PLAIN) p->sched_name[4] += ", plain";
   }
   // single cubic plans with separate passes: fixed-layout or layout-rotating steps
   const int n0 = p->d.n[0];
   if (!batch && !p->plane.on && p->d.n[1] == n0 && p->d.n[2] == n0 && find_rot(n0, p->prec)) {
-    const std::string key = tune_key(arch, p, 5);
+    const std::string key = tune_key(arch, p, 5, batch);
     int c = 0;
     auto it = cache.find(key);
     const int nrot = [&] { int k = 0; while (find_rot(n0, p->prec, k)) ++k; return k; }();

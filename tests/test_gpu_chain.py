@@ -20,24 +20,64 @@ def _same(a, b):
     return torch.equal(torch.view_as_real(a), torch.view_as_real(b))
 
 
-@pytest.mark.parametrize("coef", [0.04, 0.5], ids=["small", "mixed"])
-@pytest.mark.parametrize("prec", ["c128", "c64"])
-@pytest.mark.parametrize("shape", [(96, 48, 24), (24, 192, 2), (48, 16, 128), (384, 8, 6), (1, 64, 12)],
-                         ids=lambda s: "x".join(map(str, s)))
-def test_step_is_bitwise_its_substeps(shape, prec, coef):
-    """One step (x y z N z y x) against single sub-steps: the turning pass equals the two
-    passes and the rotation that it replaces."""
+def _forced(shape, prec, coef, choice, path):
+    """A plan whose chain was chosen by a tuning file: choice = carrier + 3 for the plain form."""
+    import json
+
     import paper_2003_03590_amd as gp
     plan = gp.Plan(shape, 0.3, coef / 0.01, 0.01, prec)
+    plan.select_variant(4, choice % 3)           # ends a plane pass that is on by default
+    key = "{}/{}/{}x{}x{}/t2/a".format(torch.cuda.get_device_properties(0).gcnArchName.split(":")[0], prec, *shape)
+    path.write_text(json.dumps({key + "0": 0, key + "1": 0, key + "2": 0, key + "3/r1": 0, key + "4": choice, key + "5": 0}))
+    plan.autotune(reps=1, cache=str(path))
+    assert plan.schedule(4) == "nl: " + "xyz"[choice % 3] + " pass" + (", plain" if choice > 2 else "")
+    return plan
+
+
+@pytest.mark.parametrize("coef", [0.04, 0.5], ids=["small", "mixed"])
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("shape", [(96, 48, 24), (24, 192, 2), (48, 16, 128), (384, 8, 6), (6, 384, 768), (768, 12, 384),
+                                   (1, 64, 12)], ids=lambda s: "x".join(map(str, s)))
+def test_steps_are_bitwise_their_substeps(shape, prec, coef, tmp_path):
+    """The chain x y z N z y x N ... against single sub-steps: a turning pass equals the two
+    passes and the rotation that it replaces, and the plain form takes these.  Every carrier,
+    both forms, one to three steps; 384 and 768 points along each axis."""
     psi0 = _state(shape, prec, 51)
-    a = plan.step_n(psi0.clone(), 1)
-    b = psi0.clone()
-    for axis in (0, 1, 2):
-        plan.substep_linear(b, axis, 0.005)
-    plan.substep_nonlinear(b, 0.01)
-    for axis in (2, 1, 0):
-        plan.substep_linear(b, axis, 0.005)
-    assert _same(a, b)
+    for choice in range(6):
+        first = choice % 3
+        if shape[first] == 1:
+            continue
+        plan = _forced(shape, prec, coef, choice, tmp_path / "tune.json")
+        order = [first, 1 if first == 0 else 0, 1 if first == 2 else 2]
+        for n in (1, 2, 3):
+            a = plan.step_n(psi0.clone(), n)
+            b = psi0.clone()
+            for k in range(n + 1):
+                if k:
+                    plan.substep_nonlinear(b, 0.01)
+                for axis in (order[::-1] if k % 2 else order):
+                    plan.substep_linear(b, axis, 0.005 if k in (0, n) else 0.01)
+            assert _same(a, b), (choice, n)
+        plan.close()
+
+
+@pytest.mark.parametrize("shape,prec", [((384, 12, 6), "c128"), ((12, 384, 384), "c128"), ((192, 24, 384), "c128"),
+                                        ((384, 96, 24), "c128"), ((768, 384, 8), "c128"), ((384, 768, 1), "c128"),
+                                        ((1, 24, 384), "c128"), ((192, 8, 6), "c64"), ((1024, 6, 4), "c64"),
+                                        ((512, 12, 8), "c64"), ((384, 8, 6), "c64")],
+                         ids=lambda v: v if isinstance(v, str) else "x".join(map(str, v)))
+def test_default_chain_on_long_axes(shape, prec):
+    """Shapes at which the default takes another first axis or the plain form, against the
+    oracle's literal steps (round-off of three steps)."""
+    import paper_2003_03590_amd as gp
+    from oracle import gp as O
+    psi0 = I.random_field(shape[::-1], seed=35)
+    base = psi0.astype(np.complex64).astype(np.complex128) if prec == "c64" else psi0
+    plan = gp.Plan(shape, 0.3, 4.0, 0.01, prec)
+    for n in (3, -2):
+        got = plan.step_n(torch.from_numpy(psi0).to(DEV).to(plan.dtype).contiguous(), n).cpu().numpy()
+        ref = O.evolve(base, 0.3, 4.0, 0.01, n)
+        assert np.linalg.norm(got - ref) < (1e-12 if prec == "c128" else 5e-6) * np.linalg.norm(ref)
     plan.close()
 
 
@@ -84,4 +124,24 @@ def test_rotation_across_the_border_of_the_short_series(lo, hi):
     ulp = 2.0 ** -24
     assert np.abs(got - ref).max() < 8 * ulp
     assert abs(np.mean((np.abs(got) / np.abs(x0)) ** 2 - 1.0)) < 6 * np.sqrt(2.0) * ulp / n ** 1.5
+    plan.close()
+
+
+def test_tuning_file_of_three_passes_a_step_is_not_obeyed(tmp_path):
+    """Entries without the tag of the running chain were timed for another one: a file that holds
+    only such entries is timed again and keeps them."""
+    import json
+
+    import paper_2003_03590_amd as gp
+    arch = torch.cuda.get_device_properties(0).gcnArchName.split(":")[0]
+    old = {f"{arch}/c64/128x128x128/a{a}": v for a, v in enumerate((2, 2, 2))}
+    old[f"{arch}/c64/128x128x128/a4"] = 2
+    path = tmp_path / "tune.json"
+    path.write_text(json.dumps(old))
+    plan = gp.Plan(128, 0.3, 4.0, 0.01, "c64")
+    plan.autotune(reps=2, cache=str(path))
+    data = json.loads(path.read_text())
+    assert all(data[k] == v for k, v in old.items())
+    assert {k.split("/")[-1] for k in data if "/t2/" in k} >= {"a0", "a1", "a2", "a4"}
+    assert plan.schedule(4) != "nl: z pass"          # z is never timed as the first axis
     plan.close()
