@@ -2151,32 +2151,44 @@ static gp_status time_calls(gp_plan_s* p, int reps, double* us, const std::funct
 constexpr size_t kSmallState = (size_t)16 << 20;
 
 // time the selected schedule of an axis: microseconds of one in-place propagator pass plus, for
-// single plans, one turning pass (they run both, and a schedule with many points a lane may do well in the
-// first and run out of registers in the second: 48^3 runs took 65 to 90 us a turning pass
-// with most schedules and 197 us with one that a propagator pass alone could choose).
-// `plain`: the fastest propagator pass of the axis so far; a schedule 15 % slower than that
-// is not timed further, which pays for the turning passes.
+// single plans, one turning pass (they run both, and a schedule with many points a lane may do
+// well in the first and run out of registers in the second: 48^3 runs took 65 to 90 us a
+// turning pass with most schedules and 197 us with one that a propagator pass alone could
+// choose).  `plain`: the fastest propagator pass of the axis so far; a schedule 15 % slower
+// than that in the better of two samples is not timed further, which pays for the turning
+// passes.
 static gp_status time_axis(gp_plan_s* p, int axis, void* scratch, int reps, bool batch, double* plain, double* us) {
   const double nl = p->d.beta * p->d.dt;
   gp_status st, inner = GP_OK;
-  auto run = [&](StageMode mode, int n, bool warm, double* t) {
+  auto run = [&](StageMode mode, int n, double* t) {
     const gp_status e = time_calls(p, n, t, [&] {
       if (inner == GP_OK) inner = stage(p, axis, mode, scratch, TAU_DT, TAU_DT, nl);
-    }, warm);
+    }, false);
     return e != GP_OK ? e : inner;
+  };
+  // (launches of a few us: several a sample, so that the events do not count)
+  const bool small = (size_t)p->ntot * p->S < kSmallState;
+  const int each = small ? (reps + 1) / 2 : 1;
+  auto better_of_two = [&](StageMode mode, double* t) {
+    double a = 0, b = 0;
+    gp_status e = run(mode, each, &a);
+    if (e == GP_OK) e = run(mode, each, &b);
+    *t = std::min(a, b);
+    return e;
   };
   double t = 0, more = 0, turn = 0;
   *us = 1e300;
-  if ((st = run(S_PLAIN, 1, true, &t)) != GP_OK) return st;
+  if ((st = better_of_two(S_PLAIN, &t)) != GP_OK) return st;
   if (t > 1.15 * *plain) return GP_OK;
-  if (reps > 3) {
-    if ((st = run(S_PLAIN, reps - 3, false, &more)) != GP_OK) return st;
+  if (!small && reps > 3) {
+    if ((st = run(S_PLAIN, reps - 3, &more)) != GP_OK) return st;
     t = (t + (reps - 3) * more) / (reps - 2);
   }
   *plain = std::min(*plain, t);
-  // (in the swapping chain x never turns: 1024^3 complex64 has 3.6 ms propagator and 9.4 ms
-  // turning passes with 4 pencils a tile, 4.0 and 6.3 with 8)
-  if (!batch && !(axis == 0 && swaps(p)) && (st = run(S_TURN, 1, true, &turn)) != GP_OK) return st;
+  // (the swapping chain is what such a plan starts with, and x does not turn in it: 1024^3
+  // complex64 has 3.6 ms propagator and 9.4 ms turning passes with 4 pencils a tile, 4.0 and
+  // 6.3 with 8)
+  if (!batch && !(axis == 0 && swaps(p)) && (st = better_of_two(S_TURN, &turn)) != GP_OK) return st;
   *us = t + turn;
   return GP_OK;
 }
@@ -2261,8 +2273,8 @@ static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, bool b
 // whose rotation is the short series); keep the fastest, as carrier + 3 form.  The carrier
 // decides which axis lies in the middle: y for x, x for y, and x again for z, which is
 // therefore not timed on its own.
-// Each candidate is timed twice at least (small states: half of `reps` cycles each time, so
-// that the events do not count; larger ones: one), those within 5 % of the best once more.
+// Each candidate is timed twice (small states: half of `reps` cycles each time, so that the
+// events do not count; larger ones: one, and those within 5 % of the best once more).
 // The form that the plan would take by itself comes first, so that it stays in a tie.
 static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {
   gp_status st, inner = GP_OK;
@@ -2279,7 +2291,7 @@ static gp_status tune_nl(gp_plan_s* p, void* scratch, int reps, int* choice) {
     for (int a = 0; a < 2; ++a)
       if (p->ax[a].n > 1) cand.insert(a + 3 * form == own ? cand.begin() : cand.end(), {a + 3 * form, 1e300});
   const bool small = (size_t)p->ntot * p->S < kSmallState;
-  for (int round = 0; round < 3; ++round) {
+  for (int round = 0; round < (small ? 2 : 3); ++round) {
     double best = 1e300;
     for (const auto& c : cand) best = std::min(best, c.us);
     for (auto& c : cand) {
@@ -2359,6 +2371,7 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
   p->nl_axis = -1;               // an earlier choice does not count in what follows
   p->form = FORM_RULE;
   p->sched_name[4] = "nl: first axis";
+  bool filled = false;
   for (int a = 0; a < 3; ++a) {
     chosen[a] = 0;
     if (p->ax[a].n == 1) continue;
@@ -2366,13 +2379,19 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
     auto it = cache.find(key);
     if (it != cache.end() && find_entry(p->ax[a].n, p->prec, it->second)) {
       chosen[a] = it->second;
-      if ((st = gp_select_variant(p, a, it->second)) != GP_OK) return st;
+      if (p->ax[a].e->variant != it->second && (st = gp_select_variant(p, a, it->second)) != GP_OK) return st;
       continue;
     }
     const int nv = gp_variant_count(p->ax[a].n, p->prec);
     double best = 1e300, plain = 1e300;
     int bestv = 0;
-    for (int v = 0; v < nv; ++v) {
+    // psi = 1: the time of a turning pass depends on the angles
+    if (nv > 1 && !filled) {
+      launch_fill(p->prec, scratch, p->ntot, 1.0, 0.0, p->stream);
+      if ((st = check_launch(p)) != GP_OK) return st;
+      filled = true;
+    }
+    for (int v = 0; v < nv && nv > 1; ++v) {
       if (!find_entry(p->ax[a].n, p->prec, v)) continue;
       if ((st = gp_select_variant(p, a, v)) != GP_OK) return st;
       double us = 0;
@@ -2380,7 +2399,7 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
       if (us < 1e299) tune_note(p, "schedule", a, v, us);
       if (us < TUNE_TIE * best) { best = us; bestv = v; }
     }
-    if ((st = gp_select_variant(p, a, bestv)) != GP_OK) return st;
+    if (p->ax[a].e->variant != bestv && (st = gp_select_variant(p, a, bestv)) != GP_OK) return st;
     cache[key] = bestv;
     chosen[a] = bestv;
   }

@@ -145,3 +145,19 @@ def test_tuning_file_of_three_passes_a_step_is_not_obeyed(tmp_path):
     assert {k.split("/")[-1] for k in data if "/t2/" in k} >= {"a0", "a1", "a2", "a4"}
     assert plan.schedule(4) != "nl: z pass"          # z is never timed as the first axis
     plan.close()
+
+
+def test_tuning_starts_from_a_state_of_its_own():
+    """The time of a turning pass depends on the angles: what the caller's scratch state holds
+    does not count."""
+    import ctypes as C
+
+    import paper_2003_03590_amd as gp
+    plan = gp.Plan((128, 2, 2), 0.3, 4.0, 0.01, "c64")
+    scratch = torch.full(plan.shape, float("nan"), dtype=plan.dtype, device=DEV)
+    bp = gp.BatchPlan([dict(n=(128, 2, 2), alpha=0.3, beta=4.0, dt=0.01)], "c64")
+    assert gp.lib().gp_autotune(bp._h, C.c_void_p(scratch.data_ptr()), 2, None) == 0
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(torch.view_as_real(scratch)).all())
+    plan.close()
+    bp.close()
