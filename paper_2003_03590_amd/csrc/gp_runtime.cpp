@@ -386,7 +386,7 @@ PassEntry plane_as_entry(const PlaneEntry& pe) {
 // one alpha the x and y multipliers are the same table)
 gp_status build_plane_tables(gp_plan_s* p) {
   auto& P = p->plane;
-  if (P.tw) return GP_OK;
+  if (P.mult[NTAU - 1]) return GP_OK;
   const PassEntry e = plane_as_entry(*P.e);
   gp_status st;
   if ((st = upload_cplx(p, &P.tw, stage_twiddles(e))) != GP_OK) return st;
@@ -504,8 +504,10 @@ void plan_free(gp_plan_s* p) {
   delete p;
 }
 
-// the recorded step graphs of a batch plan are stale (kernels, tables or states changed)
+// the recorded step graphs of a batch plan are stale (kernels, tables or states changed);
+// a launch of one may still run
 void drop_graphs(gp_plan_s* p) {
+  (void)hipStreamSynchronize(p->stream);
   for (auto& row : p->gexec)
     for (auto& x : row)
       if (x) { (void)hipGraphExecDestroy(x); x = nullptr; }
@@ -1087,15 +1089,67 @@ int32_t gp_variant_count(int32_t n, int32_t prec) {
   return c;
 }
 
+// What the selections of a single plan change.  A selection that fails (no memory for its
+// tables) puts all of it back: half of it would leave null tables to the kernels.  Tables
+// stay allocated until the plan is destroyed, so the old ones are still there.
+struct Choices {
+  Axis ax[3];
+  std::string sched_name[6];
+  gp_plan_s::Plane plane;
+  gp_plan_s::Rot rot;
+  int nl_axis = -1, form = FORM_RULE;
+  double* kin_part = nullptr;
+};
+static Choices choices_of(const gp_plan_s* p) {
+  Choices c;
+  std::copy(p->ax, p->ax + 3, c.ax);
+  std::copy(p->sched_name, p->sched_name + 6, c.sched_name);
+  c.plane = p->plane;
+  c.rot = p->rot;
+  c.nl_axis = p->nl_axis;
+  c.form = p->form;
+  c.kin_part = p->kin_part;
+  return c;
+}
+static void put_back(gp_plan_s* p, const Choices& c) {
+  if (p->rot.work && p->rot.work != c.rot.work) {       // allocated since
+    (void)(p->stream ? hipStreamSynchronize(p->stream) : hipDeviceSynchronize());
+    (void)hipFree(p->rot.work);
+  }
+  for (int a = 0; a < 3; ++a)                           // one-off tables in another order
+    if (p->ax[a].e != c.ax[a].e)
+      for (auto it = p->substep_tables.begin(); it != p->substep_tables.end();)
+        it = it->first.first == a ? p->substep_tables.erase(it) : std::next(it);
+  std::copy(c.ax, c.ax + 3, p->ax);
+  std::copy(c.sched_name, c.sched_name + 6, p->sched_name);
+  p->plane = c.plane;
+  p->rot = c.rot;
+  p->nl_axis = c.nl_axis;
+  p->form = c.form;
+  p->kin_part = c.kin_part;
+}
+// the plan's own choices, or those of every run of a batch plan
+static std::vector<Choices> all_choices(const gp_plan_s* p) {
+  std::vector<Choices> v;
+  if (!p->is_batch) v.push_back(choices_of(p));
+  for (const auto* r : p->runs) v.push_back(choices_of(r));
+  return v;
+}
+static void put_all_back(gp_plan_s* p, const std::vector<Choices>& v) {
+  if (!p->is_batch) put_back(p, v[0]);
+  else
+    for (size_t i = 0; i < p->runs.size(); ++i) put_back(p->runs[i], v[i]);
+}
+
 static gp_status select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
   gp_status st = usable(p);
   if (st != GP_OK) return st;
   if (p->is_batch) {   // the xy choice for every run that has a plane schedule
     if (axis != 3) return fail(GP_ERR_STATE, "batch plan: axis schedules are chosen by gp_autotune");
+    drop_graphs(p);
     for (auto* r : p->runs)
       if (r->plane.e || variant == 0)
         if ((st = gp_select_variant(r, 3, variant)) != GP_OK) return st;
-    drop_graphs(p);
     return GP_OK;
   }
   if (axis == 3) {   // xy plane: 0 = separate x and y passes, 1 = one plane pass
@@ -1179,7 +1233,10 @@ static gp_status select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
 }
 
 gp_status gp_select_variant(gp_plan_t* p, int32_t axis, int32_t variant) {
+  if (!p) return fail(GP_ERR_ARG, "null plan");
+  const auto was = all_choices(p);
   const gp_status st = select_variant(p, axis, variant);
+  if (st != GP_OK) put_all_back(p, was);
   // a choice for the separate passes ends a plane pass that was not chosen
   if (st == GP_OK && axis != 3 && p->plane.by_default) plane_off(p);
   return st;
@@ -2242,6 +2299,7 @@ static gp_status tune_xy(gp_plan_s* p, void* scratch, int reps, int runs, bool b
   if ((st = build_plane_tables(p)) != GP_OK) return st;
   const size_t need = 4 * (size_t)runs;
   if (p->n_tune_ptrs < need) {
+    p->n_tune_ptrs = 0;
     if ((st = dev_alloc(p, (void**)&p->d_tune_ptrs, need * sizeof(RunPtrs))) != GP_OK) return st;
     p->n_tune_ptrs = need;
   }
@@ -2450,11 +2508,8 @@ static gp_status tune_plan(gp_plan_s* p, void* scratch, int reps, std::map<std::
   return GP_OK;
 }
 
-gp_status gp_autotune(gp_plan_t* p, void* scratch, int32_t reps, const char* cache_path) {
-  gp_status st = usable(p);
-  if (st != GP_OK) return st;
-  if (!scratch) return fail(GP_ERR_ARG, "null scratch state");
-  if (reps < 1) return fail(GP_ERR_ARG, "reps must be >= 1");
+static gp_status autotune(gp_plan_t* p, void* scratch, int32_t reps, const char* cache_path) {
+  gp_status st;
   auto cache = read_cache(cache_path);
   const std::string arch = arch_name();
   if (!p->is_batch) {
@@ -2471,11 +2526,21 @@ gp_status gp_autotune(gp_plan_t* p, void* scratch, int32_t reps, const char* cac
           if ((st = gp_select_variant(p->runs[g.members[i]], a, chosen[a])) != GP_OK) return st;
         }
     }
-    // kernels and tables changed: the recorded graphs are stale
-    drop_graphs(p);
   }
   write_cache(cache_path, cache);
   return GP_OK;
+}
+
+gp_status gp_autotune(gp_plan_t* p, void* scratch, int32_t reps, const char* cache_path) {
+  gp_status st = usable(p);
+  if (st != GP_OK) return st;
+  if (!scratch) return fail(GP_ERR_ARG, "null scratch state");
+  if (reps < 1) return fail(GP_ERR_ARG, "reps must be >= 1");
+  if (p->is_batch) drop_graphs(p);       // kernels and tables change
+  const auto was = all_choices(p);
+  st = autotune(p, scratch, reps, cache_path);
+  if (st != GP_OK) put_all_back(p, was);
+  return st;
 }
 
 }  // extern "C"
