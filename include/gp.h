@@ -120,7 +120,8 @@ GP_API gp_status gp_init_phase(gp_plan_t* p, const double* theta, void* psi);
  * profile of width xi, phase atan2(z~, r - R)) times the conjugates of its six mirror
  * images, evaluated at ((x, y, z) permuted) - (X, Y, Z) mod 2 pi.  pairs: host,
  * npairs x 6 doubles (R, d, X, Y, Z, permutation 0..5 in the order (x,y,z), (x,z,y),
- * (y,x,z), (y,z,x), (z,x,y), (z,y,x)).  psi: dev, out.  Synchronizes. */
+ * (y,x,z), (y,z,x), (z,x,y), (z,y,x)).  psi: dev, out.  Allocates 48 + 24 max(n) bytes of
+ * device memory a pair and frees them (GP_ERR_NOMEM: psi is untouched).  Synchronizes. */
 GP_API gp_status gp_init_rvr(gp_plan_t* p, const double* pairs, int32_t npairs, double xi, void* psi);
 
 /* One directional linear sub-step S(s, L_axis) psi = F_j^-1 exp(-i alpha k_j^2 s) F_j psi,

@@ -1270,8 +1270,13 @@ gp_status gp_init_rvr(gp_plan_t* p, const double* pairs, int32_t npairs, double 
   void* d = nullptr;
   // the pairs and, after them, their coordinate tables
   const size_t nmax = (size_t)std::max(p->d.n[0], std::max(p->d.n[1], p->d.n[2]));
-  HIPCHK(p, hipMalloc(&d, h.size() * (sizeof(RP) + 3 * nmax * sizeof(double))));
-  hipError_t e = hipMemcpyAsync(d, h.data(), h.size() * sizeof(RP), hipMemcpyHostToDevice, p->stream);
+  const size_t bytes = h.size() * (sizeof(RP) + 3 * nmax * sizeof(double));
+  hipError_t e = fault_injected("alloc") ? hipErrorOutOfMemory : hipMalloc(&d, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(GP_ERR_NOMEM, "gp_init_rvr: %zu bytes for %d pairs: %s", bytes, npairs, hipGetErrorString(e));
+  }
+  e = hipMemcpyAsync(d, h.data(), h.size() * sizeof(RP), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess) {
     const double s201 = std::sqrt(201.0);
     launch_init_rvr(p->prec, d, (RP*)d + h.size(), npairs, xi, (73.0 + 3.0 * s201) / 352.0, (6.0 + s201) / 528.0, (21.0 + s201) / 96.0,

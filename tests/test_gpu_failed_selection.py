@@ -1,5 +1,6 @@
 """A selection or a tuning that finds no memory for its tables leaves the plan as it was: the same
-schedules, the same bits of the next steps, and the selection can be made later.  (The failure
+schedules, the same bits of the next steps, and the selection can be made later; a call that
+needs memory for itself leaves the plan usable.  (The failure
 is forced on the host: every device allocation is refused before it is made.)"""
 import pytest
 
@@ -78,3 +79,20 @@ def test_failed_tuning_changes_nothing(monkeypatch, prec):
         assert all(_same(a, b) for a, b in zip(again, ref))
     plan.close()
     bp.close()
+
+
+def test_vortex_rings_without_memory(monkeypatch):
+    """The pairs and their coordinates need device memory for the call."""
+    import paper_2003_03590_amd as gp
+    plan = gp.Plan((24, 16, 8), 0.3, 4.0, 0.01, "c128")
+    pairs = [(1.5, 3.0, 1.0, 2.0, 3.0, 4), (1.0, 2.0, 4.0, 5.0, 0.5, 1)]
+    ref = plan.init_rvr(pairs, 0.3)
+    out = torch.full_like(ref, 7.0)
+    monkeypatch.setenv("GP_FAULT_INJECT", "alloc")
+    with pytest.raises(gp.GPError) as ei:
+        plan.init_rvr(pairs, 0.3, out=out)
+    assert ei.value.status == gp._lib.GP_ERR_NOMEM
+    monkeypatch.delenv("GP_FAULT_INJECT")
+    assert bool((out == 7.0).all())
+    assert _same(plan.init_rvr(pairs, 0.3, out=out), ref)          # the plan is still usable
+    plan.close()
