@@ -33,7 +33,7 @@ WORKLOAD = "tg256"
 DIAG_EVERY = 100
 
 
-def pass_traffic(name="axis_pass_tg256_traffic.json", schedules=None):
+def pass_traffic(name="chain_tg256_traffic.json", schedules=None):
     """HBM bytes per axis-pass launch from a committed rocprofv3 counter summary
     (FETCH_SIZE and WRITE_SIZE scaled by a plain copy of known size), or None when
     the kernel sources changed since the counters were taken, or when `schedules`
@@ -48,9 +48,8 @@ def pass_traffic(name="axis_pass_tg256_traffic.json", schedules=None):
         if h.hexdigest() != rec["source_sha256"]:
             return None
         if schedules is not None:
-            for ax, sched in zip(rec["axes"], schedules):
-                shape = " ".join(sched.split()[:4])          # "N=.. T=.. W=.. R=.."
-                if shape not in ax["kernel"]:
+            for prof, sched in zip(rec["schedules"], schedules):
+                if prof.split()[:4] != sched.split()[:4]:    # "N=.. T=.. W=.. R=.."
                     return None
         return rec["traffic_bytes_per_launch"]
     except (OSError, KeyError, ValueError):
@@ -58,10 +57,11 @@ def pass_traffic(name="axis_pass_tg256_traffic.json", schedules=None):
 
 
 def chain_passes(plan, steps):
-    """Passes of one step_n call: with the layout-rotating forms three per linear step; else
-    each nonlinear rotation sits in a pass between the two linear sub-steps of one axis
-    (turning pass), which leaves one middle pass per linear step and the two ends."""
-    if plan.schedule(5).startswith("layout: rotating"):
+    """Passes of one step_n call: with the layout-rotating forms and without turning passes
+    three per linear step; else each nonlinear rotation sits in a pass between the two linear
+    sub-steps of one axis (turning pass), which leaves one middle pass per linear step and the
+    two ends."""
+    if plan.schedule(5).startswith("layout: rotating") or plan.schedule(4).endswith("plain"):
         return 3 * (steps + 1)
     return 2 * (steps + 1) + 1
 
@@ -272,11 +272,11 @@ def large_form(gp, torch, I, steps=5):
                         "per_launch": "one axis pass: reads and writes the whole state once (2 N^3 S bytes)",
                         "traffic": (pass_traffic("mixed_pass_rvr1024_traffic.json") if mixed else
                                     pass_traffic("rot_pass_rvr1024_traffic.json") if rot else
-                                    pass_traffic("axis_pass_rvr1024_traffic.json",
+                                    pass_traffic("chain_rvr1024_traffic.json",
                                                  [plan.schedule(ax) for ax in range(3)])),
-                        "traffic_source": "profiles/%s_pass_rvr1024_traffic.json (null once the kernel "
+                        "traffic_source": "profiles/%s_rvr1024_traffic.json (null once the kernel "
                                           "sources or schedules differ from the profiled ones)"
-                                          % ("mixed" if mixed else "rot" if rot else "axis"),
+                                          % ("mixed_pass" if mixed else "rot_pass" if rot else "chain"),
                         "mean_launch_us": ms * 1e3 / launches,
                         "copy_gbs": copy_gbs, "frac_of_copy": gbs / copy_gbs,
                         "copy": "gp_copy_state: read 8 GiB, write 8 GiB, one 16-byte unit per lane "
@@ -334,14 +334,15 @@ def argle_form(gp, torch, I, steps=200, warmup=20):
     return out
 
 
-def passes_mode(gp, torch, spec, reps, tune=False, variants=None, rotating=False):
+def passes_mode(gp, torch, spec, reps, tune=False, variants=None, rotating=False, chain=False):
     """Each axis pass (propagator sub-step S(s, L_j)) `reps` times on a random
     N^3 field, then `reps` plain device copies of the same bytes (gp_copy_state:
     the bandwidth reference, and the calibration of the FETCH_SIZE / WRITE_SIZE
     counters); prints one JSON line of event timings.  With `tune`, the schedules
     are autotuned first; `variants` (one schedule variant per axis) fixes them
     instead, e.g. to those a timed run selected.  With `rotating`, the passes are
-    the layout-rotating ones: `reps` calls of one Strang step (six passes)."""
+    the layout-rotating ones: `reps` calls of one Strang step (six passes).  With `chain`,
+    those of the running chain: `reps` calls of five Strang steps."""
     n, prec = spec.split(":")
     n = int(n)
     plan = gp.Plan(n, 0.05, 40.0, 1e-3, prec)
@@ -370,7 +371,11 @@ def passes_mode(gp, torch, spec, reps, tune=False, variants=None, rotating=False
         b.record(st)
         torch.cuda.synchronize()
         return a.elapsed_time(b) / k * 1e3
-    if rotating:
+    if chain:
+        us = timed(lambda: plan.step_n(psi, 5), reps) / chain_passes(plan, 5)
+        out["chain_us"] = us
+        out["chain_GBs"] = 2 * n ** 3 * S / us / 1e3
+    elif rotating:
         us = timed(lambda: plan.step_n(psi, 1), reps) / 6
         out["rot_us"] = us
         out["rot_GBs"] = 2 * n ** 3 * S / us / 1e3
@@ -468,6 +473,7 @@ def main(argv=None):
     ap.add_argument("--reps", type=int, default=5)
     ap.add_argument("--tune", action="store_true", help="with --passes: autotune the schedules first")
     ap.add_argument("--rotating", action="store_true", help="with --passes: the layout-rotating passes")
+    ap.add_argument("--chain", action="store_true", help="with --passes: the running chain of gp_step_n")
     ap.add_argument("--variants", default=None, metavar="VX,VY,VZ",
                     help="with --passes: schedule variant of each axis (as reported by a timed run)")
     a = ap.parse_args(argv)
@@ -491,7 +497,8 @@ def main(argv=None):
     import paper_2003_03590_amd as gp
 
     if a.passes:
-        return passes_mode(gp, torch, a.passes, a.reps, tune=a.tune, variants=a.variants, rotating=a.rotating)
+        return passes_mode(gp, torch, a.passes, a.reps, tune=a.tune, variants=a.variants, rotating=a.rotating,
+                           chain=a.chain)
     if a.argle:
         print(json.dumps(argle_form(gp, torch, I)))
         return 0

@@ -24,13 +24,11 @@ def _same(a, b):
                                                 ((48, 48, 2), 3, 1), ((32, 32, 32), 5, 1), ((32, 32, 32), 5, 2)])
 def test_failed_selection_changes_nothing(monkeypatch, shape, axis, variant, prec):
     import paper_2003_03590_amd as gp
+    if axis == 3 and prec == "c64":            # 48 points start with the plane pass there
+        shape = (96, 96, 2)
     plan = gp.Plan(shape, 0.3, 4.0, 0.01, prec)
     if axis != 3:
         plan.select_variant(4, 0)              # separate passes
-    elif prec == "c64":
-        pytest.skip("48 points complex64 start with the plane tables built")
-    if axis < 3 and gp.lib().gp_variant_count(shape[axis], plan.prec) < 2:
-        pytest.skip("one schedule")
     psi0 = _state(shape, plan)
     before = plan.step_n(psi0.clone(), 3)
     names = [plan.schedule(a) for a in range(6)]
