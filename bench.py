@@ -49,7 +49,7 @@ def pass_traffic(name="chain_tg256_traffic.json", schedules=None):
             return None
         if schedules is not None:
             for prof, sched in zip(rec["schedules"], schedules):
-                if prof.split()[:4] != sched.split()[:4]:    # "N=.. T=.. W=.. R=.."
+                if prof and prof.split()[:4] != sched.split()[:4]:   # "N=.. T=.. W=.. R=..", null: unused
                     return None
         return rec["traffic_bytes_per_launch"]
     except (OSError, KeyError, ValueError):
