@@ -161,3 +161,28 @@ def test_tuning_starts_from_a_state_of_its_own():
     assert bool(torch.isfinite(torch.view_as_real(scratch)).all())
     plan.close()
     bp.close()
+
+
+@pytest.mark.parametrize("coef", [0.04, 0.5], ids=["small", "mixed"])
+@pytest.mark.parametrize("shape", [(96, 48, 24), (24, 64, 1), (1, 48, 1), (192, 6, 4), (4, 384, 6), (2, 6, 768)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_adjoint_on_axes_of_several_stages(shape, coef):
+    """The passes that store the tape and those that rotate by it, along axes whose schedules have
+    two and three stages, against the oracle; one, two and three real axes.  The bound is 1e-12, a
+    few hundred times one step's round-off, times the growth of an error through n adjoint
+    rotations, each of which multiplies by up to 1 + 2 coef |phi|^2 (|phi|^2 of about 2)."""
+    import paper_2003_03590_amd as gp
+    from oracle import adjoint as OA
+    alpha, dt = 0.3, 0.01
+    beta = coef / dt
+    psi0, lam0 = I.random_field(shape[::-1], seed=61), I.random_field(shape[::-1], seed=62)
+    plan = gp.Plan(shape, alpha, beta, dt, "c128")
+    for n in (1, 2, 5):
+        lam = torch.from_numpy(lam0).to(DEV)
+        plan.adjoint_step_n(torch.from_numpy(psi0).to(DEV), lam, n)
+        states, ref = OA.forward_states(psi0, alpha, beta, dt, n), lam0
+        for k in range(n - 1, -1, -1):
+            ref = OA.step_adjoint(states[k], ref, alpha, beta, dt)
+        err = np.linalg.norm(lam.cpu().numpy() - ref) / np.linalg.norm(ref)
+        assert err < 1e-12 * (1 + 4 * coef) ** n, n
+    plan.close()
